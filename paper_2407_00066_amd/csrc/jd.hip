@@ -1022,31 +1022,133 @@ __global__ void jd_iota_kernel(int32_t* out, int n) {
   for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) out[e] = e;
 }
 
-// ||B_i A_i||_F^2 = sum_{l,l'} (B_i^T B_i)[l][l'] (A_i A_i^T)[l][l'], one
-// workgroup per LoRA; also w2[i] = 1 / norms2[i] and w[i] = 1 / ||B_i A_i||.
-__global__ __launch_bounds__(kJT) void jd_norms_kernel(const float* A, const float* B, int r_l, int d_in,
+// ||B_i A_i||_F^2 = sum_{l,l'} (B_i^T B_i)[l][l'] (A_i A_i^T)[l][l'], and
+// w2[i] = 1 / norms2[i], w[i] = 1 / ||B_i A_i||.
+//
+// Bound by the one read of A and B.  A workgroup takes 16 NBL rows of A and
+// columns of B: one LoRA (r_l = 16 NBL) or 16 / r_l of them, whose Gram
+// matrices are then the blocks on the diagonal of one 16 x 16 product.  Both
+// operands of a Gram product are the same rows, so a lane's value serves as
+// both, and a lane may hold any k as long as its 16 rows agree: A goes in as
+// 16-byte loads (four k per lane), B, whose rows run along k, as 4-byte loads
+// of 64 consecutive floats.  The four waves take a quarter of the reduction
+// each, kNormLoads loads in flight per wave, and add their tiles in wave order.
+// 1000 LoRAs of rank 16, 4096 x 4096: 3130 -> 110 us, 4.9 TB/s.
+constexpr int kNormLoads = 8;
+
+// g += X X^T over this wave's share of `steps` steps; load(block, step) gives
+// a lane's V values of row block `block` (KV consecutive products per step).
+template <int NBL, int KV, typename LD>
+__device__ __forceinline__ void gram_share(int steps, const LD& load, f32x4 (&g)[NBL][NBL]) {
+  constexpr int U = kNormLoads / NBL;                // steps whose loads go out together
+  const int wave = threadIdx.x >> 6;
+  const int lo = steps * wave / (kJT / 64), hi = steps * (wave + 1) / (kJT / 64);
+  for (int s = lo; s < hi; s += U) {
+    float x[U][NBL][KV];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int b = 0; b < NBL; ++b) load(b, s + u, s + u < hi, x[u][b]);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int v = 0; v < KV; ++v)
+#pragma unroll
+        for (int i = 0; i < NBL; ++i)
+#pragma unroll
+          for (int j = 0; j < NBL; ++j) g[i][j] = mfma4(x[u][i][v], x[u][j][v], g[i][j]);
+  }
+}
+
+// dst [16 NBL][16 NBL] = sum of the waves' g, in wave order
+template <int NBL>
+__device__ __forceinline__ void gram_sum(const f32x4 (&g)[NBL][NBL], float* dst) {
+  constexpr int R = 16 * NBL;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int fr = lane & 15, fk = lane >> 4;
+  for (int w = 0; w < kJT / 64; ++w) {
+    if (wave == w) {
+#pragma unroll
+      for (int i = 0; i < NBL; ++i)
+#pragma unroll
+        for (int j = 0; j < NBL; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            float* d = dst + (16 * i + 4 * fk + v) * R + 16 * j + fr;
+            *d = w == 0 ? g[i][j][v] : *d + g[i][j][v];
+          }
+    }
+    __syncthreads();
+  }
+}
+
+template <int NBL>
+__global__ __launch_bounds__(kJT) void jd_norms_kernel(const float* A, const float* B, int n, int r_l, int d_in,
                                                        int d_out, float* norms2, float* w2, float* w) {
-  __shared__ float ga[64 * 64], gb[64 * 64];
-  const int i = blockIdx.x;
-  const float* Ai = A + static_cast<int64_t>(i) * r_l * d_in;
-  const float* Bi = B + static_cast<int64_t>(i) * d_out * r_l;
-  const int nn = r_l * r_l;
-  for (int e = threadIdx.x; e < nn; e += kJT) {
-    const int l = e / r_l, l2 = e - l * r_l;
-    float sa = 0.f, sb = 0.f;
-    for (int c = 0; c < d_in; ++c) sa = fmaf(Ai[static_cast<int64_t>(l) * d_in + c], Ai[static_cast<int64_t>(l2) * d_in + c], sa);
-    for (int o = 0; o < d_out; ++o) sb = fmaf(Bi[static_cast<int64_t>(o) * r_l + l], Bi[static_cast<int64_t>(o) * r_l + l2], sb);
-    ga[e] = sa;
-    gb[e] = sb;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
+  constexpr int R = 16 * NBL;
+  __shared__ float ga[R * R], gb[R * R];
+  const int lpw = R / r_l;                           // LoRAs of this workgroup: 1, or 16 / r_l
+  const int i0 = blockIdx.x * lpw, nl = min(lpw, n - i0);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int fr = lane & 15, fk = lane >> 4;
+  f32x4 g[NBL][NBL];
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < NBL; ++i)
+#pragma unroll
+      for (int j = 0; j < NBL; ++j) g[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  const bool in = fr / r_l < nl || NBL > 1;          // this lane's LoRA exists
+  // A: rows (LoRA, l) are contiguous; step s covers k = 16 s .. 16 s + 15
+  clear();
+  const float* ar = A + (static_cast<int64_t>(i0) * r_l + fr) * d_in;
+  gram_share<NBL, 4>((d_in + 15) / 16, [&](int b, int s, bool ok, float (&x)[4]) {
+    const int k = 16 * s + 4 * fk;
+    float4 q = {0.f, 0.f, 0.f, 0.f};
+    if (ok && in && k < d_in) q = *reinterpret_cast<const float4*>(ar + static_cast<int64_t>(16 * b) * d_in + k);
+    x[0] = q.x; x[1] = q.y; x[2] = q.z; x[3] = q.w;
+  }, g);
+  gram_sum<NBL>(g, ga);
+  // B^T: rows (LoRA, l) are columns of B_i; step s covers k = 4 s .. 4 s + 3
+  clear();
+  const int ql = fr / r_l;                           // 0 when NBL > 1
+  const float* br = B + static_cast<int64_t>(i0 + ql) * d_out * r_l + (fr - ql * r_l);
+  gram_share<NBL, 1>((d_out + 3) / 4, [&](int b, int s, bool ok, float (&x)[1]) {
+    const int o = 4 * s + fk;
+    x[0] = (ok && in && o < d_out) ? br[static_cast<int64_t>(o) * r_l + 16 * b] : 0.f;
+  }, g);
+  gram_sum<NBL>(g, gb);
+  // wave q sums LoRA q's entries: lanes strided, then the lanes in order of a tree
+  if (wave < nl) {
     float s = 0.f;
-    for (int e = 0; e < nn; ++e) s = fmaf(ga[e], gb[e], s);
-    norms2[i] = s;
-    if (w2) w2[i] = 1.f / s;
-    if (w) w[i] = 1.f / sqrtf(s);
+    for (int e = lane; e < r_l * r_l; e += 64) {
+      const int a = (wave * r_l + e / r_l) * R + wave * r_l + e % r_l;
+      s = fmaf(ga[a], gb[a], s);
+    }
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) s += __shfl_down(s, h);
+    if (lane == 0) {
+      norms2[i0 + wave] = s;
+      if (w2) w2[i0 + wave] = 1.f / s;
+      if (w) w[i0 + wave] = 1.f / sqrtf(s);
+    }
   }
+}
+
+hipError_t launch_norms(const float* A, const float* B, const cts_jd_problem* p, float* norms2, float* w2, float* w,
+                        hipStream_t st) {
+  const int lpw = p->r_lora < 16 ? 16 / p->r_lora : 1;
+  const dim3 grid((p->n + lpw - 1) / lpw);
+  if (p->r_lora <= 16)
+    hipLaunchKernelGGL(jd_norms_kernel<1>, grid, dim3(kJT), 0, st, A, B, p->n, p->r_lora, p->d_in, p->d_out, norms2,
+                       w2, w);
+  else if (p->r_lora == 32)
+    hipLaunchKernelGGL(jd_norms_kernel<2>, grid, dim3(kJT), 0, st, A, B, p->n, p->r_lora, p->d_in, p->d_out, norms2,
+                       w2, w);
+  else
+    hipLaunchKernelGGL(jd_norms_kernel<4>, grid, dim3(kJT), 0, st, A, B, p->n, p->r_lora, p->d_in, p->d_out, norms2,
+                       w2, w);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------ k-means pieces
@@ -1498,9 +1600,7 @@ hipError_t store_bases(Jd& j, float* U, float* Vt) {
 
 hipError_t norms(Jd& j, const float* A, const float* B) {
   const cts_jd_problem* p = j.p;
-  hipLaunchKernelGGL(jd_norms_kernel, dim3(p->n), dim3(kJT), 0, j.st, A, B, p->r_lora, p->d_in, p->d_out,
-                     j.at<float>(j.pl.off_n2), j.at<float>(j.pl.off_w2), j.at<float>(j.pl.off_w));
-  return hipGetLastError();
+  return launch_norms(A, B, p, j.at<float>(j.pl.off_n2), j.at<float>(j.pl.off_w2), j.at<float>(j.pl.off_w), j.st);
 }
 
 // `iters` iterations (early stop below tau, waiting per iteration) on the
@@ -1692,9 +1792,7 @@ int cts_lora_norms2(const cts_jd_problem* p, const float* A, const float* B, flo
   Jd j{p, {}, static_cast<char*>(workspace), static_cast<hipStream_t>(stream)};
   cts::plan_jd(p, 0, &j.pl);
   if (workspace_bytes < j.pl.total) return CTS_ERR_WORKSPACE;
-  hipLaunchKernelGGL(cts::jd_norms_kernel, dim3(p->n), dim3(cts::kJT), 0, j.st, A, B, p->r_lora, p->d_in,
-                     p->d_out, norms2, nullptr, nullptr);
-  return hipGetLastError() == hipSuccess ? CTS_OK : CTS_ERR_HIP;
+  return cts::launch_norms(A, B, p, norms2, nullptr, nullptr, j.st) == hipSuccess ? CTS_OK : CTS_ERR_HIP;
 }
 
 int cts_jd_full(const cts_jd_problem* p, const float* A, const float* B, const float* U0, const float* Vt0,
