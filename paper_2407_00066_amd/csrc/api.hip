@@ -144,7 +144,7 @@ int plan_piece(const cts_problem* p, bool compressed, Plan* pl) {
   int max_split = 1;
   if (p->dtype == CTS_F32) {
     pl->main_tile = Tile::F32;
-  } else if (T >= 2048) {
+  } else if (T >= 2048 && p->d_in >= 128) {       // (its prologue loads four whole 32-deep k-tiles)
     pl->main_tile = Tile::Large;
   } else if (T > 64 && (tiles_of(Tile::Wide) >= 192 || p->d_in >= 8192)) {
     pl->main_tile = Tile::Wide;

@@ -18,12 +18,16 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
   return __uint_as_float(static_cast<uint32_t>(b) << 16);
 }
 
-// float -> bfloat16, round to nearest, ties to even; NaN stays NaN.
+// float -> bfloat16, round to nearest, ties to even; NaN stays NaN.  gfx950
+// converts two at a time (v_cvt_pk_bf16_f32); the same rounding by integer
+// arithmetic takes seven instructions a value.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t f32_to_bf16_pair(float lo, float hi) {
+  const bf16x2 v = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
+  return __builtin_bit_cast(uint32_t, v);
+}
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return static_cast<uint16_t>((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return static_cast<uint16_t>(u >> 16);
+  return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f));
 }
 
 // ---------------------------------------------------------------- bucketing
@@ -135,8 +139,8 @@ struct GemmParams {
   int64_t part_ld;
 };
 
-// Tile shapes of the segmented GEMM (BM x BN x BK).  Large 256x256x64, Wide
-// 256x128x64, Mid 128x128x64, Narrow 128x64x128, Decode 64x64x128 and Shrink
+// Tile shapes of the segmented GEMM (BM x BN x BK).  Large 256x256x32 (the
+// prefill kernel), Wide 256x128x64, Mid 128x128x64, Narrow 128x64x128, Decode 64x64x128 and Shrink
 // 64x64x64 load their k-tiles straight into LDS; Small 64x64x64 stages them
 // in registers; F32 is the fp32 path.  Explicit token tiles are taken by
 // the 64-wide ones (Decode, Shrink, Small, F32).

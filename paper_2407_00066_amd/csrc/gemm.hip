@@ -371,10 +371,10 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void seg_gemm_kernel(const GemmP
         const f32x4 lo = *reinterpret_cast<const f32x4*>(s);
         const f32x4 hi = *reinterpret_cast<const f32x4*>(s + 4);
         uint4 v;
-        v.x = f32_to_bf16(lo[0]) | (static_cast<uint32_t>(f32_to_bf16(lo[1])) << 16);
-        v.y = f32_to_bf16(lo[2]) | (static_cast<uint32_t>(f32_to_bf16(lo[3])) << 16);
-        v.z = f32_to_bf16(hi[0]) | (static_cast<uint32_t>(f32_to_bf16(hi[1])) << 16);
-        v.w = f32_to_bf16(hi[2]) | (static_cast<uint32_t>(f32_to_bf16(hi[3])) << 16);
+        v.x = f32_to_bf16_pair(lo[0], lo[1]);
+        v.y = f32_to_bf16_pair(lo[2], lo[3]);
+        v.z = f32_to_bf16_pair(hi[0], hi[1]);
+        v.w = f32_to_bf16_pair(hi[2], hi[3]);
         const int64_t row = p.out_perm ? t_perm[jl] : static_cast<int64_t>(j0 + jl);
         *reinterpret_cast<uint4*>(out + row * p.ldo + m0 + mc) = v;
       }
@@ -440,44 +440,26 @@ struct DmaCfg {
 // DIRECT: the epilogue writes straight from the accumulators (4 consecutive
 // output features of one token per lane) instead of staging the tile in LDS;
 // used when the fp32 tile does not fit in LDS.
-// PFD > 0 (rings of two or three stages): during k-tile t the workgroup also
-// touches, one 4-byte load per cache line, its share of the weight rows and
-// token rows of dense k-tile t + P - 1 + PFD, so that the LDS loads of that
-// k-tile find them in L2.  Tiles of one XCD come in blocks of 8 row tiles
-// (tile_of_block), so the 8 workgroups on one column tile each take every
-// 8th token row; the WSPL workgroups on one row tile (4 with 256 tiles of
-// 256x256) each take every WSPL-th weight row.
-// RANKED: the segments have ranks (p.seg_rank, with each column's rank in
-// p.sorted_rank): a cluster run takes only its adapter k-tiles below its
-// rank, from a schedule listed in LDS.
 // MODS: the launch may hold several modules (p.n_mod > 0).
-template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT, int PFD = 0, int WSPL = 1,
-          int FSORT = 0, int RANKED = 0, int MODS = 0>
+template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT, int FSORT = 0, int MODS = 0>
 __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const GemmParams p) {
   using C = DmaCfg<BM, BN, BK, WM, WN, MB, P, DIRECT>;
-  static_assert(PFD == 0 || P <= 3, "prefetch wait counts cover rings of two or three stages");
-  constexpr int NPF = PFD > 0 ? 1 : 0;                     // prefetch loads per wave per k-tile
-  constexpr int PFW = C::NW / 2;                           // waves prefetching weight rows
   using MT = MfmaTraits<bf16_t, MB>;
   typedef typename MT::accv accv;
   constexpr uint32_t ELT = 2;
 
   __shared__ __attribute__((aligned(1024))) char smem[C::SMEM];
   __shared__ int32_t t_perm[BN];
-  __shared__ int32_t t_seg[BN];
-  __shared__ int32_t run_start[BN + 1];
-  __shared__ int32_t wave_runs[C::NW];
-  __shared__ uint2 sched[RANKED ? 2 * BN : 1];             // adapter k-tiles (K1 <= 2 BK)
-  __shared__ int32_t t_rank[RANKED ? BN : 1];
-  __shared__ int32_t n_sched_s;
-  __shared__ uint32_t pf_sink[PFD > 0 ? 64 : 1];
+  // adapter k-tiles (K1 <= 2 BK) closed by an entry of rank 0, and their number
+  __shared__ __attribute__((aligned(8))) uint64_t sched[2 * BN + 1];
+  __shared__ uint32_t n_sched_s;
   constexpr int FS = FSORT ? kFuseSortMaxT : 1;
   __shared__ uint64_t fs_raw[FS];                          // (key << 8) | token, in token order
   __shared__ uint32_t fs_key[FS];                          // keys, sorted
   __shared__ int32_t fs_perm[FS], fs_tile[FS + 1];
   __shared__ int32_t fs_cnt[2];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   // FSORT: bucketing of the (at most kFuseSortMaxT) tokens in LDS.  The key
   // is cluster << bits_n | adapter (the adapter alone without a cluster
@@ -635,19 +617,6 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   const int m0 = mt * BM;
   static_assert(BN <= C::NT, "one token column per thread");
 
-  // ---- token columns of this tile (loads only; stored to LDS below) -------
-  int v_perm = 0, v_seg = 0, v_rank = 0;
-  if (tid < jn) {
-    if (FSORT) {
-      v_perm = fs_perm[j0 + tid];
-      v_seg = static_cast<int>(fs_key[j0 + tid] >> fs_cshift);
-    } else {
-      v_perm = p.perm[j0 + tid];
-      v_seg = p.sorted_seg ? p.sorted_seg[j0 + tid] : 0;
-      if (RANKED) v_rank = p.sorted_rank[j0 + tid];
-    }
-  }
-
   // ---- load mapping: this lane's row and chunk in each 1 KB load ------------
   // load j of wave w covers tile rows [RPI*(w + NW*j), +RPI) of A (j < QA) or
   // B; lane l takes row +l/CH and global chunk (l%CH) ^ key(row), stored at
@@ -697,132 +666,129 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   const int nd_full = nd - ((nd > 0 && d_hi * BK > K0) ? 1 : 0);
   auto dk = [&](int i) __attribute__((always_inline)) { return d_lo + i; };   // dense k-tile at position i
 
-  // The weight rows do not depend on the token order: when the first P-1
-  // k-tiles are whole dense tiles, their weight loads go out now, in flight
-  // while the token columns and cluster runs are set up (the token operand's
-  // loads follow once its rows are known).  With four stages the first
-  // k-tile's wait below is adjusted for this order.
-  const bool early = (P <= 4) && nd_full >= P - 1;
-  if (early) {
+  // ---- the tokens of this lane's B rows, this thread's column for the
+  // epilogue and, for wave 0, the clusters and ranks of columns lane + 64 q
+  // (indices past the tile repeat its last column: no branch around the loads,
+  // and each waits for the loads before it only)
+  constexpr int NQ = (BN + 63) / 64;
+  uint32_t tok[C::QB];
 #pragma unroll
-    for (int st = 0; st < P - 1; ++st)
+  for (int j = 0; j < C::QB; ++j) {
+    const int jc = j0 + min(C::RPI * (wave + C::NW * j) + lrow, jn - 1);
+    tok[j] = static_cast<uint32_t>(FSORT ? fs_perm[jc] : p.perm[jc]);
+  }
+  const bool adapters = !tlist && p.sorted_seg && K1 > 0;
+  int v_perm = 0, v_seg[NQ], v_rank[NQ];
 #pragma unroll
-      for (int j = 0; j < C::QA; ++j)
-        load16_lds(rA0, smem_a + st * C::SB + j * C::NW * 1024, a0_v[j],
-                   static_cast<uint32_t>(dk(st) * BK) * ELT);
+  for (int q = 0; q < NQ; ++q) { v_seg[q] = 0; v_rank[q] = K1; }
+  if (!tlist) v_perm = p.perm[j0 + min(tid, jn - 1)];
+  if (wave == 0 && adapters) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) v_seg[q] = p.sorted_seg[j0 + min(lane + 64 * q, jn - 1)];
+    if (p.seg_rank)
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) v_rank[q] = p.sorted_rank[j0 + min(lane + 64 * q, jn - 1)];
   }
 
-  // ---- token columns: perm, segment, and segment runs ----------------------
-  if (tid < BN) {
-    t_perm[tid] = v_perm;
-    t_seg[tid] = v_seg;
-    if (RANKED) t_rank[tid] = v_rank;
-  }
-  __syncthreads();
-  int n_runs = 0;
-  for (int base = 0; base < BN; base += C::NT) {
-    const int i = base + tid;
-    const bool st = (i < jn) && (i == 0 || t_seg[i] != t_seg[i - 1]);
-    const uint64_t bal = __ballot(st);
-    if (lane == 0) wave_runs[wave] = __popcll(bal);
-    __syncthreads();
-    int before = 0, total = 0;
+  // The weight rows do not depend on the token order: the first P - 1 dense
+  // k-tiles' weight loads go out now, their token loads as soon as the lane's
+  // tokens are known, and the cluster runs are listed while both are on their
+  // way.  (A k-tile past the dense ones is loaded below, once the list is
+  // there; its loads here are masked.)  With four stages the first k-tile's
+  // wait in the loop is adjusted for this order.
+  auto edge = [&](int st) __attribute__((always_inline)) {
+    return st < nd_full ? 0u : (st < nd && static_cast<uint32_t>(dk(st) * BK) + celem < static_cast<uint32_t>(K0) ? 0u : kOob);
+  };
 #pragma unroll
-    for (int w = 0; w < C::NW; ++w) {
-      const int c = wave_runs[w];
-      before += (w < wave) ? c : 0;
-      total += c;
-    }
-    if (st) {
-      const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-      run_start[n_runs + before + __popcll(bal & lt)] = i;
-    }
-    n_runs += total;
-    __syncthreads();
-  }
-  if (!(p.sorted_seg && K1 > 0)) n_runs = 0;
-  if (tid == 0) run_start[n_runs] = jn;
-  __syncthreads();
-  // this split's runs: q_first + i q_step, i < my_runs
-  const int my_runs = (n_runs > q_first) ? (n_runs - q_first + q_step - 1) / q_step : 0;
-
-  // ---- k-tile schedule: the dense tiles, then each cluster run's tiles ------
-  // With ranks, run q takes only its k-tiles of this split below its rank
-  // (the k-tiles past a cluster's rank are not visited).  Wave 0 lists the
-  // adapter k-tiles in LDS, run by run: .x = first column | columns << 9 |
-  // k-tile << 18, .y = segment | rank << 16.
-  int n_sched = my_runs * ns;
-  if (RANKED && my_runs > 0 && ns > 0) {
-    if (wave == 0) {
-      int tot = 0;
-      for (int base = 0; base < my_runs; base += 64) {
-        const int q = q_first + (base + lane) * q_step;
-        int c = 0;
-        uint32_t ex = 0, ey = 0;
-        if (base + lane < my_runs) {
-          const int lo = run_start[q], hi = run_start[q + 1];
-          const int seg = t_seg[lo];
-          const int kl = min(max(t_rank[lo], 0), K1);
-          c = max(0, min(s_hi, (kl + BK - 1) / BK) - s_lo);
-          ex = static_cast<uint32_t>(lo) | (static_cast<uint32_t>(hi - lo) << 9);
-          ey = static_cast<uint32_t>(seg) | (static_cast<uint32_t>(kl) << 16);
-        }
-        int x = c;                                          // inclusive scan over the wave
+  for (int st = 0; st < P - 1; ++st) {
+    const uint32_t m = edge(st);
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-          const int y = __shfl_up(x, d);
-          if (lane >= d) x += y;
-        }
-        for (int i = 0; i < c; ++i)
-          sched[tot + x - c + i] = make_uint2(ex | (static_cast<uint32_t>(s_lo + i) << 18), ey);
-        tot += __shfl(x, 63);
-      }
-      if (lane == 0) n_sched_s = tot;
-    }
-    __syncthreads();
-    n_sched = n_sched_s;
+    for (int j = 0; j < C::QA; ++j)
+      load16_lds(rA0, smem_a + st * C::SB + j * C::NW * 1024, a0_v[j] | m,
+                 static_cast<uint32_t>(dk(st) * BK) * ELT);
   }
-  const int ntiles = nd + n_sched;
-
   // ---- token operand rows -------------------------------------------------
 #pragma unroll
   for (int j = 0; j < C::QB; ++j) {
     const int jl = C::RPI * (wave + C::NW * j) + lrow;
-    const uint32_t tok = static_cast<uint32_t>(t_perm[jl]);
-    const uint32_t r1 = p.b1_gather ? tok : static_cast<uint32_t>(j0 + jl);
+    const uint32_t r1 = p.b1_gather ? tok[j] : static_cast<uint32_t>(j0 + jl);
     b_jl[j] = jl;
-    const uint32_t r0 = b0_gather ? tok : static_cast<uint32_t>(j0 + jl);
+    const uint32_t r0 = b0_gather ? tok[j] : static_cast<uint32_t>(j0 + jl);
     b0_v[j] = (jl < jn) ? r0 * static_cast<uint32_t>(ldb0) * ELT + cbytes : kOob;
     b1_v[j] = r1 * static_cast<uint32_t>(p.ldb1) * ELT + cbytes;
   }
   const __amdgpu_buffer_rsrc_t rB0 = make_rsrc(B0, b0_bytes);
   const __amdgpu_buffer_rsrc_t rB1 = make_rsrc(B1v, b1v_bytes);
-  int lt = 0, lq = 0, lkt = s_lo;
+#pragma unroll
+  for (int st = 0; st < P - 1; ++st) {
+    const uint32_t m = edge(st);
+#pragma unroll
+    for (int j = 0; j < C::QB; ++j)
+      load16_lds(rB0, smem_b + st * C::SB + j * C::NW * 1024, b0_v[j] | m,
+                 static_cast<uint32_t>(dk(st) * BK) * ELT);
+  }
 
-  // L2 prefetch: this lane's weight row or token row (kOob when none)
-  uint32_t pf_v = kOob;
-  const bool pf_w = __builtin_amdgcn_readfirstlane(wave) < PFW;
-  if (PFD > 0) {
-    static_assert(PFD == 0 || (BM % (WSPL * PFW) == 0 && BM / WSPL / PFW <= 64 &&
-                               BN % (8 * PFW) == 0 && BN / 8 / PFW <= 64), "prefetch lanes");
-    if (pf_w) {
-      const int m = m0 + WSPL * (wave * (BM / WSPL / PFW) + lane) + (nt % WSPL);
-      if (lane < BM / WSPL / PFW && m < Mv) pf_v = static_cast<uint32_t>(m) * static_cast<uint32_t>(lda0) * ELT;
-    } else {
-      const int jl = 8 * ((wave - PFW) * (BN / 8 / PFW) + lane) + (mt_grid & 7);
-      if (lane < BN / 8 / PFW && jl < jn) {
-        const uint32_t r0 = b0_gather ? static_cast<uint32_t>(t_perm[jl]) : static_cast<uint32_t>(j0 + jl);
-        pf_v = r0 * static_cast<uint32_t>(ldb0) * ELT;
+  // ---- k-tile schedule: the dense tiles, then each cluster run's tiles ------
+  // Wave 0 finds this split's runs (q_first, q_first + q_step, ...) from its
+  // registers and lists their adapter k-tiles of this split below the run's
+  // rank: low word = first column | columns << 9 | k-tile << 18, high word =
+  // segment | rank << 16.
+  const uint32_t sched_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(sched));
+  const uint32_t count_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(&n_sched_s));
+  if (!tlist && tid < BN) lds_write4(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(t_perm)) + 4u * tid, v_perm);
+  if (wave == 0) {
+    uint32_t tot = 0;
+    if (adapters) {
+      uint64_t start[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        int prev = __shfl_up(v_seg[q], 1);
+        if (q > 0 && lane == 0) prev = __builtin_amdgcn_readlane(v_seg[q > 0 ? q - 1 : 0], 63);
+        const int col = lane + 64 * q;
+        start[q] = __ballot(col < jn && (col == 0 || v_seg[q] != prev));
+      }
+      int run0 = 0;                                         // runs that start before column 64 q
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int lo = lane + 64 * q;
+        int hi = jn;                                        // the next run's first column
+#pragma unroll
+        for (int q2 = NQ - 1; q2 > q; --q2)
+          if (start[q2]) hi = 64 * q2 + __builtin_ctzll(start[q2]);
+        const uint64_t above = start[q] & ~(lt_mask | (1ull << lane));
+        if (above) hi = 64 * q + __builtin_ctzll(above);
+        const int run = run0 + __popcll(start[q] & lt_mask);
+        const bool mine = ((start[q] >> lane) & 1ull) && run >= q_first &&
+                          (q_step == 1 || (run - q_first) % q_step == 0);
+        const int kl = min(max(v_rank[q], 0), K1);
+        const int c = mine ? max(0, min(s_hi, (kl + BK - 1) / BK) - s_lo) : 0;   // 0, 1 or 2
+        const uint64_t b0 = __ballot(c & 1), b1 = __ballot(c & 2);
+        const uint32_t at = tot + __popcll(b0 & lt_mask) + 2 * __popcll(b1 & lt_mask);
+        const uint32_t ex = static_cast<uint32_t>(lo) | (static_cast<uint32_t>(hi - lo) << 9);
+        const uint64_t ey =
+            static_cast<uint64_t>(static_cast<uint32_t>(v_seg[q]) | (static_cast<uint32_t>(kl) << 16)) << 32;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          if (i < c) lds_write8(sched_addr + 8u * (at + i), ey | (ex | (static_cast<uint32_t>(s_lo + i) << 18)));
+        tot += __popcll(b0) + 2 * __popcll(b1);
+        run0 += __popcll(start[q]);
       }
     }
+    if (lane == 0) {
+      lds_write8(sched_addr + 8u * tot, 0ull);              // rank 0: every load masked
+      lds_write4(count_addr, tot);
+    }
   }
-  // dense k-tile ti of this split (ti counted from d_lo; past the whole
-  // dense tiles the load touches nothing)
-  auto prefetch = [&](int ti) __attribute__((always_inline)) {
-    if (PFD > 0)
-      load4_lds(pf_w ? rA0 : rB0, pf_sink, (ti < nd_full) ? pf_v : kOob,
-                static_cast<uint32_t>(dk(ti) * BK) * ELT);
-  };
+  lds_barrier();
+  uint32_t n_sched_v;
+  lds_read4(n_sched_v, count_addr);
+  wait_lgkmcnt<0>();
+  pin(n_sched_v);
+  const int n_sched = __builtin_amdgcn_readfirstlane(n_sched_v);
+  const int ntiles = nd + n_sched;
+
+  int lt = 0;
+
   // Per-k-tile load state, prepared once per k-tile (the loads themselves may
   // be issued in several groups between the multiply steps).
   struct TileLoad {
@@ -830,13 +796,16 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
     uint32_t kk, kmask, span, dsel;   // kk: uniform k byte offset of the k-tile
     int lo;
   };
-  auto prep_next = [&, jn, n_runs, n_sched, nd, ntiles, s_lo, s_hi, q_first, q_step]() __attribute__((always_inline)) {
+  // the list's entry of the next k-tile to load (issued; the reader waits)
+  auto read_entry = [&](uint64_t& e) __attribute__((always_inline)) {
+    lds_read8(e, sched_addr + 8u * static_cast<uint32_t>(min(max(lt - nd, 0), n_sched)));
+  };
+  auto prep_next = [&](uint64_t entry) __attribute__((always_inline)) {
     TileLoad L;
     const bool valid = lt < ntiles;
     uint32_t k0, klim;
     if (lt < nd) {
-      // dense phase (W X): a wave-uniform branch that touches no LDS, so the
-      // steady state pays no lookup latency between barrier and multiply
+      // dense phase (W X)
       L.lo = 0;
       L.span = static_cast<uint32_t>(jn);
       L.rA = rA0;
@@ -844,39 +813,22 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
       L.dsel = 0xffffffffu;
       k0 = static_cast<uint32_t>(dk(lt) * BK);
       klim = static_cast<uint32_t>(K0);
-    } else if (RANKED) {
-      // adapter phase with ranks: the next entry of the schedule (past its
-      // end, while the ring runs dry, the loads are masked off)
-      const uint2 e = sched[min(lq, max(n_sched - 1, 0))];
-      const uint32_t ex = valid ? __builtin_amdgcn_readfirstlane(e.x) : 0u;
-      const uint32_t ey = valid ? __builtin_amdgcn_readfirstlane(e.y) : 0u;
+    } else {
+      // adapter phase (U_k Z'): the entry of one k-tile of one cluster run
+      // (past the end the closing entry, whose rank 0 masks every load)
+      const uint32_t ex = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(entry));
+      const uint32_t ey = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(entry >> 32));
       L.lo = static_cast<int>(ex & 511u);
       L.span = (ex >> 9) & 511u;
       const int seg = static_cast<int>(ey & 0xffffu);
       L.rA = make_rsrc(static_cast<const char*>(A1v) + static_cast<int64_t>(seg) * a1_seg_bytes,
                        a1_seg_bytes);
       L.rB = rB1;
-      L.dsel = 0u;
-      k0 = (ex >> 18) * BK;
-      klim = ey >> 16;
-      ++lq;
-    } else {
-      // adapter phase (U_k Z'): one cluster run of the tile per k-tile group
-      const int q = min(q_first + lq * q_step, max(n_runs - 1, 0));
-      L.lo = run_start[q];
-      const int hi = run_start[q + 1];
-      const int seg = __builtin_amdgcn_readfirstlane(t_seg[L.lo]);
-      L.rA = make_rsrc(static_cast<const char*>(A1v) + static_cast<int64_t>(seg) * a1_seg_bytes,
-                       a1_seg_bytes);
-      L.rB = rB1;
-      L.span = static_cast<uint32_t>(hi - L.lo);
       // phase select by mask arithmetic (a conditional pick between the two
       // offset arrays would make the compiler keep them in scratch memory)
       L.dsel = 0u;
-      k0 = static_cast<uint32_t>(lkt * BK);
-      klim = static_cast<uint32_t>(K1);
-      ++lkt;
-      if (lkt >= s_hi) { lkt = s_lo; ++lq; }
+      k0 = (ex >> 18) * BK;
+      klim = ey >> 16;
     }
     L.kmask = (valid && k0 + celem < klim) ? 0u : kOob;
     L.kk = k0 * ELT;
@@ -911,11 +863,6 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
       if (j + C::QA >= g0 && j + C::QA < g1)
         load16_lds(rB0, smem_b + st * C::SB + j * C::NW * 1024, b0_v[j], L.kk);
   };
-  auto load_next = [&](int st) __attribute__((always_inline)) {
-    const TileLoad L = prep_next();
-    issue(L, st, 0, C::LPT);
-  };
-
   // ---- fragment addresses ---------------------------------------------------
   const int wm = wave / WN, wn = wave % WN;
   const int fr = lane % MB, fg = lane / MB;                 // row in block, k group
@@ -958,7 +905,6 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   // load where a step has more loads than both (load-heavy, narrow tiles)
   constexpr int NSL0 = NM > NR ? NM : NR;
   constexpr int NSL = NSL0 > GPS ? NSL0 : GPS;
-  static_assert(NPF == 0 || GPS < NSL, "a slot for the prefetch");
   bf16x8 fa[2][C::FM], fb[2][C::FN];
   auto read_frag = [&](int buf, int r, uint32_t sa, uint32_t sb, uint32_t sl) __attribute__((always_inline)) {
     if (r < C::FM) lds_read16(fa[buf][r], sa + sl + r * MB * C::ROWB);
@@ -969,24 +915,22 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
     acc[i][j] = MT::mma(fa[buf][i], fb[buf][j], acc[i][j]);
   };
 
-  // prefetch of the first PFD k-tiles after the ring's (waited for with them)
-#pragma unroll
-  for (int i = 0; i < PFD; ++i) prefetch(P - 1 + i);
-  if (early) {
-    // weight loads of k-tiles 0..P-2 are out; add their token loads
-#pragma unroll
-    for (int st = 0; st < P - 1; ++st) {
-      TileLoad L;
-      L.kk = static_cast<uint32_t>(dk(st) * BK) * ELT;
-      issue_fast(L, st, C::QA, C::LPT);
+  lt = P - 1;
+  if (nd < P - 1) {
+    // k-tiles of the prologue that belong to the adapter phase: after the
+    // masked loads into their stages
+    wait_vmcnt<0>();
+    for (int st = nd; st < P - 1; ++st) {
+      lt = st;
+      uint64_t e;
+      read_entry(e);
+      wait_lgkmcnt<0>();
+      pin(e);
+      issue(prep_next(e), st, 0, C::LPT);
     }
-    lt = P - 1;
-    wait_vmcnt<(P - 2) * C::QB>();       // k-tile 0's token loads, and all weight loads
-  } else {
-#pragma unroll
-    for (int st = 0; st < P - 1; ++st) load_next(st);
-    wait_vmcnt<(P - 2) * C::LPT>();
+    wait_vmcnt<0>();
   }
+  wait_vmcnt<(P - 2) * C::QB>();         // k-tile 0's token loads, and all weight loads
   __builtin_amdgcn_s_barrier();
 #pragma unroll
   for (int r = 0; r < NR; ++r) read_frag(0, r, a_row_addr, b_row_addr, slot[0]);
@@ -997,7 +941,10 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   const int nfast = max(0, min(ntiles, nd_full - (P - 1)));
   int cur = 0;   // LDS stage of k-tile t
   int t = 0;
-  auto ktile = [&](const TileLoad L, const bool fast) __attribute__((always_inline)) {
+  auto ktile = [&](const bool fast) __attribute__((always_inline)) {
+    TileLoad L;
+    uint64_t entry = 0;
+    if (!fast) read_entry(entry);                          // waited for with the fragments
     int nst = cur + P - 1; if (nst >= P) nst -= P;         // stage of k-tile t+P-1
     int ncur = cur + 1; if (ncur >= P) ncur -= P;          // stage of k-tile t+1
     const uint32_t sa = a_row_addr + cur * C::SB, sb = b_row_addr + cur * C::SB;
@@ -1014,13 +961,21 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
       for (int i = 0; i < C::FM; ++i) pin(fa[b][i]);
 #pragma unroll
       for (int j = 0; j < C::FN; ++j) pin(fb[b][j]);
+      if (s2 == 0) {
+        if (fast) {                                        // dense k-tile lt, whole
+          L.kk = static_cast<uint32_t>(dk(lt) * BK) * ELT;
+          ++lt;
+        } else {
+          pin(entry);
+          L = prep_next(entry);
+        }
+      }
       if (s2 + 1 < C::NKS) {
 #pragma unroll
         for (int m = 0; m < NSL; ++m) {
           if (m < NM) mma(b, m);
           if (m < NR) read_frag(b ^ 1, m, sa, sb, slot[s2 + 1]);
           if (s2 < NLG && m < GPS) iss(s2 * GPS + m, s2 * GPS + m + 1);
-          if (NPF && s2 == NLG - 1 && m == GPS) prefetch(t + P - 1 + PFD);   // after every load
           __builtin_amdgcn_sched_barrier(0);
         }
       } else {
@@ -1029,14 +984,11 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
           mma(b, m);
           __builtin_amdgcn_sched_barrier(0);
         }
-        // this lane's loads of k-tile t+1.  In the early order (weight loads
+        // this lane's loads of k-tile t+1.  In the prologue's order (weight loads
         // of k-tiles 0..2, then their token loads) k-tile 1's token loads
         // are followed by k-tile 2's token loads and k-tile 3's loads only.
-        // With prefetches each k-tile's loads are followed by one prefetch
-        // load; the prologue's go out before its ring loads.
-        if (P == 4 && early && t == 0) wait_vmcnt<(P == 4 ? 2 * C::LPT - C::QA : 0)>();
-        else if (P == 3 && NPF && t == 0) wait_vmcnt<(P - 2) * C::LPT + NPF>();
-        else wait_vmcnt<(P - 2) * C::LPT + (P - 1) * NPF>();
+        if (P == 4 && t == 0) wait_vmcnt<(P == 4 ? 2 * C::LPT - C::QA : 0)>();
+        else wait_vmcnt<(P - 2) * C::LPT>();
         __builtin_amdgcn_s_barrier();                      // ... and every wave's
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -1049,13 +1001,8 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
     }
     cur = ncur;
   };
-  for (; t < nfast; ++t) {
-    TileLoad L;                                            // dense k-tile lt, whole
-    L.kk = static_cast<uint32_t>(dk(lt) * BK) * ELT;
-    ++lt;
-    ktile(L, true);
-  }
-  for (; t < ntiles; ++t) ktile(prep_next(), false);
+  for (; t < nfast; ++t) ktile(true);
+  for (; t < ntiles; ++t) ktile(false);
   wait_lgkmcnt<0>();
   wait_vmcnt<0>();
   __syncthreads();
@@ -1078,8 +1025,8 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
             *reinterpret_cast<f32x4*>(partv + (static_cast<int64_t>(ks) * p.N + j0 + jl) * part_ld + m) = val;
           } else if (p.out_dtype == 1) {
             uint2 w;
-            w.x = f32_to_bf16(val[0]) | (static_cast<uint32_t>(f32_to_bf16(val[1])) << 16);
-            w.y = f32_to_bf16(val[2]) | (static_cast<uint32_t>(f32_to_bf16(val[3])) << 16);
+            w.x = f32_to_bf16_pair(val[0], val[1]);
+            w.y = f32_to_bf16_pair(val[2], val[3]);
             *reinterpret_cast<uint2*>(static_cast<uint16_t*>(outv) + orow * ldov + m) = w;
           } else {
             *reinterpret_cast<f32x4*>(static_cast<float*>(outv) + orow * ldov + m) = val;
@@ -1123,10 +1070,10 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
         const f32x4 lo = *reinterpret_cast<const f32x4*>(s);
         const f32x4 hi = *reinterpret_cast<const f32x4*>(s + 4);
         uint4 v;
-        v.x = f32_to_bf16(lo[0]) | (static_cast<uint32_t>(f32_to_bf16(lo[1])) << 16);
-        v.y = f32_to_bf16(lo[2]) | (static_cast<uint32_t>(f32_to_bf16(lo[3])) << 16);
-        v.z = f32_to_bf16(hi[0]) | (static_cast<uint32_t>(f32_to_bf16(hi[1])) << 16);
-        v.w = f32_to_bf16(hi[2]) | (static_cast<uint32_t>(f32_to_bf16(hi[3])) << 16);
+        v.x = f32_to_bf16_pair(lo[0], lo[1]);
+        v.y = f32_to_bf16_pair(lo[2], lo[3]);
+        v.z = f32_to_bf16_pair(hi[0], hi[1]);
+        v.w = f32_to_bf16_pair(hi[2], hi[3]);
         const int64_t row = p.out_perm ? t_perm[jl] : static_cast<int64_t>(j0 + jl);
         *reinterpret_cast<uint4*>(out + row * ldov + m0 + mc) = v;
       }
@@ -1145,8 +1092,398 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   }
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT = 0, int PFD = 0,
-          int WSPL = 1, int FSORT = 0, int RANKED = 0, int MODS = 0>
+// ---------------------------------------------------------------------------
+// Prefill tile: 256 x 256 outputs per workgroup of eight waves (64 x 128 each),
+// bf16 in, 16x16x32 MFMA.
+//
+// A tile of this size needs 64 B of operands per matrix-core cycle pair from
+// L2, and what bounds it is how long a load may take: with the whole LDS as
+// two 64-deep stages a load had three quarters of a k-tile to arrive.  Here
+// the reduction is walked in 32-deep units through a ring of four, and a unit's
+// slot is refilled as soon as its last fragment has been read, so a load has
+// three units (one and a half of those k-tiles) to arrive:
+//   first part   12 of 32 MFMAs; under them the reads of the wave's second 64
+//                columns
+//   wait         those reads (after which this wave is done with the unit's
+//                slot) and this wave's loads of unit u + 1; then the barrier
+//   second part  the other 20; under them the fragment reads of unit u + 1  Fragments take 64 registers (a unit's rows and half its columns,
+// twice) beside the 128 accumulators, so nothing spills.
+// The adapter phase is a list of (run, unit) entries in LDS, uniform or mixed
+// ranks alike: one 8-byte read per unit, a unit ahead of its loads.
+// The waits and the barrier leave 16% of the matrix-core slots unused; the
+// clock is 1.74 GHz, held down by power (1.98 GHz with the ring's loads left
+// out), so the rest costs more time than it looks.  The setup before the loop
+// holds no wait for the weights in flight and one round trip for the tokens
+// (6.0 -> 3.7 us), and the output leaves as whole rows (8.7 -> 5.0 us).
+// T = 4096, 4096 x 4096, 17 clusters of rank 64: 124 -> 112 us a launch; the
+// two-stage 64-deep ring it replaces ran at 1315 cycles a unit, this at 1220.
+struct PrefillCfg {
+  static constexpr int BM = 256, BN = 256, BK = 32, NW = 8, NT = 512, P = 4;
+  static constexpr int ROWB = BK * 2, SB = (BM + BN) * ROWB;
+  static constexpr int WM = 4, WTM = 64, WTN = 128;   // waves 4 x 2
+  static constexpr int ST_ROWB = BM * 2 + 16;         // staged bf16 output row (bytes)
+  static constexpr int SMEM = P * SB > BN * ST_ROWB ? P * SB : BN * ST_ROWB;
+  static constexpr int MAXU = 4;                      // adapter units per run: rank <= 128
+};
+
+__global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p) {
+  using C = PrefillCfg;
+  using MT = MfmaTraits<bf16_t, 16>;
+  __shared__ __attribute__((aligned(1024))) char smem[C::SMEM];
+  // the adapter units' list, closed by an entry of rank 0, and its length
+  __shared__ __attribute__((aligned(8))) uint64_t sched[C::MAXU * C::BN + 1];
+  __shared__ uint32_t n_sched_s;
+  using std::integral_constant;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int mt, nt, ks;
+  const int gm_all = p.n_mod > 0 ? p.mod_rt[p.n_mod] : (p.M + C::BM - 1) / C::BM;
+  tile_of_block(gm_all, (p.N + C::BN - 1) / C::BN, &mt, &nt, &ks, 0, p.group_m);
+  int Mv = p.M;
+  const void* A0v = p.A0;
+  const void* A1v = p.A1;
+  const void* B1v = p.B1;
+  void* outv = p.out;
+  int64_t ldov = p.ldo;
+  uint32_t a0_bytes = p.a0_bytes, a1_seg_bytes = p.a1_seg_bytes, b1_bytes = p.b1_bytes;
+  if (p.n_mod > 0) {                                  // the module that owns this row tile
+    int mod = 0;
+#pragma unroll
+    for (int q = 1; q < kMaxGemmModules; ++q) mod += (q < p.n_mod && mt >= p.mod_rt[q]) ? 1 : 0;
+    mod = __builtin_amdgcn_readfirstlane(mod);
+    mt -= p.mod_rt[mod];
+    Mv = p.mod_M[mod];
+    A0v = p.mod_A0[mod]; a0_bytes = p.mod_a0_bytes[mod];
+    A1v = p.mod_A1[mod]; a1_seg_bytes = p.mod_a1_seg_bytes[mod];
+    B1v = p.mod_B1[mod]; b1_bytes = p.mod_b1_bytes[mod];
+    outv = p.mod_out[mod]; ldov = p.mod_ldo[mod];
+  }
+  const int m0 = mt * C::BM, j0 = nt * C::BN, jn = min(C::BN, p.N - j0);
+  const int K0 = p.K0, K1 = p.sorted_seg ? p.K1 : 0;
+
+  // ---- load mapping: wave w's loads cover rows 16 w + {0, 128} .. + 16 of each
+  // operand; lane l takes row l / 4 and stores chunk (l % 4) ^ key there
+  const int lrow = 16 * wave + (lane >> 2);
+  const int lchunk = (lane & 3) ^ swz_key<32>(lane >> 2);
+  const uint32_t cbytes = static_cast<uint32_t>(lchunk * 16);
+  uint32_t a0_v[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int m = m0 + lrow + 128 * j;
+    a0_v[j] = m < Mv ? static_cast<uint32_t>(m) * static_cast<uint32_t>(p.lda0) * 2 + cbytes : kOob;
+  }
+  const __amdgpu_buffer_rsrc_t rA0 = make_rsrc(A0v, a0_bytes);
+  const __amdgpu_buffer_rsrc_t rB0 = make_rsrc(p.B0, p.b0_bytes);
+  const __amdgpu_buffer_rsrc_t rB1 = make_rsrc(B1v, b1_bytes);
+  char* const smem_a = smem + wave * 1024;
+  char* const smem_b = smem + C::BM * C::ROWB + wave * 1024;
+
+  // ---- the tokens whose rows this lane loads; for wave 0, which lists the
+  // cluster runs, the clusters and ranks of columns lane + 64 q (indices past
+  // the tile repeat its last column: no branch around the loads)
+  uint32_t b0_v[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) b0_v[j] = static_cast<uint32_t>(p.perm[j0 + min(lrow + 128 * j, jn - 1)]);
+  int v_seg[4] = {0, 0, 0, 0}, v_rank[4] = {K1, K1, K1, K1};
+  if (wave == 0 && K1 > 0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v_seg[q] = p.sorted_seg[j0 + min(lane + 64 * q, jn - 1)];
+    if (p.seg_rank)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v_rank[q] = p.sorted_rank[j0 + min(lane + 64 * q, jn - 1)];
+  }
+
+  // The weight rows do not wait for the token order: the first units' go out
+  // now, the token rows' as soon as this lane's two tokens are known, and the
+  // adapter units are listed while both are on their way.
+  const int nd = (K0 + C::BK - 1) / C::BK, nd_full = K0 / C::BK;   // nd_full >= P
+#pragma unroll
+  for (int u = 0; u < C::P; ++u)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      load16_lds(rA0, smem_a + u * C::SB + j * 8192, a0_v[j], static_cast<uint32_t>(u * C::ROWB));
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+    b0_v[j] = lrow + 128 * j < jn ? b0_v[j] * static_cast<uint32_t>(p.ldb0) * 2 + cbytes : kOob;
+#pragma unroll
+  for (int u = 0; u < C::P - 1; ++u)                  // (unit 3's go out in unit 0)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      load16_lds(rB0, smem_b + u * C::SB + j * 8192, b0_v[j], static_cast<uint32_t>(u * C::ROWB));
+
+  // ---- the adapter phase's list: run by run, unit by unit.  Low word = first
+  // column | columns << 9 | unit << 18, high word = segment | rank << 16.
+  const uint32_t sched_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(sched));
+  const uint32_t count_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(&n_sched_s));
+  if (wave == 0) {
+    const uint64_t lt = (1ull << lane) - 1ull;
+    uint64_t start[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      int prev = __shfl_up(v_seg[q], 1);
+      if (q > 0 && lane == 0) prev = __builtin_amdgcn_readlane(v_seg[q > 0 ? q - 1 : 0], 63);
+      const int col = lane + 64 * q;
+      start[q] = __ballot(K1 > 0 && col < jn && (col == 0 || v_seg[q] != prev));
+    }
+    uint32_t tot = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bool st = (start[q] >> lane) & 1ull;
+      const int lo = lane + 64 * q;
+      int hi = jn;                                    // the next run's first column
+#pragma unroll
+      for (int q2 = 3; q2 > q; --q2)
+        if (start[q2]) hi = 64 * q2 + __builtin_ctzll(start[q2]);
+      const uint64_t above = start[q] & ~(lt | (1ull << lane));
+      if (above) hi = 64 * q + __builtin_ctzll(above);
+      const int kl = min(max(v_rank[q], 0), K1);
+      const int c = st ? (kl + C::BK - 1) / C::BK : 0;
+      const uint64_t b0 = __ballot(c & 1), b1 = __ballot(c & 2), b2 = __ballot(c & 4);
+      const uint32_t at = tot + __popcll(b0 & lt) + 2 * __popcll(b1 & lt) + 4 * __popcll(b2 & lt);
+      tot += __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
+      const uint32_t ex = static_cast<uint32_t>(lo) | (static_cast<uint32_t>(hi - lo) << 9);
+      const uint64_t ey = static_cast<uint64_t>(static_cast<uint32_t>(v_seg[q]) | (static_cast<uint32_t>(kl) << 16)) << 32;
+#pragma unroll
+      for (int i = 0; i < C::MAXU; ++i)
+        if (i < c) lds_write8(sched_addr + 8u * (at + i), ey | (ex | (static_cast<uint32_t>(i) << 18)));
+    }
+    if (lane == 0) {
+      lds_write8(sched_addr + 8u * tot, 0ull);        // rank 0: every load masked
+      lds_write4(count_addr, tot);
+    }
+    wait_lgkmcnt<0>();
+  }
+
+  // loads of a whole dense unit: loop-invariant lane offsets, uniform k offset
+  auto issue_fast = [&](int u, int slot, int j) __attribute__((always_inline)) {
+    const uint32_t k = static_cast<uint32_t>(u * C::ROWB);
+    if (j < 2) load16_lds(rA0, smem_a + slot * C::SB + j * 8192, a0_v[j], k);
+    else load16_lds(rB0, smem_b + slot * C::SB + (j - 2) * 8192, b0_v[j - 2], k);
+  };
+  // loads of any unit: the ragged dense tail, an adapter unit, or (past the
+  // end) nothing, every load masked
+  struct UnitLoad {
+    __amdgpu_buffer_rsrc_t rA, rB;
+    uint32_t av[2], bv[2];
+  };
+  int n_sched = 0;                                    // read after the first barrier
+  auto read_entry = [&](int u, uint64_t& e) __attribute__((always_inline)) {
+    lds_read8(e, sched_addr + 8u * static_cast<uint32_t>(min(max(u - nd, 0), n_sched)));
+  };
+  // entry: the list's entry of unit u (read_entry, waited for)
+  auto prep = [&](int u, uint64_t entry) __attribute__((always_inline)) {
+    UnitLoad L;
+    if (u < nd) {
+      L.rA = rA0; L.rB = rB0;
+      const uint32_t k = static_cast<uint32_t>(u * C::BK);
+      const uint32_t mask = k + lchunk * 8 < static_cast<uint32_t>(K0) ? 0u : kOob;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        L.av[j] = (a0_v[j] + 2 * k) | mask;
+        L.bv[j] = (b0_v[j] + 2 * k) | mask;
+      }
+    } else {
+      const uint32_t ex = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(entry));
+      const uint32_t ey = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(entry >> 32));
+      const int lo = static_cast<int>(ex & 511u);
+      const uint32_t span = (ex >> 9) & 511u, k = (ex >> 18) * C::BK;
+      const int64_t seg = static_cast<int64_t>(ey & 0xffffu);
+      const uint32_t mask = k + lchunk * 8 < (ey >> 16) ? 0u : kOob;
+      L.rA = make_rsrc(static_cast<const char*>(A1v) + seg * a1_seg_bytes, a1_seg_bytes);
+      L.rB = rB1;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int m = m0 + lrow + 128 * j, jl = lrow + 128 * j;
+        L.av[j] = (static_cast<uint32_t>(m) * static_cast<uint32_t>(p.lda1) * 2 + cbytes + 2 * k) | mask |
+                  (m < Mv ? 0u : kOob);
+        L.bv[j] = (static_cast<uint32_t>(j0 + jl) * static_cast<uint32_t>(p.ldb1) * 2 + cbytes + 2 * k) | mask |
+                  (static_cast<uint32_t>(jl - lo) < span ? 0u : kOob);
+      }
+    }
+    return L;
+  };
+  auto issue = [&](const UnitLoad& L, int slot, int j) __attribute__((always_inline)) {
+    if (j < 2) load16_lds(L.rA, smem_a + slot * C::SB + j * 8192, L.av[j]);
+    else load16_lds(L.rB, smem_b + slot * C::SB + (j - 2) * 8192, L.bv[j - 2]);
+  };
+
+  // ---- fragments ----------------------------------------------------------------
+  const int wm = wave >> 1, wn = wave & 1;
+  const int fr = lane & 15, fg = lane >> 4;
+  const uint32_t smem_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
+  const uint32_t sl = static_cast<uint32_t>((fg ^ swz_key<32>(fr)) * 16);
+  // slots 0 and 1 lie within an instruction offset of one address, slots 2 and
+  // 3 of another
+  static_assert(2 * C::SB == 65536, "slots per address");
+  uint32_t a_addr[2], b_addr[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    a_addr[h] = smem_base + 2 * h * C::SB + static_cast<uint32_t>((wm * C::WTM + fr) * C::ROWB) + sl;
+    b_addr[h] = smem_base + 2 * h * C::SB + static_cast<uint32_t>((C::BM + wn * C::WTN + fr) * C::ROWB) + sl;
+  }
+  bf16x8 fa[2][4], fb[2][4];
+  f32x4 acc[4][8];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // fragment i of the rows, or of half of the columns, of the unit in a slot
+  auto rd_a = [&](auto slot_c, int buf, auto i_c) __attribute__((always_inline)) {
+    constexpr int S = decltype(slot_c)::value, I = decltype(i_c)::value;
+    lds_read16_at<(S & 1) * C::SB + I * 16 * C::ROWB>(fa[buf][I], a_addr[S >> 1]);
+  };
+  auto rd_b = [&](auto slot_c, auto half_c, auto i_c) __attribute__((always_inline)) {
+    constexpr int S = decltype(slot_c)::value, H = decltype(half_c)::value, I = decltype(i_c)::value;
+    lds_read16_at<(S & 1) * C::SB + (4 * H + I) * 16 * C::ROWB>(fb[H][I], b_addr[S >> 1]);
+  };
+
+  // ---- prologue: units 0 .. 2 and the weights of unit 3 in flight, unit 0's
+  // first fragments
+  wait_vmcnt<4>();                                    // the token loads of units 1 and 2
+  __builtin_amdgcn_s_barrier();
+  uint32_t n_sched_v;
+  lds_read4(n_sched_v, count_addr);
+  unrolled<4>([&](auto i) __attribute__((always_inline)) {
+    rd_a(integral_constant<int, 0>{}, 0, i);
+    rd_b(integral_constant<int, 0>{}, integral_constant<int, 0>{}, i);
+  });
+  wait_lgkmcnt<0>();
+  pin(n_sched_v);
+  n_sched = __builtin_amdgcn_readfirstlane(n_sched_v);
+  const int ntot = nd + n_sched;
+  UnitLoad L;
+
+  // unit u in slot S (= u % 4).  Its first half issues the token loads of unit
+  // u + 3 (whose weight loads went out in the unit before), its second half
+  // the weight loads of unit u + 4 into the slot just freed: the loads are
+  // spread over the unit, since eight waves issuing theirs at once fill the
+  // load queue and hold up the MFMAs behind it.
+  auto unit = [&](auto slot_c, auto fast_c, int u) __attribute__((always_inline)) {
+    constexpr int S = decltype(slot_c)::value;
+    constexpr bool FAST = decltype(fast_c)::value;
+    constexpr int SN = (S + 1) & 3, SP = (S + 3) & 3, PA = S & 1;
+    uint64_t entry = 0;
+    auto load = [&](int uu, int slot, int j) __attribute__((always_inline)) {
+      if (FAST) issue_fast(uu, slot, j);
+      else issue(L, slot, j);
+    };
+    wait_lgkmcnt<0>();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { pin(fa[PA][i]); pin(fb[0][i]); }
+    unrolled<12>([&](auto m_c) __attribute__((always_inline)) {
+      constexpr int m = decltype(m_c)::value;
+      acc[m >> 2][m & 3] = MT::mma(fa[PA][m >> 2], fb[0][m & 3], acc[m >> 2][m & 3]);
+      if constexpr (m < 4) rd_b(slot_c, integral_constant<int, 1>{}, m_c);
+      if (!FAST && m == 4) read_entry(u + C::P, entry);
+      if (m == 5) load(u + C::P - 1, SP, 2);
+      if (m == 9) load(u + C::P - 1, SP, 3);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    wait_lgkmcnt<0>();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) pin(fb[1][i]);
+    if (!FAST) {
+      pin(entry);
+      L = prep(u + C::P, entry);
+    }
+    if (S == 0 && u == 0) wait_vmcnt<4>();            // the prologue's order: weights, then tokens
+    else if (S == 1 && u == 1) wait_vmcnt<6>();
+    else wait_vmcnt<8>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    unrolled<20>([&](auto k_c) __attribute__((always_inline)) {
+      constexpr int k = decltype(k_c)::value;
+      constexpr int m = k < 4 ? 12 + k : k - 4, h = k < 4 ? 0 : 1;
+      acc[m >> 2][4 * h + (m & 3)] = MT::mma(fa[PA][m >> 2], fb[h][m & 3], acc[m >> 2][4 * h + (m & 3)]);
+      // (fb[0]'s last use is k = 3)
+      if constexpr (k < 4) rd_a(integral_constant<int, SN>{}, PA ^ 1, k_c);
+      else if constexpr (k < 8) rd_b(integral_constant<int, SN>{}, integral_constant<int, 0>{}, integral_constant<int, k - 4>{});
+      if (k == 10) load(u + C::P, S, 0);
+      if (k == 15) load(u + C::P, S, 1);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  typedef std::integral_constant<bool, true> FastT;
+  typedef std::integral_constant<bool, false> AnyT;
+  int u = 0;
+  for (; u + 2 * C::P <= nd_full; u += 4) {           // units u .. u + 3 load whole dense units
+    unit(integral_constant<int, 0>{}, FastT{}, u);
+    unit(integral_constant<int, 1>{}, FastT{}, u + 1);
+    unit(integral_constant<int, 2>{}, FastT{}, u + 2);
+    unit(integral_constant<int, 3>{}, FastT{}, u + 3);
+  }
+  L = prep(u + C::P - 1, 0);                          // a whole dense unit
+  while (u < ntot) {
+    unit(integral_constant<int, 0>{}, AnyT{}, u);
+    if (++u >= ntot) break;
+    unit(integral_constant<int, 1>{}, AnyT{}, u);
+    if (++u >= ntot) break;
+    unit(integral_constant<int, 2>{}, AnyT{}, u);
+    if (++u >= ntot) break;
+    unit(integral_constant<int, 3>{}, AnyT{}, u);
+    ++u;
+  }
+  wait_lgkmcnt<0>();
+  wait_vmcnt<0>();
+  __syncthreads();
+
+  if (p.out_dtype == 1) {
+    // ---- bf16 epilogue: the tile as [token][row] in LDS, then 512 contiguous
+    // bytes of a token per half wave
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f32x4 v = acc[i][j];
+        uint2 w;
+        w.x = f32_to_bf16_pair(v[0], v[1]);
+        w.y = f32_to_bf16_pair(v[2], v[3]);
+        const int col = wn * C::WTN + j * 16 + fr, row = wm * C::WTM + i * 16 + 4 * fg;
+        *reinterpret_cast<uint2*>(smem + col * C::ST_ROWB + row * 2) = w;
+      }
+    __syncthreads();
+    const int mc = (tid & 31) * 8;
+    if (m0 + mc < Mv)
+      for (int jl = tid >> 5; jl < jn; jl += C::NT / 32) {
+        const uint4 v = *reinterpret_cast<const uint4*>(smem + jl * C::ST_ROWB + mc * 2);
+        const int64_t orow = p.out_perm ? p.perm[j0 + jl] : static_cast<int64_t>(j0 + jl);
+        *reinterpret_cast<uint4*>(static_cast<uint16_t*>(outv) + orow * ldov + m0 + mc) = v;
+      }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int jl = wn * C::WTN + j * 16 + fr;
+    const int64_t orow = p.out_perm ? p.perm[j0 + min(jl, jn - 1)] : static_cast<int64_t>(j0 + jl);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int m = m0 + wm * C::WTM + i * 16 + 4 * fg;
+      if (jl < jn && m < Mv) *reinterpret_cast<f32x4*>(static_cast<float*>(outv) + orow * ldov + m) = acc[i][j];
+    }
+  }
+}
+
+hipError_t launch_prefill(const GemmParams& p, hipStream_t stream) {
+  using C = PrefillCfg;
+  if (p.tile_start || p.fs_adapter || p.ksplit != 1 || p.part || p.K0 <= 0 || p.b1_gather || p.K1 > C::MAXU * C::BK ||
+      p.K0 < C::P * C::BK)
+    return hipErrorInvalidValue;
+  if (p.seg_rank && !p.sorted_rank) return hipErrorInvalidValue;
+  int gm = (p.M + C::BM - 1) / C::BM;
+  if (p.n_mod > 0) {
+    if (p.n_mod > kMaxGemmModules || p.mod_rt[0] != 0) return hipErrorInvalidValue;
+    for (int m = 0; m < p.n_mod; ++m)
+      if (p.mod_rt[m + 1] - p.mod_rt[m] != (p.mod_M[m] + C::BM - 1) / C::BM) return hipErrorInvalidValue;
+    gm = p.mod_rt[p.n_mod];
+  }
+  const int gn = (p.N + C::BN - 1) / C::BN;
+  GemmParams q = p;
+  q.group_m = xcd_group_m(gm, gn, 1);
+  hipLaunchKernelGGL(prefill_gemm_kernel, dim3(gm * gn), dim3(C::NT), 0, stream, q);
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT = 0, int FSORT = 0, int MODS = 0>
 hipError_t launch_dma1(const GemmParams& p, hipStream_t stream) {
   const int gn = (p.tile_start || FSORT) ? p.max_tiles : (p.N + BN - 1) / BN;
   // row tiles: the modules' together when the launch holds several
@@ -1167,28 +1504,24 @@ hipError_t launch_dma1(const GemmParams& p, hipStream_t stream) {
     grid = dim3(static_cast<unsigned>(std::min<int64_t>(gmt * gn + p.split_target, gmt * gn * p.ksplit)));
   }
   GemmParams q = p;
-  // the L2 prefetch splits its lines over groups of kGroupM row tiles
-  q.group_m = (p.tile_start || FSORT || PFD > 0) ? 0 : xcd_group_m(gm, (p.N + BN - 1) / BN, p.ksplit);
-  hipLaunchKernelGGL((seg_gemm_dma_kernel<BM, BN, BK, WM, WN, MB, P, DIRECT, PFD, WSPL, FSORT, RANKED, MODS>),
+  q.group_m = (p.tile_start || FSORT) ? 0 : xcd_group_m(gm, (p.N + BN - 1) / BN, p.ksplit);
+  hipLaunchKernelGGL((seg_gemm_dma_kernel<BM, BN, BK, WM, WN, MB, P, DIRECT, FSORT, MODS>),
                      grid, dim3(WM * WN * 64), 0, stream, q);
   return hipGetLastError();
 }
 
-// A segment phase with a rank table takes the RANKED kernel; its schedule
-// holds at most two k-tiles per cluster run.
-template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT = 0, int PFD = 0,
-          int WSPL = 1, int FSORT = 0>
+template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT = 0, int FSORT = 0>
 hipError_t launch_dma(const GemmParams& p, hipStream_t stream) {
-  const bool ranked = p.seg_rank && p.sorted_seg && p.K1 > 0 && !p.tile_start && !FSORT;
+  // the list of adapter k-tiles holds at most two per cluster run
+  if (!(p.tile_start || FSORT) && p.K1 > 2 * BK) return hipErrorInvalidValue;
+  // (token tiles keep no output row numbers: they write partials only)
+  if ((p.tile_start || FSORT) && !p.part) return hipErrorInvalidValue;
+  if (p.seg_rank && !p.sorted_rank && !(p.tile_start || FSORT)) return hipErrorInvalidValue;
   if (p.n_mod > 0) {
-    if (ranked || p.tile_start || FSORT) return hipErrorInvalidValue;
-    if constexpr (FSORT == 0) return launch_dma1<BM, BN, BK, WM, WN, MB, P, DIRECT, PFD, WSPL, 0, 0, 1>(p, stream);
+    if (p.seg_rank || p.tile_start || FSORT) return hipErrorInvalidValue;
+    if constexpr (FSORT == 0) return launch_dma1<BM, BN, BK, WM, WN, MB, P, DIRECT, 0, 1>(p, stream);
   }
-  if (!ranked) return launch_dma1<BM, BN, BK, WM, WN, MB, P, DIRECT, PFD, WSPL, FSORT>(p, stream);
-  if (p.K1 > 2 * BK || !p.sorted_rank) return hipErrorInvalidValue;
-  if constexpr (FSORT == 0)
-    return launch_dma1<BM, BN, BK, WM, WN, MB, P, DIRECT, PFD, WSPL, 0, 1>(p, stream);
-  return hipErrorInvalidValue;
+  return launch_dma1<BM, BN, BK, WM, WN, MB, P, DIRECT, FSORT>(p, stream);
 }
 
 template <typename TI, int BM, int BN, int BK, int WM, int WN, int STAGES, int OCC, int MB = 16>
@@ -1205,7 +1538,7 @@ hipError_t launch_cfg(const GemmParams& p, hipStream_t stream) {
 
 // Tile shapes (BM x BN x BK: d_out rows x tokens x k; chosen by the plan from
 // measurements on MI355X).  The ring tiles use 16x16x32 MFMA:
-//   Large   256 x 256 x  64, 8 waves, 2-stage ring + L2 prefetch      T >= 2048
+//   Large   256 x 256 x  32, 8 waves, 4-unit ring (prefill kernel)    T >= 2048
 //   Wide    256 x 128 x  64, 8 waves, 3 stages     many row tiles or d_in >= 8192
 //   Mid     128 x 128 x  64, 8 waves, 4 stages     >= 128 tiles
 //   Narrow  128 x  64 x 128, 4 waves, 3 stages     other T > 64
@@ -1215,7 +1548,7 @@ hipError_t launch_cfg(const GemmParams& p, hipStream_t stream) {
 //   F32      64 x  64 x  32, register-staged, fp32 inputs
 void tile_dims(Tile tile, int* BM, int* BN, int* BK) {
   switch (tile) {
-    case Tile::Large: *BM = 256; *BN = 256; *BK = 64; return;
+    case Tile::Large: *BM = 256; *BN = 256; *BK = 32; return;
     case Tile::Wide: *BM = 256; *BN = 128; *BK = 64; return;
     case Tile::Narrow: *BM = 128; *BN = 64; *BK = 128; return;
     case Tile::Decode: *BM = 64; *BN = 64; *BK = 128; return;
@@ -1241,12 +1574,12 @@ hipError_t launch_seg_gemm(const GemmParams& p, int in_dtype, Tile tile, hipStre
     return hipErrorInvalidValue;
   if (in_dtype == 0) return launch_cfg<float, 64, 64, 32, 2, 2, 1, 2, 16>(p, stream);
   switch (tile) {
-    case Tile::Large: return launch_dma<256, 256, 64, 4, 2, 16, 2, 1, 6, 4>(p, stream);
+    case Tile::Large: return launch_prefill(p, stream);
     case Tile::Wide: return launch_dma<256, 128, 64, 4, 2, 16, 3, 1>(p, stream);
     case Tile::Narrow: return launch_dma<128, 64, 128, 4, 1, 16, 3, 1>(p, stream);
     case Tile::Decode: return launch_dma<64, 64, 128, 2, 2, 16, 4, 1>(p, stream);
     case Tile::Shrink:
-      if (p.fs_adapter) return launch_dma<64, 64, 64, 2, 2, 16, 3, 1, 0, 1, 1>(p, stream);
+      if (p.fs_adapter) return launch_dma<64, 64, 64, 2, 2, 16, 3, 1, 1>(p, stream);
       return launch_dma<64, 64, 64, 2, 2, 16, 3, 1>(p, stream);
     case Tile::Mid: return launch_dma<128, 128, 64, 4, 2, 16, 4, 1>(p, stream);
     default: return launch_cfg<bf16_t, 64, 64, 64, 2, 2, 2, 2, 32>(p, stream);

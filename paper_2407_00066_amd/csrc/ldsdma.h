@@ -4,6 +4,9 @@
 // LDS fragment reads.  Device code only; nothing here is part of the ABI.
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "cts_internal.h"
 
 namespace cts {
@@ -40,11 +43,55 @@ template <int N> __device__ __forceinline__ void wait_lgkmcnt() {
 #endif
 }
 
+// Workgroup barrier for ordinary LDS data: waits for this wave's LDS
+// operations only, and not, as __syncthreads does, for every load it has in
+// flight into LDS.
+__device__ __forceinline__ void lds_barrier() {
+  wait_lgkmcnt<0>();
+  __builtin_amdgcn_s_barrier();
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" ::: "memory");
+#endif
+}
+
 // 16-byte LDS read issued as assembly: its completion is waited for with
 // wait_lgkmcnt, and pin() ties the fragment to that wait.
 __device__ __forceinline__ void lds_read16(bf16x8& dst, uint32_t addr) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("ds_read_b128 %0, %1" : "=v"(dst) : "v"(addr) : "memory");
+#endif
+}
+
+// The same at addr + OFF (0 <= OFF < 65536): the offset goes into the
+// instruction, so reads a constant apart share one address register.
+template <int OFF> __device__ __forceinline__ void lds_read16_at(bf16x8& dst, uint32_t addr) {
+  static_assert(OFF >= 0 && OFF < 65536, "16-bit offset");
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
+#endif
+}
+
+// 8- and 4-byte LDS reads and writes as assembly, waited for with
+// wait_lgkmcnt: the compiler would first wait for every load in flight into
+// LDS, which it cannot tell apart from them.
+__device__ __forceinline__ void lds_read8(uint64_t& dst, uint32_t addr) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("ds_read_b64 %0, %1" : "=v"(dst) : "v"(addr) : "memory");
+#endif
+}
+__device__ __forceinline__ void lds_read4(uint32_t& dst, uint32_t addr) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("ds_read_b32 %0, %1" : "=v"(dst) : "v"(addr) : "memory");
+#endif
+}
+__device__ __forceinline__ void lds_write8(uint32_t addr, uint64_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("ds_write_b64 %0, %1" ::"v"(addr), "v"(v) : "memory");
+#endif
+}
+__device__ __forceinline__ void lds_write4(uint32_t addr, uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(v) : "memory");
 #endif
 }
 
@@ -59,20 +106,31 @@ __device__ __forceinline__ void load16_lds(__amdgpu_buffer_rsrc_t r, char* lds, 
 #endif
 }
 
-// 4-byte buffer load of each lane into LDS, used as an L2 prefetch: the data
-// lands in a scratch LDS slot nobody reads, only the cache fill matters.
-__device__ __forceinline__ void load4_lds(__amdgpu_buffer_rsrc_t r, void* lds, uint32_t voff,
-                                          uint32_t soff) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 4, voff,
-                                           soff, 0, 0);
-#endif
-}
-
 __device__ __forceinline__ void pin(bf16x8& v) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("" : "+v"(v));
 #endif
+}
+
+__device__ __forceinline__ void pin(uint64_t& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(v));
+#endif
+}
+
+__device__ __forceinline__ void pin(uint32_t& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(v));
+#endif
+}
+
+// f(0), ..., f(N - 1), the index a compile-time constant
+template <typename F, int... I>
+__device__ __forceinline__ void unrolled_steps(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F> __device__ __forceinline__ void unrolled(F&& f) {
+  unrolled_steps(f, std::make_integer_sequence<int, N>{});
 }
 
 }  // namespace cts

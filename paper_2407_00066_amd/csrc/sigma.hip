@@ -332,10 +332,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
   }
   if (OUT_BF16) {
     uint4 w;
-    w.x = f32_to_bf16(acc[0]) | (static_cast<uint32_t>(f32_to_bf16(acc[1])) << 16);
-    w.y = f32_to_bf16(acc[2]) | (static_cast<uint32_t>(f32_to_bf16(acc[3])) << 16);
-    w.z = f32_to_bf16(acc[4 % V]) | (static_cast<uint32_t>(f32_to_bf16(acc[5 % V])) << 16);
-    w.w = f32_to_bf16(acc[6 % V]) | (static_cast<uint32_t>(f32_to_bf16(acc[7 % V])) << 16);
+    w.x = f32_to_bf16_pair(acc[0], acc[1]);
+    w.y = f32_to_bf16_pair(acc[2], acc[3]);
+    w.z = f32_to_bf16_pair(acc[4 % V], acc[5 % V]);
+    w.w = f32_to_bf16_pair(acc[6 % V], acc[7 % V]);
     *reinterpret_cast<uint4*>(static_cast<uint16_t*>(out) + row * ldo + m) = w;
   } else {
     *reinterpret_cast<f32x4*>(static_cast<float*>(out) + row * ldo + m) =
