@@ -18,6 +18,15 @@ _LIB_PATH = os.environ.get("CTS_LIB") or os.path.join(os.path.dirname(os.path.ab
 _lib = None
 _lock = threading.Lock()
 
+try:
+    from ._marshal import address as _address
+except ImportError as _e:          # no fallback: every call says so
+    _marshal_error = str(_e)
+
+    def _address(*_):
+        raise RuntimeError("_marshal.so is not built or does not load (%s); run "
+                           "`python -m paper_2407_00066_amd.build`" % _marshal_error)
+
 CTS_OK, CTS_ERR_INVALID_ARG, CTS_ERR_UNSUPPORTED, CTS_ERR_WORKSPACE, CTS_ERR_HIP, CTS_ERR_BAD_IDS = range(6)
 CTS_F32, CTS_BF16 = 0, 1
 
@@ -142,6 +151,18 @@ def _dt(t: torch.Tensor, name: str) -> int:
 
 
 def _dev(t: torch.Tensor, name: str, device: torch.device, dtype=None, shape=None):
+    """t's address after its checks (None when it is empty).  The checks run
+    natively; one that fails is gone through again here for its message."""
+    a = _address(t, device, dtype, shape)
+    if a > 0:
+        return a
+    if a < 0:
+        _check_tensor(t, name, device, dtype, shape)
+        return t.data_ptr() if t.numel() else None
+    return None
+
+
+def _check_tensor(t, name: str, device: torch.device, dtype, shape) -> None:
     if not isinstance(t, torch.Tensor):
         raise TypeError("%s must be a torch.Tensor" % name)
     if t.device != device:
@@ -152,11 +173,11 @@ def _dev(t: torch.Tensor, name: str, device: torch.device, dtype=None, shape=Non
         raise TypeError("%s must be %s, got %s" % (name, dtype, t.dtype))
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
-    return ctypes.c_void_p(t.data_ptr()) if t.numel() else None
 
 
 def _stream(device: torch.device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    return torch.cuda.current_stream(device).cuda_stream if device.index is None else \
+        torch._C._cuda_getCurrentRawStream(device.index)
 
 
 _ws_cache: dict = {}
@@ -221,7 +242,7 @@ def sort_by_cluster(adapter_id: torch.Tensor, cluster_of: torch.Tensor | None, n
             torch.empty(max(bucketing_size(T, n, K), 1), dtype=torch.uint8, device=dev)
         if bk.device != dev or bk.dtype != torch.uint8:
             raise ValueError("bucketing must be a uint8 tensor on %s" % dev)
-        bp, bn = ctypes.c_void_p(bk.data_ptr()), bk.numel()
+        bp, bn = bk.data_ptr(), bk.numel()
     _check(lib().cts_sort_by_cluster(a, c, T, n, K, pp, oo, bp, bn, _stream(dev)), "cts_sort_by_cluster")
     return (perm, offsets) if bk is None else (perm, offsets, bk)
 
@@ -248,9 +269,9 @@ def apply(x, adapter_id, cluster_of, W, U, Vt, Sigma, out=None, out_dtype=None, 
             _dev(Vt, "Vt", dev, tdt, (K, r, d_in)),
             _dev(Sigma, "Sigma", dev, tdt, (n, r, r)),
             _dev(out, "out", dev, None, (T, d_out))]
-    nbytes = workspace_size(p, True)   # 0 for an invalid problem: cts_apply reports why
-    ws = _workspace(dev, nbytes, workspace)
-    _check(lib().cts_apply(ctypes.byref(p), *args, ctypes.c_void_p(ws.data_ptr()), ws.numel(),
+    # (size 0 for an invalid problem: cts_apply reports why)
+    ws = _workspace(dev, workspace_size(p, True) if workspace is None else 0, workspace)
+    _check(lib().cts_apply(ctypes.byref(p), *args, ws.data_ptr(), ws.numel(),
                            _stream(dev)), "cts_apply")
     return out
 
@@ -310,9 +331,8 @@ def apply_diag(x, adapter_id, cluster_of, W, U, Vt, sigma, out=None, out_dtype=N
             _dev(Vt, "Vt", dev, tdt, (K, r, d_in)),
             _dev(sigma, "sigma", dev, tdt, (n, r)),
             _dev(out, "out", dev, None, (T, d_out))]
-    nbytes = workspace_size(p, True)
-    ws = _workspace(dev, nbytes, workspace)
-    _check(lib().cts_apply_diag(ctypes.byref(p), *args, ctypes.c_void_p(ws.data_ptr()), ws.numel(),
+    ws = _workspace(dev, workspace_size(p, True) if workspace is None else 0, workspace)
+    _check(lib().cts_apply_diag(ctypes.byref(p), *args, ws.data_ptr(), ws.numel(),
                                 _stream(dev)), "cts_apply_diag")
     return out
 
@@ -342,9 +362,8 @@ def apply_ranked(x, adapter_id, cluster_of, W, U, Vt, Sigma, rank_of_cluster, ou
             _dev(Sigma, "Sigma", dev, tdt, (n, r, r)),
             _dev(rank_of_cluster, "rank_of_cluster", dev, torch.int32, (K,)),
             _dev(out, "out", dev, None, (T, d_out))]
-    nbytes = workspace_size(p, True)
-    ws = _workspace(dev, nbytes, workspace)
-    _check(lib().cts_apply_ranked(ctypes.byref(p), *args, ctypes.c_void_p(ws.data_ptr()), ws.numel(),
+    ws = _workspace(dev, workspace_size(p, True) if workspace is None else 0, workspace)
+    _check(lib().cts_apply_ranked(ctypes.byref(p), *args, ws.data_ptr(), ws.numel(),
                                   _stream(dev)), "cts_apply_ranked")
     return out
 
@@ -370,9 +389,8 @@ def apply_uncompressed_ranked(x, adapter_id, W, A, B, rank_of_adapter, out=None,
             _dev(B, "B", dev, tdt, (n, d_out, r_l)),
             _dev(rank_of_adapter, "rank_of_adapter", dev, torch.int32, (n,)),
             _dev(out, "out", dev, None, (T, d_out))]
-    nbytes = workspace_size(p, False)
-    ws = _workspace(dev, nbytes, workspace)
-    _check(lib().cts_apply_uncompressed_ranked(ctypes.byref(p), *args, ctypes.c_void_p(ws.data_ptr()),
+    ws = _workspace(dev, workspace_size(p, False) if workspace is None else 0, workspace)
+    _check(lib().cts_apply_uncompressed_ranked(ctypes.byref(p), *args, ws.data_ptr(),
                                                ws.numel(), _stream(dev)), "cts_apply_uncompressed_ranked")
     return out
 
@@ -395,9 +413,8 @@ def apply_uncompressed(x, adapter_id, W, A, B, out=None, out_dtype=None, workspa
             _dev(A, "A", dev, tdt, (n, r_l, d_in)),
             _dev(B, "B", dev, tdt, (n, d_out, r_l)),
             _dev(out, "out", dev, None, (T, d_out))]
-    nbytes = workspace_size(p, False)
-    ws = _workspace(dev, nbytes, workspace)
-    _check(lib().cts_apply_uncompressed(ctypes.byref(p), *args, ctypes.c_void_p(ws.data_ptr()),
+    ws = _workspace(dev, workspace_size(p, False) if workspace is None else 0, workspace)
+    _check(lib().cts_apply_uncompressed(ctypes.byref(p), *args, ws.data_ptr(),
                                         ws.numel(), _stream(dev)), "cts_apply_uncompressed")
     return out
 
@@ -432,13 +449,12 @@ def apply_multi(x, adapter_id, cluster_of, Ws, Us, Vt, Sigmas, outs=None, out_dt
     Sp = (vp * M)(*[_dev(sg, "Sigma[%d]" % m, dev, tdt, (n, r, r)) for m, sg in enumerate(Sigmas)])
     Yp = (vp * M)(*[_dev(y, "out[%d]" % m, dev, None, (T, d_out[m])) for m, y in enumerate(outs)])
     dims = (ctypes.c_int32 * M)(*d_out)
-    nbytes = workspace_size_multi(p, d_out)
-    ws = _workspace(dev, nbytes, workspace)
+    ws = _workspace(dev, workspace_size_multi(p, d_out) if workspace is None else 0, workspace)
     _check(lib().cts_apply_multi(ctypes.byref(p), M, dims, _dev(x, "x", dev, tdt, (T, d_in)),
                                  _dev(adapter_id, "adapter_id", dev, torch.int32, (T,)),
                                  _dev(cluster_of, "cluster_of", dev, torch.int32, (n,)), Wp, Up,
                                  _dev(Vt, "Vt", dev, tdt, (K, M * r, d_in)), Sp, Yp,
-                                 ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream(dev)), "cts_apply_multi")
+                                 ws.data_ptr(), ws.numel(), _stream(dev)), "cts_apply_multi")
     return outs
 
 
@@ -468,13 +484,12 @@ def apply_multi_sorted(perm, bucketing, x, Ws, Us, Vt, Sigmas, outs=None, out_dt
     dims = (ctypes.c_int32 * M)(*d_out)
     if bucketing.device != dev or bucketing.dtype != torch.uint8:
         raise ValueError("bucketing must be a uint8 tensor on %s" % dev)
-    nbytes = workspace_size_multi(p, d_out)
-    ws = _workspace(dev, nbytes, workspace)
+    ws = _workspace(dev, workspace_size_multi(p, d_out) if workspace is None else 0, workspace)
     _check(lib().cts_apply_multi_sorted(ctypes.byref(p), M, dims, _dev(perm, "perm", dev, torch.int32, (T,)),
-                                        ctypes.c_void_p(bucketing.data_ptr()), bucketing.numel(),
+                                        bucketing.data_ptr(), bucketing.numel(),
                                         _dev(x, "x", dev, tdt, (T, d_in)), Wp, Up,
                                         _dev(Vt, "Vt", dev, tdt, (K, M * r, d_in)), Sp, Yp,
-                                        ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream(dev)),
+                                        ws.data_ptr(), ws.numel(), _stream(dev)),
            "cts_apply_multi_sorted")
     return outs
 
@@ -513,14 +528,13 @@ def apply_multi_packed(x, Ws, Us, Vt, Sigmas, adapter_id=None, cluster_of=None, 
         raise ValueError("bucketing must be a uint8 tensor on %s" % dev)
     ids = (_dev(adapter_id, "adapter_id", dev, torch.int32, (T,)), _dev(cluster_of, "cluster_of", dev, torch.int32,
                                                                       (n,))) if adapter_id is not None else (None, None)
-    srt = (_dev(perm, "perm", dev, torch.int32, (T,)), ctypes.c_void_p(bucketing.data_ptr()),
+    srt = (_dev(perm, "perm", dev, torch.int32, (T,)), bucketing.data_ptr(),
            bucketing.numel()) if perm is not None else (None, None, 0)
-    nbytes = workspace_size_multi(p, d_out)
-    ws = _workspace(dev, nbytes, workspace)
+    ws = _workspace(dev, workspace_size_multi(p, d_out) if workspace is None else 0, workspace)
     _check(lib().cts_apply_multi_packed(ctypes.byref(p), M, dims, *ids, *srt, _dev(x, "x", dev, tdt, (T, d_in)),
                                         Wp, Up, _dev(Vt, "Vt", dev, tdt, (K, M * r, d_in)), Sp,
                                         _dev(out, "out", dev, None, tuple(out.shape)), int(out.shape[1]),
-                                        ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream(dev)),
+                                        ws.data_ptr(), ws.numel(), _stream(dev)),
            "cts_apply_multi_packed")
     return out
 

@@ -1,4 +1,5 @@
-"""Builds libcts.so (the HIP kernels and the C ABI) in-tree for gfx950.
+"""Builds libcts.so (the HIP kernels and the C ABI) in-tree for gfx950, and
+_marshal.so (the Python binding's tensor checks, host code).
 
     python -m paper_2407_00066_amd.build
 
@@ -19,6 +20,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libcts.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
@@ -51,6 +53,27 @@ def _compile(src: str, build_dir: str = BUILD, sanitize: bool = False) -> str:
     return obj
 
 
+def build_marshal() -> str:
+    """Compile the binding's tensor checks (csrc/marshal.cpp: host code, torch's
+    C++ API) into _marshal.so."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    tmp = MARSHAL + ".tmp%d" % os.getpid()
+    inc = [a for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]] for a in ("-isystem", d)]
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)] + inc + \
+          [os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on marshal.cpp:\n%s%s" % (r.stdout, r.stderr))
+    os.replace(tmp, MARSHAL)
+    return MARSHAL
+
+
 def build(verbose: bool = True, out: str | None = None, sanitize: bool = False) -> str:
     """Compile every source and link libcts.so (into `out` if given; with
     sanitize, the host code under AddressSanitizer and
@@ -59,7 +82,8 @@ def build(verbose: bool = True, out: str | None = None, sanitize: bool = False) 
     build_dir = os.path.join(os.path.dirname(lib), "_build_san") if sanitize else BUILD
     os.makedirs(build_dir, exist_ok=True)
     srcs = sources()
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as ex:
+        marshal = ex.submit(build_marshal) if out is None else None
         objs = list(ex.map(lambda s_: _compile(s_, build_dir, sanitize), srcs))
     tmp = lib + ".tmp%d" % os.getpid()
     cmd = [HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", tmp] + objs
@@ -69,6 +93,8 @@ def build(verbose: bool = True, out: str | None = None, sanitize: bool = False) 
     if r.returncode != 0:
         raise RuntimeError("link failed:\n%s%s" % (r.stdout, r.stderr))
     os.replace(tmp, lib)
+    if marshal is not None:
+        marshal.result()
     if verbose:
         print("built", lib)
     return lib

@@ -40,7 +40,7 @@ def lora_norms2(A, B, r=16, workspace=None):
     ws = _workspace(dev, workspace_size(A, B, r), workspace)
     _check(lib().cts_lora_norms2(ctypes.byref(p), _dev(A, "A", dev, F32, (n, r_l, d_in)),
                                  _dev(B, "B", dev, F32, (n, d_out, r_l)), _dev(out, "norms2", dev, F32, (n,)),
-                                 ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream(dev)), "cts_lora_norms2")
+                                 ws.data_ptr(), ws.numel(), _stream(dev)), "cts_lora_norms2")
     return out
 
 
@@ -60,7 +60,7 @@ def jd_full(A, B, U0, Vt0, iters=10, tau=0.0, normalize=False, workspace=None):
                              _dev(B, "B", dev, F32, (n, d_out, r_l)), _dev(U0, "U0", dev, F32, (d_out, r)),
                              _dev(Vt0, "Vt0", dev, F32, (r, d_in)), int(iters), float(tau), int(bool(normalize)),
                              _dev(U, "U", dev, F32), _dev(Vt, "Vt", dev, F32), _dev(S, "Sigma", dev, F32),
-                             _dev(crit, "crit", dev, F32), ctypes.byref(done), ctypes.c_void_p(ws.data_ptr()),
+                             _dev(crit, "crit", dev, F32), ctypes.byref(done), ws.data_ptr(),
                              ws.numel(), _stream(dev)), "cts_jd_full")
     return U, Vt, S, crit, int(done.value)
 
@@ -79,7 +79,7 @@ def jd_diag(A, B, U0, Vt0, sweeps=10, normalize=False, workspace=None):
                              _dev(B, "B", dev, F32, (n, d_out, r_l)), _dev(U0, "U0", dev, F32, (d_out, r)),
                              _dev(Vt0, "Vt0", dev, F32, (r, d_in)), int(sweeps), int(bool(normalize)),
                              _dev(U, "U", dev, F32), _dev(Vt, "Vt", dev, F32), _dev(sig, "sigma", dev, F32),
-                             ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream(dev)), "cts_jd_diag")
+                             ws.data_ptr(), ws.numel(), _stream(dev)), "cts_jd_diag")
     return U, Vt, sig
 
 
@@ -93,7 +93,7 @@ def jd_sigma(A, B, U, Vt, workspace=None):
     _check(lib().cts_jd_sigma(ctypes.byref(p), _dev(A, "A", dev, F32, (n, r_l, d_in)),
                               _dev(B, "B", dev, F32, (n, d_out, r_l)), _dev(U, "U", dev, F32, (d_out, r)),
                               _dev(Vt, "Vt", dev, F32, (r, d_in)), _dev(S, "Sigma", dev, F32),
-                              ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream(dev)), "cts_jd_sigma")
+                              ws.data_ptr(), ws.numel(), _stream(dev)), "cts_jd_sigma")
     return S
 
 
@@ -120,6 +120,6 @@ def jd_cluster(A, B, K, U0, Vt0, Uc0, Vtc0, init_idx, jd_iters=10, max_rounds=20
                                 _dev(Vtc0, "Vtc0", dev, F32, (K, r, d_in)), init, int(jd_iters), int(max_rounds),
                                 int(bool(normalize)), _dev(cof, "cluster_of", dev, torch.int32),
                                 _dev(U, "U", dev, F32), _dev(Vt, "Vt", dev, F32), _dev(S, "Sigma", dev, F32),
-                                ctypes.byref(rounds), ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream(dev)),
+                                ctypes.byref(rounds), ws.data_ptr(), ws.numel(), _stream(dev)),
            "cts_jd_cluster")
     return cof, U, Vt, S, int(rounds.value)
