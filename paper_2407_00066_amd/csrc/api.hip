@@ -6,6 +6,9 @@
 //   3. core               Z' = Sigma_i Z per token                     sigma.hip
 //   4. fused base + up    Y  = W X + U_k Z' scattered to token order   gemm.hip
 //   (5. split-K reduce    only when the fused GEMM is split along k)   sigma.hip
+// Small bf16 batches run three launches instead (small_split_of): the shrink's
+// also holds W X (which needs no bucketing), then the core, then one kernel
+// that sums W X's partials and adds U_k Z'.
 // The uncompressed comparison path runs the same stages with one segment per
 // adapter, V_k^T -> A_i, U_k -> B_i and no core product.
 #include <stdlib.h>
@@ -36,6 +39,7 @@ struct Plan {
   int rank, nseg;
   Tile main_tile, shrink_tile;
   int main_split, shrink_split;
+  int small_split;                // > 0: W X rides with the shrink in that many pieces
   int max_items, max_ctiles;
   size_t off_perm, off_seg, off_aid, off_srank, off_offs, off_items, off_nitems, off_ctiles, off_nctiles,
       off_iaid, off_cseg, off_ssplit, off_zpart, off_zp, off_ypart, total;
@@ -45,28 +49,44 @@ constexpr uint64_t kMaxOperandBytes = 0x7fffffffull;   // buffer-load offsets ar
 
 int ceil_div(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }
 
-// The shrink's split along d_in for `rank` rank rows.  When the tiles come
-// from the separate sort (bf16, T > kFuseSortMaxT) the split follows the
-// tile count on the device: 512 workgroups, at least 8 k-tiles each, and
-// this returns the most it could use (the split for the fewest tiles,
-// ceil(T / 64)).  Otherwise (fp32, or the bucketing inside the shrink) it is
-// fixed: 256 (bf16) or 512 (fp32) workgroups over an estimate of the tiles
-// (token tiles plus half of the possible segment starts), at least 2
-// k-tiles each.
-constexpr int kShrinkAdaptiveTarget = 512;
+// The bf16 shrink's split along d_in follows the tile count on the device:
+// `target` workgroups, at least `kmin` k-tiles each.  Alone it takes 512 (256
+// where every workgroup buckets the tokens itself); beside the dense product
+// it has that product's time to finish in, so fewer, longer pieces (q/k/v of 33
+// tokens: 36.4 us a call at 128 and 8, 40.8 at 256, 42.6 at 64).
+struct ShrinkSplit { int target, kmin; };
+ShrinkSplit shrink_rule(int T, bool small) {
+  if (small) return {128, 8};
+  return T > cts::kFuseSortMaxT ? ShrinkSplit{512, 8} : ShrinkSplit{256, 2};
+}
 
-bool shrink_adaptive(int T, Tile t) { return t == Tile::Shrink && T > cts::kFuseSortMaxT; }
-
-int shrink_split_of(int T, int rank, int nseg, int d_in, Tile t) {
+// The most pieces the shrink may split `rank` rank rows into: for the bf16
+// tile the split for the fewest tiles, ceil(T / 64); for fp32, which is not
+// chosen on the device, 512 workgroups over an estimate of the tiles (token
+// tiles plus half of the possible segment starts), at least 2 k-tiles each.
+int shrink_split_of(int T, int rank, int nseg, int d_in, Tile t, bool small) {
   int BM, BN, BK;
   cts::tile_dims(t, &BM, &BN, &BK);
-  const bool adaptive = shrink_adaptive(T, t);
-  const int expect = ceil_div(std::max(T, 1), BN) + (adaptive ? 0 : std::min(nseg, std::max(T, 1)) / 2);
+  const bool f32 = t == Tile::F32;
+  const ShrinkSplit rule = f32 ? ShrinkSplit{512, 2} : shrink_rule(T, small);
+  const int expect = ceil_div(std::max(T, 1), BN) + (f32 ? std::min(nseg, std::max(T, 1)) / 2 : 0);
   const int tiles = ceil_div(rank, BM) * std::max(expect, 1);
   const int nk = ceil_div(d_in, BK);
-  const int target = adaptive ? kShrinkAdaptiveTarget : (t == Tile::F32 ? 512 : 256);
-  const int kmin = adaptive ? 8 : 2;
-  return std::max(1, std::min(std::min(ceil_div(target, tiles), std::max(1, nk / kmin)), 64));
+  return std::max(1, std::min(std::min(ceil_div(rule.target, tiles), std::max(1, nk / rule.kmin)), 64));
+}
+
+// Pieces of d_in when the dense product W X rides with the shrink, 0 when it
+// does not.  It does for bf16 batches that the shrink can bucket itself and
+// whose 64 x 64 tiles fit one round of 256 compute units (4096 -> 14336: at 64
+// tokens 224 tiles, 65 -> 56 us a call; at 100 tokens and rank 128 448 tiles,
+// 88 us in separate launches and 95 so).  More pieces than three (four past
+// d_in = 8192) cost more in partials than the shorter reduction gives: 4096 x
+// 4096 at 64 tokens 19.7, 21.4 and 21.8 us at three, four and seven.
+int small_split_of(int dtype, int T, int row_tiles, int d_in) {
+  const int tiles = row_tiles * ceil_div(T, 64);
+  if (dtype != CTS_BF16 || T < 1 || T > cts::kFuseSortMaxT || tiles > 256) return 0;
+  const int cap = std::min(d_in >= 8192 ? 4 : 3, cts::kExpandMaxSplit);
+  return std::max(1, std::min(std::min(cap, 256 / tiles), ceil_div(d_in, 64) / 4));
 }
 
 // Batches of more than kSortMaxT tokens (the one-workgroup bucketing's
@@ -167,16 +187,12 @@ int plan_piece(const cts_problem* p, bool compressed, Plan* pl) {
     const int s = std::min(std::min(std::max(1, 256 / tiles), max_split), std::max(1, nk / 4));
     pl->main_split = std::max(1, s);
   }
+  pl->small_split = small_split_of(p->dtype, T, ceil_div(p->d_out, 64), p->d_in);
   // shrink: one workgroup per (cluster segment tile of <= kSegTile tokens,
-  // 64 rank rows), split along d_in so that about 256 (bf16) or 512 (fp32)
-  // workgroups run; the Sigma stage sums the split partials.  The bf16
-  // shrink takes its split from the tile count on the device (at most
-  // shrink_split, the split for the fewest tiles T can make); the fp32 one
-  // from an estimate of the tile count.
+  // 64 rank rows, piece of d_in); the Sigma stage sums the pieces' partials
   pl->shrink_tile = (p->dtype == CTS_F32) ? Tile::F32 : Tile::Shrink;
-  cts::tile_dims(pl->shrink_tile, &BM, &BN, &BK);
   pl->max_ctiles = cts::max_seg_tiles(T, pl->nseg);
-  pl->shrink_split = shrink_split_of(T, pl->rank, pl->nseg, p->d_in, pl->shrink_tile);
+  pl->shrink_split = shrink_split_of(T, pl->rank, pl->nseg, p->d_in, pl->shrink_tile, pl->small_split > 0);
   pl->max_items = cts::max_sigma_items(T, p->n_adapters);
 
   // every operand a kernel reads through a buffer resource must stay below 2^31 bytes
@@ -204,7 +220,8 @@ int plan_piece(const cts_problem* p, bool compressed, Plan* pl) {
   pl->off_zpart = off; off = align_up(off + 4ull * pl->shrink_split * T * pl->rank);
   pl->off_zp = off;    off = align_up(off + static_cast<size_t>(pl->elt) * T * pl->rank);
   pl->off_ypart = off;
-  if (pl->main_split > 1) off = align_up(off + 4ull * pl->main_split * T * p->d_out);
+  const int pieces = pl->small_split > 0 ? pl->small_split : pl->main_split > 1 ? pl->main_split : 0;
+  off = align_up(off + 4ull * pieces * T * p->d_out);
   pl->total = off;
   return CTS_OK;
 }
@@ -322,9 +339,9 @@ int run_layer(const cts_problem* p, const Plan& pl, bool compressed, const void*
   g.ksplit = pl.shrink_split; g.part = zpart;
   g.tile_start = ctiles; g.n_tiles = n_ctiles; g.max_tiles = pl.max_ctiles; g.tile_seg = cseg;
   int32_t* ssplit = nullptr;
-  if (shrink_adaptive(T, pl.shrink_tile)) {
+  if (pl.shrink_tile == Tile::Shrink) {
     ssplit = reinterpret_cast<int32_t*>(ws + pl.off_ssplit);
-    g.split_target = kShrinkAdaptiveTarget; g.split_out = ssplit;
+    g.split_target = shrink_rule(T, pl.small_split > 0).target; g.split_out = ssplit;
   }
   if (fuse_sort) {
     g.tile_start = nullptr; g.n_tiles = nullptr; g.tile_seg = nullptr;
@@ -336,6 +353,11 @@ int run_layer(const cts_problem* p, const Plan& pl, bool compressed, const void*
     g.fs_bits_n = bits_n;
     g.fs_perm = perm; g.fs_seg = sseg; g.fs_aid = said; g.fs_items = items; g.fs_nitems = n_items;
   }
+  if (pl.small_split > 0) {
+    g.d_blocks = 1; g.d_split = pl.small_split; g.d_M = p->d_out; g.d_A0 = W;
+    g.d_a0_bytes = static_cast<uint32_t>(static_cast<uint64_t>(p->d_out) * p->d_in * pl.elt);
+    g.d_part = ypart; g.part_ld = p->d_out;
+  }
   e = cts::launch_seg_gemm(g, p->dtype, pl.shrink_tile, stream);
   if (e != hipSuccess || mark(2, stream) != hipSuccess) return CTS_ERR_HIP;
 
@@ -343,6 +365,22 @@ int run_layer(const cts_problem* p, const Plan& pl, bool compressed, const void*
                         pl.max_items, compressed ? Sigma : nullptr, zp, p->dtype, stream, sigma_diag,
                         sseg, seg_rank, seg_rank ? srank : nullptr, 0, ssplit, nullptr, 0, iaid);
   if (e != hipSuccess || mark(3, stream) != hipSuccess) return CTS_ERR_HIP;
+
+  if (pl.small_split > 0) {
+    cts::ExpandParams x{};
+    x.T = T; x.r = rank; x.ldz = rank; x.S = pl.small_split;
+    x.part = ypart; x.part_ld = p->d_out;
+    x.perm = perm; x.sorted_seg = sseg; x.sorted_rank = seg_rank ? srank : nullptr;
+    x.zp = zp; x.zp_bytes = static_cast<uint32_t>(static_cast<uint64_t>(T) * rank * pl.elt);
+    x.out_dtype = p->out_dtype;
+    x.n_mod = 1; x.rb[1] = ceil_div(p->d_out, 64); x.M[0] = p->d_out;
+    x.U[0] = Ubasis;
+    x.u_seg_bytes[0] = static_cast<uint32_t>(static_cast<uint64_t>(p->d_out) * rank * pl.elt);
+    x.out[0] = y; x.ldo[0] = p->d_out;
+    e = cts::launch_expand(x, stream);
+    if (e != hipSuccess || mark(4, stream) != hipSuccess) return CTS_ERR_HIP;
+    return mark(5, stream) == hipSuccess ? CTS_OK : CTS_ERR_HIP;
+  }
 
   cts::GemmParams f{};
   f.M = p->d_out; f.N = T;
@@ -564,6 +602,7 @@ struct MultiPlan {
   // grouped: every module's fused GEMM in one launch, with the tile and split
   // of one GEMM as wide as all the modules together (bf16 inputs, M > 1)
   bool grouped;
+  bool small;                  // as in Plan, for all modules together (pieces: g_split)
   Tile g_tile;
   int g_split, d_sum;
   size_t off_zpart, off_zp, off_ypart, total;
@@ -583,8 +622,12 @@ int multi_plan_piece(const cts_problem* p, int M, const int32_t* d_out, MultiPla
   const int T = p->T;
   mp->rtot = M * p->r;
   if (static_cast<uint64_t>(mp->rtot) * p->d_in * p0.elt > kMaxOperandBytes) return CTS_ERR_UNSUPPORTED;
+  int row_tiles = 0;
+  for (int m = 0; m < M; ++m) row_tiles += ceil_div(d_out[m], 64);
+  const int small = small_split_of(p->dtype, T, row_tiles, p->d_in);
+  mp->small = small > 0;
   // shrink over the stacked rank: as for one module, with M r rank rows
-  mp->shrink_split = shrink_split_of(T, mp->rtot, p0.nseg, p->d_in, p0.shrink_tile);
+  mp->shrink_split = shrink_split_of(T, mp->rtot, p0.nseg, p->d_in, p0.shrink_tile, mp->small);
   size_t off = p0.off_zpart;                        // the shared sort arrays of module 0's layout
   mp->off_zpart = off; off = align_up(off + 4ull * mp->shrink_split * T * mp->rtot);
   mp->off_zp = off;    off = align_up(off + static_cast<size_t>(p0.elt) * T * mp->rtot);
@@ -596,7 +639,9 @@ int multi_plan_piece(const cts_problem* p, int M, const int32_t* d_out, MultiPla
   // and three split-K sums); two launches of a round each are kept apart
   // (gate/up at T = 512: 448 grouped workgroups were slower than 2 x 224)
   mp->grouped = false;
-  if (M > 1 && p0.elt == 2) {
+  if (mp->small) {
+    mp->g_split = small;
+  } else if (M > 1 && p0.elt == 2) {
     cts_problem q = *p;
     q.d_out = mp->d_sum;
     Plan gp;
@@ -614,7 +659,9 @@ int multi_plan_piece(const cts_problem* p, int M, const int32_t* d_out, MultiPla
     }
   }
   size_t yp = 0;
-  if (mp->grouped) {
+  if (mp->small) {
+    yp = 4ull * mp->g_split * T * mp->d_sum;
+  } else if (mp->grouped) {
     if (mp->g_split > 1) yp = 4ull * mp->g_split * T * mp->d_sum;
   } else {
     for (int m = 0; m < M; ++m)
@@ -705,9 +752,9 @@ int run_multi(const cts_problem* p, const MultiPlan& mp, const int32_t* d_out, c
   g.ksplit = mp.shrink_split; g.part = zpart;
   g.tile_start = ctiles; g.n_tiles = n_ctiles; g.max_tiles = pl.max_ctiles; g.tile_seg = cseg;
   int32_t* ssplit = nullptr;
-  if (shrink_adaptive(T, pl.shrink_tile)) {
+  if (pl.shrink_tile == Tile::Shrink) {
     ssplit = reinterpret_cast<int32_t*>(ws + pl.off_ssplit);
-    g.split_target = kShrinkAdaptiveTarget; g.split_out = ssplit;
+    g.split_target = shrink_rule(T, mp.small).target; g.split_out = ssplit;
   }
   if (fuse_sort) {
     g.tile_start = nullptr; g.n_tiles = nullptr; g.tile_seg = nullptr;
@@ -719,6 +766,19 @@ int run_multi(const cts_problem* p, const MultiPlan& mp, const int32_t* d_out, c
     g.fs_bits_n = bits_n;
     g.fs_perm = perm; g.fs_seg = sseg; g.fs_aid = said; g.fs_items = items; g.fs_nitems = n_items;
   }
+  if (mp.small) {
+    g.d_blocks = 1; g.d_split = mp.g_split; g.d_M = d_out[0]; g.d_A0 = W[0];
+    g.d_a0_bytes = static_cast<uint32_t>(static_cast<uint64_t>(d_out[0]) * p->d_in * pl.elt);
+    g.d_part = ypart; g.part_ld = mp.d_sum;
+    g.n_mod = mp.M;
+    for (int m = 0, col = 0; m < mp.M; col += d_out[m], ++m) {
+      g.mod_rt[m + 1] = g.mod_rt[m] + ceil_div(d_out[m], 64);
+      g.mod_M[m] = d_out[m];
+      g.mod_col[m] = col;
+      g.mod_A0[m] = W[m];
+      g.mod_a0_bytes[m] = static_cast<uint32_t>(static_cast<uint64_t>(d_out[m]) * p->d_in * pl.elt);
+    }
+  }
   e = cts::launch_seg_gemm(g, p->dtype, pl.shrink_tile, stream);
   if (e != hipSuccess || mark(2, stream) != hipSuccess) return CTS_ERR_HIP;
 
@@ -727,6 +787,29 @@ int run_multi(const cts_problem* p, const MultiPlan& mp, const int32_t* d_out, c
                         zp, p->dtype, stream, false, sseg, nullptr, nullptr, rt, ssplit, Sigma, mp.M, iaid);
   if (e != hipSuccess) return CTS_ERR_HIP;
   if (mark(3, stream) != hipSuccess) return CTS_ERR_HIP;
+
+  if (mp.small) {
+    cts::ExpandParams x{};
+    x.T = T; x.r = r; x.ldz = rt; x.S = mp.g_split;
+    x.part = ypart; x.part_ld = mp.d_sum;
+    x.perm = perm; x.sorted_seg = sseg;
+    x.zp = zp; x.zp_bytes = static_cast<uint32_t>(static_cast<uint64_t>(T) * rt * pl.elt);
+    x.out_dtype = p->out_dtype;
+    x.n_mod = mp.M;
+    for (int m = 0, col = 0; m < mp.M; col += d_out[m], ++m) {
+      x.rb[m + 1] = x.rb[m] + ceil_div(d_out[m], 64);
+      x.M[m] = d_out[m];
+      x.col[m] = col;
+      x.zoff[m] = m * r;
+      x.U[m] = U[m];
+      x.u_seg_bytes[m] = static_cast<uint32_t>(static_cast<uint64_t>(d_out[m]) * r * pl.elt);
+      x.out[m] = y[m];
+      x.ldo[m] = ldy > 0 ? ldy : d_out[m];
+    }
+    e = cts::launch_expand(x, stream);
+    if (e != hipSuccess || mark(4, stream) != hipSuccess) return CTS_ERR_HIP;
+    return mark(5, stream) == hipSuccess ? CTS_OK : CTS_ERR_HIP;
+  }
 
   if (mp.grouped) {
     // one launch: module m's row tiles follow module m-1's

@@ -137,6 +137,15 @@ struct GemmParams {
   int64_t mod_ldo[kMaxGemmModules];
   uint32_t mod_a0_bytes[kMaxGemmModules], mod_a1_seg_bytes[kMaxGemmModules], mod_b1_bytes[kMaxGemmModules];
   int64_t part_ld;
+  // A shrink launch may hold the dense product W x too (d_blocks > 0, the count
+  // set by the launcher; bf16 shrink tile): its last d_blocks workgroups write the
+  // fp32 partials of W x, d_split pieces of d_in, to d_part[ks][token][m], rows
+  // part_ld apart, in token order (no bucketing is waited for); the rest are
+  // the shrink's.  d_M rows of d_A0 (with n_mod > 0: the modules', as above,
+  // without A1, B1, out), x = B1 with K1 = d_in.
+  int d_blocks, d_split, d_M;
+  const void* d_A0; uint32_t d_a0_bytes;
+  float* d_part;
 };
 
 // Tile shapes of the segmented GEMM (BM x BN x BK).  Large 256x256x32 (the
@@ -175,6 +184,28 @@ hipError_t launch_sigma(const float* zpart, int S, int T, int r, const int32_t* 
                         int ldz = 0, const int32_t* split_dev = nullptr,
                         const void* const* sigmas = nullptr, int nmod = 0,
                         const int32_t* item_aid = nullptr);
+
+// ------------------------------------------------- expansion of small batches
+// out_q[perm[j]][m] = sum_s part[s][perm[j]][col_q + m] + sum_k U_{seg(j)}[m][k] zp[j][zoff_q + k]
+// for the modules q: the dense product's partials (in token order) and the
+// up-projection, k below the segment's rank, in fp32, converted to out_dtype.
+struct ExpandParams {
+  int T, r, ldz, S;
+  const float* part; int64_t part_ld;
+  const int32_t* perm; const int32_t* sorted_seg;
+  const int32_t* sorted_rank;      // optional
+  const void* zp; uint32_t zp_bytes;
+  int out_dtype;
+  int n_mod;
+  int rb[kMaxGemmModules + 1];     // 64-row blocks before module q's
+  int M[kMaxGemmModules], col[kMaxGemmModules], zoff[kMaxGemmModules];
+  const void* U[kMaxGemmModules];
+  uint32_t u_seg_bytes[kMaxGemmModules];
+  void* out[kMaxGemmModules];
+  int64_t ldo[kMaxGemmModules];
+};
+constexpr int kExpandMaxSplit = 4;
+hipError_t launch_expand(const ExpandParams& p, hipStream_t stream);
 
 // Records stage event i of the profiling aid (cts_set_stage_events) on s when
 // it is on; a no-op otherwise.

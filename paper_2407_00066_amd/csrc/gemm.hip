@@ -100,13 +100,11 @@ __device__ __forceinline__ int split_lo(int n, int ks, int S) { return (int)((in
 constexpr int kXcds = 8;
 constexpr int kGroupM = 8;
 // group_m: m-tiles per group (0: kGroupM).
-__device__ __forceinline__ void tile_of_block(int gm, int gn, int* mt, int* nt, int* ks, int nb_used = 0,
+// b of nb: this workgroup among those that share the order.
+__device__ __forceinline__ void tile_of_block(int gm, int gn, int* mt, int* nt, int* ks, int b, int nb,
                                               int group_m = 0) {
-  const int b = blockIdx.x;
   const int nb_mn = gm * gn;
   const int G = group_m > 0 ? group_m : kGroupM;
-  // nb_mn * ksplit workgroups (the grid, or its first nb_used)
-  const int nb = nb_used > 0 ? nb_used : static_cast<int>(gridDim.x);
   const int q = nb / kXcds, rem = nb % kXcds;
   const int x = b % kXcds, i = b / kXcds;
   const int L = x * q + min(x, rem) + i;
@@ -157,7 +155,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void seg_gemm_kernel(const GemmP
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int mt, nt, ks;
-  tile_of_block((p.M + BM - 1) / BM, gn, &mt, &nt, &ks);
+  tile_of_block((p.M + BM - 1) / BM, gn, &mt, &nt, &ks, blockIdx.x, gridDim.x);
   if (p.tile_start && nt >= p.n_tiles[0]) return;    // whole workgroup: no tile
   const int m0 = mt * BM;
   const int j0 = p.tile_start ? p.tile_start[nt] : nt * BN;
@@ -441,7 +439,13 @@ struct DmaCfg {
 // output features of one token per lane) instead of staging the tile in LDS;
 // used when the fp32 tile does not fit in LDS.
 // MODS: the launch may hold several modules (p.n_mod > 0).
-template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT, int FSORT = 0, int MODS = 0>
+// DENSE: a shrink launch whose last p.d_blocks workgroups compute W x.
+// Both roles read their operands at once and neither waits for the other: at
+// 64 tokens, 4096 x 4096, 8.2 us for what took a shrink of 4.3 and a fused GEMM
+// of 9.3 us and the gap between them.  Four stages: at six and eight the longer
+// prologue costs more than the deeper ring gives (8.9 and 9.7 us).
+template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT, int FSORT = 0, int MODS = 0,
+          int DENSE = 0>
 __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const GemmParams p) {
   using C = DmaCfg<BM, BN, BK, WM, WN, MB, P, DIRECT>;
   using MT = MfmaTraits<bf16_t, MB>;
@@ -460,13 +464,18 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   __shared__ int32_t fs_cnt[2];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the workgroup's role, and its number among those of its role
+  const int d_blocks = DENSE ? p.d_blocks : 0;
+  const int nblk = static_cast<int>(gridDim.x) - d_blocks;     // the shrink's
+  const bool dense_role = DENSE && static_cast<int>(blockIdx.x) >= nblk;
+  const int blk = static_cast<int>(blockIdx.x) - (dense_role ? nblk : 0);
   const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   // FSORT: bucketing of the (at most kFuseSortMaxT) tokens in LDS.  The key
   // is cluster << bits_n | adapter (the adapter alone without a cluster
   // map); the rank of token t is the number of smaller keys plus equal keys
   // of earlier tokens, the stable order of the separate sort.
   const int fs_cshift = p.fs_cluster ? p.fs_bits_n : 0;
-  if (FSORT) {
+  if (FSORT && !dense_role) {
     static_assert(!FSORT || (C::NT >= kFuseSortMaxT && BN >= 64), "one token per thread; 64-token tiles");
     const int T = p.N;
     // A cluster map that fits the ring's LDS (unused until the k loop) is
@@ -517,7 +526,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
         const bool si = valid && (j % kSigmaChunk == 0 || k != kp);
         const uint64_t bt = __ballot(st), bi = __ballot(si);
         if (st) fs_tile[nt_ + __popcll(bt & lt_mask)] = j;
-        if (si && blockIdx.x == 0) {
+        if (si && blk == 0) {
           p.fs_items[ni_ + __popcll(bi & lt_mask)] = j;
           if (p.fs_item_aid)
             p.fs_item_aid[ni_ + __popcll(bi & lt_mask)] = static_cast<int32_t>(k & ((1u << p.fs_bits_n) - 1u));
@@ -528,10 +537,10 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
       if (lane == 0) {
         fs_tile[nt_] = T;
         fs_cnt[0] = nt_;
-        if (blockIdx.x == 0) { p.fs_items[ni_] = T; p.fs_nitems[0] = ni_; }
+        if (blk == 0) { p.fs_items[ni_] = T; p.fs_nitems[0] = ni_; }
       }
     }
-    if (blockIdx.x == 0 && tid < T) {
+    if (blk == 0 && tid < T) {
       const uint32_t k = fs_key[tid];
       p.fs_perm[tid] = fs_perm[tid];
       p.fs_seg[tid] = static_cast<int32_t>(k >> fs_cshift);
@@ -542,7 +551,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   // Token-tile mode (explicit tiles, each inside one segment): the tile's
   // segment operand becomes the dense operand (A = A1 of that segment, B = B1),
   // so the whole k loop takes the dense load path and there is no second phase.
-  const bool tlist = FSORT || p.tile_start != nullptr;
+  const bool tlist = !dense_role && (FSORT || p.tile_start != nullptr);
   int mt, nt, ks;
   int s_pieces = p.ksplit;
   // the split along k follows the tile count only in the shrink's tile shape
@@ -555,13 +564,16 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
     const int ntl = FSORT ? fs_cnt[0] : p.n_tiles[0];
     const int per = max(gm * ntl, 1);
     s_pieces = min(max((p.split_target + per - 1) / per, 1), p.ksplit);
-    if (blockIdx.x == 0 && tid == 0 && p.split_out) p.split_out[0] = s_pieces;
+    if (blk == 0 && tid == 0 && p.split_out) p.split_out[0] = s_pieces;
     const int used = gm * ntl * s_pieces;
-    if (static_cast<int>(blockIdx.x) >= used) return;
-    tile_of_block(gm, ntl, &mt, &nt, &ks, used);
+    if (blk >= used) return;
+    tile_of_block(gm, ntl, &mt, &nt, &ks, blk, used);
   } else {
-    const int gm_all = (MODS && !tlist && p.n_mod > 0) ? p.mod_rt[p.n_mod] : (p.M + BM - 1) / BM;
-    tile_of_block(gm_all, tlist ? p.max_tiles : (p.N + BN - 1) / BN, &mt, &nt, &ks, 0, tlist ? 0 : p.group_m);
+    const int rows = dense_role ? p.d_M : p.M;
+    const int gm_all = ((MODS || DENSE) && !tlist && p.n_mod > 0) ? p.mod_rt[p.n_mod] : (rows + BM - 1) / BM;
+    const int gn_all = tlist ? p.max_tiles : (p.N + BN - 1) / BN;
+    if (dense_role) s_pieces = p.d_split;
+    tile_of_block(gm_all, gn_all, &mt, &nt, &ks, blk, dense_role ? d_blocks : nblk, tlist ? 0 : p.group_m);
   }
   // the operands of this workgroup's module: with several modules in the
   // launch, row tiles [mod_rt[m], mod_rt[m+1]) are module m's
@@ -574,7 +586,12 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   float* partv = p.part;
   int64_t ldov = p.ldo;
   uint32_t a0v_bytes = p.a0_bytes, a1_seg_bytes = p.a1_seg_bytes, b1v_bytes = p.b1_bytes;
-  if (MODS && !tlist && p.n_mod > 0) {
+  if (dense_role) {
+    Mv = p.d_M;
+    A0v = p.d_A0; a0v_bytes = p.d_a0_bytes;
+    partv = p.d_part;
+  }
+  if ((MODS || DENSE) && !tlist && p.n_mod > 0) {
     int mod = 0;
 #pragma unroll
     for (int q = 1; q < kMaxGemmModules; ++q) mod += (q < p.n_mod && mt >= p.mod_rt[q]) ? 1 : 0;
@@ -582,13 +599,15 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
     mt -= p.mod_rt[mod];
     Mv = p.mod_M[mod];
     A0v = p.mod_A0[mod]; a0v_bytes = p.mod_a0_bytes[mod];
-    A1v = p.mod_A1[mod]; a1_seg_bytes = p.mod_a1_seg_bytes[mod];
-    B1v = p.mod_B1[mod]; b1v_bytes = p.mod_b1_bytes[mod];
-    outv = p.mod_out[mod]; ldov = p.mod_ldo[mod];
+    if (!dense_role) {
+      A1v = p.mod_A1[mod]; a1_seg_bytes = p.mod_a1_seg_bytes[mod];
+      B1v = p.mod_B1[mod]; b1v_bytes = p.mod_b1_bytes[mod];
+      outv = p.mod_out[mod]; ldov = p.mod_ldo[mod];
+    }
     if (partv) partv += p.mod_col[mod];
   }
   // row stride of the split partials (the modules' total width with several)
-  const int64_t part_ld = (MODS && p.part_ld > 0) ? p.part_ld : Mv;
+  const int64_t part_ld = ((MODS || DENSE) && !tlist && p.part_ld > 0) ? p.part_ld : Mv;
   const int S = s_pieces;
   int j0, jn;
   if (tlist) {
@@ -612,6 +631,10 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
     A0 = static_cast<const char*>(A1v) + static_cast<int64_t>(seg) * a1_seg_bytes;
     a0_bytes = a1_seg_bytes; lda0 = p.lda1; K0 = p.K1;
     B0 = B1v; b0_bytes = b1v_bytes; ldb0 = p.ldb1; b0_gather = p.b1_gather != 0;
+    K1 = 0;
+  } else if (dense_role) {
+    lda0 = p.lda1; K0 = p.K1;
+    B0 = B1v; b0_bytes = b1v_bytes; ldb0 = p.ldb1; b0_gather = false;
     K1 = 0;
   }
   const int m0 = mt * BM;
@@ -675,13 +698,13 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
 #pragma unroll
   for (int j = 0; j < C::QB; ++j) {
     const int jc = j0 + min(C::RPI * (wave + C::NW * j) + lrow, jn - 1);
-    tok[j] = static_cast<uint32_t>(FSORT ? fs_perm[jc] : p.perm[jc]);
+    tok[j] = static_cast<uint32_t>(dense_role ? jc : FSORT ? fs_perm[jc] : p.perm[jc]);
   }
   const bool adapters = !tlist && p.sorted_seg && K1 > 0;
   int v_perm = 0, v_seg[NQ], v_rank[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) { v_seg[q] = 0; v_rank[q] = K1; }
-  if (!tlist) v_perm = p.perm[j0 + min(tid, jn - 1)];
+  if (!tlist && !dense_role) v_perm = p.perm[j0 + min(tid, jn - 1)];
   if (wave == 0 && adapters) {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) v_seg[q] = p.sorted_seg[j0 + min(lane + 64 * q, jn - 1)];
@@ -984,10 +1007,11 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
           mma(b, m);
           __builtin_amdgcn_sched_barrier(0);
         }
-        // this lane's loads of k-tile t+1.  In the prologue's order (weight loads
-        // of k-tiles 0..2, then their token loads) k-tile 1's token loads
-        // are followed by k-tile 2's token loads and k-tile 3's loads only.
-        if (P == 4 && t == 0) wait_vmcnt<(P == 4 ? 2 * C::LPT - C::QA : 0)>();
+        // this lane's loads of k-tile t+1.  In the prologue's order (the weight
+        // loads of k-tiles 0 .. P-2, then their token loads) the token loads of
+        // k-tile t+1 <= P-2 are followed by those of k-tiles t+2 .. P-2 and by
+        // the t+1 k-tiles loaded since; t = 0's count serves them all.
+        if (P >= 4 && t < P - 3) wait_vmcnt<(P >= 4 ? (P - 3) * C::QB + C::LPT : 0)>();
         else wait_vmcnt<(P - 2) * C::LPT>();
         __builtin_amdgcn_s_barrier();                      // ... and every wave's
         __builtin_amdgcn_sched_barrier(0);
@@ -1138,7 +1162,7 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int mt, nt, ks;
   const int gm_all = p.n_mod > 0 ? p.mod_rt[p.n_mod] : (p.M + C::BM - 1) / C::BM;
-  tile_of_block(gm_all, (p.N + C::BN - 1) / C::BN, &mt, &nt, &ks, 0, p.group_m);
+  tile_of_block(gm_all, (p.N + C::BN - 1) / C::BN, &mt, &nt, &ks, blockIdx.x, gridDim.x, p.group_m);
   int Mv = p.M;
   const void* A0v = p.A0;
   const void* A1v = p.A1;
@@ -1483,12 +1507,14 @@ hipError_t launch_prefill(const GemmParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT = 0, int FSORT = 0, int MODS = 0>
+template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT = 0, int FSORT = 0, int MODS = 0,
+          int DENSE = 0>
 hipError_t launch_dma1(const GemmParams& p, hipStream_t stream) {
   const int gn = (p.tile_start || FSORT) ? p.max_tiles : (p.N + BN - 1) / BN;
   // row tiles: the modules' together when the launch holds several
   const bool mods = MODS && !(p.tile_start || FSORT) && p.n_mod > 0;
-  if (!MODS && p.n_mod > 0) return hipErrorInvalidValue;
+  if (!MODS && !DENSE && p.n_mod > 0) return hipErrorInvalidValue;
+  if (!DENSE != !(p.d_blocks > 0)) return hipErrorInvalidValue;
   if (mods) {
     if (p.n_mod > kMaxGemmModules || p.mod_rt[0] != 0) return hipErrorInvalidValue;
     for (int m = 0; m < p.n_mod; ++m)
@@ -1505,7 +1531,21 @@ hipError_t launch_dma1(const GemmParams& p, hipStream_t stream) {
   }
   GemmParams q = p;
   q.group_m = (p.tile_start || FSORT) ? 0 : xcd_group_m(gm, (p.N + BN - 1) / BN, p.ksplit);
-  hipLaunchKernelGGL((seg_gemm_dma_kernel<BM, BN, BK, WM, WN, MB, P, DIRECT, FSORT, MODS>),
+  if (DENSE) {
+    if (!p.d_part || p.d_split < 1 || p.n_mod > kMaxGemmModules) return hipErrorInvalidValue;
+    int dgm = (p.d_M + BM - 1) / BM;
+    if (p.n_mod > 0) {
+      if (p.mod_rt[0] != 0) return hipErrorInvalidValue;
+      for (int m = 0; m < p.n_mod; ++m)
+        if (p.mod_rt[m + 1] - p.mod_rt[m] != (p.mod_M[m] + BM - 1) / BM) return hipErrorInvalidValue;
+      dgm = p.mod_rt[p.n_mod];
+    }
+    const int dgn = (p.N + BN - 1) / BN;
+    q.d_blocks = dgm * dgn * p.d_split;
+    q.group_m = xcd_group_m(dgm, dgn, p.d_split);
+    grid.x += q.d_blocks;
+  }
+  hipLaunchKernelGGL((seg_gemm_dma_kernel<BM, BN, BK, WM, WN, MB, P, DIRECT, FSORT, MODS, DENSE>),
                      grid, dim3(WM * WN * 64), 0, stream, q);
   return hipGetLastError();
 }
@@ -1560,8 +1600,12 @@ void tile_dims(Tile tile, int* BM, int* BN, int* BK) {
 }
 
 hipError_t launch_seg_gemm(const GemmParams& p, int in_dtype, Tile tile, hipStream_t stream) {
-  // several modules in one launch: the LDS-ring tiles only, without token tiles
-  if (p.n_mod > 0 && (in_dtype == 0 || tile == Tile::Small || p.tile_start || p.fs_adapter))
+  // several modules in one launch: the LDS-ring tiles only, without token
+  // tiles (but those of a shrink that holds the modules' dense product)
+  if (p.n_mod > 0 && (in_dtype == 0 || tile == Tile::Small || ((p.tile_start || p.fs_adapter) && !p.d_blocks)))
+    return hipErrorInvalidValue;
+  // the dense product rides with the bf16 shrink's token tiles only
+  if (p.d_blocks > 0 && (in_dtype == 0 || tile != Tile::Shrink || !(p.tile_start || p.fs_adapter) || !p.part))
     return hipErrorInvalidValue;
   // explicit token tiles (at most kSegTile columns) only with the 64-wide tiles
   if (p.tile_start &&
@@ -1579,6 +1623,9 @@ hipError_t launch_seg_gemm(const GemmParams& p, int in_dtype, Tile tile, hipStre
     case Tile::Narrow: return launch_dma<128, 64, 128, 4, 1, 16, 3, 1>(p, stream);
     case Tile::Decode: return launch_dma<64, 64, 128, 2, 2, 16, 4, 1>(p, stream);
     case Tile::Shrink:
+      if (p.d_blocks > 0)
+        return p.fs_adapter ? launch_dma1<64, 64, 64, 2, 2, 16, 4, 1, 1, 0, 1>(p, stream)
+                            : launch_dma1<64, 64, 64, 2, 2, 16, 4, 1, 0, 0, 1>(p, stream);
       if (p.fs_adapter) return launch_dma<64, 64, 64, 2, 2, 16, 3, 1, 1>(p, stream);
       return launch_dma<64, 64, 64, 2, 2, 16, 3, 1>(p, stream);
     case Tile::Mid: return launch_dma<128, 128, 64, 4, 2, 16, 4, 1>(p, stream);

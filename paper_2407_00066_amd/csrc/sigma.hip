@@ -13,6 +13,7 @@
 // the stage only sums and converts.
 #include "cts.h"
 #include "cts_internal.h"
+#include "ldsdma.h"
 
 namespace cts {
 namespace {
@@ -276,6 +277,102 @@ __global__ __launch_bounds__(kSigThreads) void sigma_kernel(const float* __restr
   }
 }
 
+// Small batches: the dense product's partials are summed and the
+// up-projection U_k z'_t is added in one pass, y = sum_s part + U_k z'.
+//
+// Latency is the bound (a few MB in all), so a wave takes the smallest matrix-
+// core tile, 16 rows by 16 sorted positions, and no barrier: its partials, its
+// tokens' z' and the U rows of four cluster runs at a time are all in flight
+// together.  A wave visits only the runs among its own 16 positions (as k-tiles
+// of a whole token tile, 48 runs of one adapter each ran one after the other).
+// 64 tokens, 4096 x 4096: 3.3 us at rank 64 with one cluster, 4.4 us with 48
+// rank-16 LoRAs (with the partial sum it replaces, 13 us of the fused GEMM).
+template <int KK>
+__global__ __launch_bounds__(256) void expand_kernel(const ExpandParams p) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int nrb = p.rb[p.n_mod];
+  int rb = blockIdx.x % nrb;
+  const int j0 = (blockIdx.x / nrb) * 16;
+  int q = 0;
+#pragma unroll
+  for (int u = 1; u < kMaxGemmModules; ++u) q += (u < p.n_mod && rb >= p.rb[u]) ? 1 : 0;
+  rb -= p.rb[q];
+  const int M = p.M[q], m0 = rb * 64 + wave * 16;
+  if (m0 >= M) return;
+  const int jn = min(16, p.T - j0);
+  const int jc = lane & 15, g = lane >> 4;
+  const int j = j0 + min(jc, jn - 1);                  // (columns past the last repeat it; never stored)
+  const int tok = p.perm[j], seg = p.sorted_seg[j];
+  const int rk = p.sorted_rank ? p.sorted_rank[j] : p.r;
+  // z' of column jc, k = 32 i + 8 g ..
+  const __amdgpu_buffer_rsrc_t rZ = make_rsrc(p.zp, p.zp_bytes);
+  u32x4 z[KK];
+#pragma unroll
+  for (int i = 0; i < KK; ++i) {
+    const int k = 32 * i + 8 * g;
+    z[i] = load16(rZ, k < p.r ? static_cast<uint32_t>((j * p.ldz + p.zoff[q] + k) * 2) : kOob);
+  }
+  // the partials of rows m0 + 4 g .. + 3 (M is a multiple of 8: all or none of them exist)
+  const int mrow = m0 + 4 * g;
+  const bool live = jc < jn && mrow < M;
+  f32x4 part[kExpandMaxSplit];
+  {
+    const float* src = p.part + static_cast<int64_t>(tok) * p.part_ld + p.col[q] + (mrow < M ? mrow : 0);
+    const int64_t stride = static_cast<int64_t>(p.T) * p.part_ld;
+#pragma unroll
+    for (int s = 0; s < kExpandMaxSplit; ++s)
+      if (s < p.S) part[s] = *reinterpret_cast<const f32x4*>(src + s * stride);
+  }
+  const int prev = __shfl_up(seg, 1);
+  uint32_t st = static_cast<uint32_t>(__ballot(lane < jn && (lane == 0 || seg != prev))) & 0xffffu;
+  const uint32_t arow = static_cast<uint32_t>((m0 + jc) * p.r + 8 * g) * 2;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  constexpr int NB = 4;                                // runs whose U loads go out together
+  while (st) {
+    u32x4 a[NB][KK];
+    int lo[NB], hi[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      lo[b] = st ? __builtin_ctz(st) : 0;
+      const uint32_t rest = st & (st - 1u);
+      hi[b] = st ? (rest ? __builtin_ctz(rest) : jn) : 0;
+      const int s = __builtin_amdgcn_readlane(seg, lo[b]);
+      const int kl = st ? __builtin_amdgcn_readlane(rk, lo[b]) : 0;
+      st = st ? rest : 0u;
+      const __amdgpu_buffer_rsrc_t rU =
+          make_rsrc(static_cast<const char*>(p.U[q]) + static_cast<int64_t>(s) * p.u_seg_bytes[q], p.u_seg_bytes[q]);
+      // (rows past M lie past the segment's end and read zeros)
+#pragma unroll
+      for (int i = 0; i < KK; ++i) a[b][i] = load16(rU, 32 * i + 8 * g < kl ? arow + 64u * i : kOob);
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const bool in = jc >= lo[b] && jc < hi[b];
+#pragma unroll
+      for (int i = 0; i < KK; ++i) {
+        u32x4 zb = z[i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) zb[e] = in ? zb[e] : 0u;
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[b][i]),
+                                                      __builtin_bit_cast(bf16x8, zb), acc, 0, 0, 0);
+      }
+    }
+  }
+  f32x4 y = part[0];
+#pragma unroll
+  for (int s = 1; s < kExpandMaxSplit; ++s)
+    if (s < p.S) y += part[s];
+  y += acc;
+  if (!live) return;
+  const int64_t o = static_cast<int64_t>(tok) * p.ldo[q] + mrow;
+  if (p.out_dtype == 1) {
+    const uint2 w = {f32_to_bf16_pair(y[0], y[1]), f32_to_bf16_pair(y[2], y[3])};
+    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out[q]) + o) = w;
+  } else {
+    *reinterpret_cast<f32x4*>(static_cast<float*>(p.out[q]) + o) = y;
+  }
+}
+
 template <int OUT_BF16>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ part, int S,
                                                             int N, int M,
@@ -396,6 +493,22 @@ hipError_t launch_sigma(const float* zpart, int S, int T, int r, const int32_t* 
     else CTS_SIGMA_LAUNCH(bf16_t, 128, 16);
   }
 #undef CTS_SIGMA_LAUNCH
+  return hipGetLastError();
+}
+
+hipError_t launch_expand(const ExpandParams& p, hipStream_t stream) {
+  if (p.n_mod < 1 || p.n_mod > kMaxGemmModules || p.S < 1 || p.S > kExpandMaxSplit || p.r < 8 || p.r > 128 ||
+      p.T < 1 || p.rb[0] != 0)
+    return hipErrorInvalidValue;
+  for (int q = 0; q < p.n_mod; ++q)
+    if (p.M[q] % 8 || p.rb[q + 1] - p.rb[q] != (p.M[q] + 63) / 64) return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>(p.rb[p.n_mod]) * static_cast<unsigned>((p.T + 15) / 16));
+  switch ((p.r + 31) / 32) {
+    case 1: hipLaunchKernelGGL(expand_kernel<1>, grid, dim3(256), 0, stream, p); break;
+    case 2: hipLaunchKernelGGL(expand_kernel<2>, grid, dim3(256), 0, stream, p); break;
+    case 3: hipLaunchKernelGGL(expand_kernel<3>, grid, dim3(256), 0, stream, p); break;
+    default: hipLaunchKernelGGL(expand_kernel<4>, grid, dim3(256), 0, stream, p); break;
+  }
   return hipGetLastError();
 }
 

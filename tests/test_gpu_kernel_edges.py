@@ -94,3 +94,50 @@ def test_bf16_output_is_the_rounded_fp32_output(T, d_out):
     nan = torch.isnan(want)
     assert torch.equal(torch.isnan(y16), nan)
     assert torch.equal(y16.view(torch.int16)[~nan], want.view(torch.int16)[~nan])
+
+
+@pytest.mark.parametrize("T,d_in,d_out,r,K", [
+    (1, 8, 8, 8, 1),              # one token, one k-tile, an eighth of a row block
+    (15, 72, 72, 40, 5),
+    (16, 200, 136, 8, 7),         # exactly one block of positions
+    (17, 264, 64, 64, 17),        # one position over
+    (63, 520, 72, 72, 9),
+    (64, 2056, 200, 32, 30),
+    (65, 256, 136, 128, 40),      # a second token tile of one token
+    (128, 1032, 264, 16, 3),      # the last size that rides with the shrink
+    (129, 136, 136, 16, 3),       # the first that does not
+    (128, 64, 8200, 8, 4),        # 258 tiles: more than one round
+])
+def test_small_batch_edges(oracle_mod, T, d_in, d_out, r, K):
+    r = min(r, d_in, d_out)
+    w = wl.synthetic("small", cfg=4700 + T + d_in, T=T, d_in=d_in, d_out=d_out, r=r, n=max(K, 20), K=K, r_l=8,
+                     ids="uniform")
+    rk = wl.mixed_ranks(4700 + T, K, r, lo=8)
+    rk[0] = 0 if K > 1 else rk[0]
+    say("small T=%d %dx%d r=%d K=%d" % (T, d_in, d_out, r, K))
+    a = [dev(v) for v in (w.x, w.adapter_id, w.cluster_of, w.W, w.U, w.Vt, w.Sigma)]
+    ref = oracle_mod.apply(w.x, w.adapter_id, w.cluster_of, w.W, w.U, w.Vt, w.Sigma)
+    assert row_rel_err(host(cts.apply(*a)), ref) <= TOL["bf16"]
+    assert row_rel_err(host(cts.apply(*a, out_dtype=torch.float32)), ref) <= TOL["bf16"]
+    assert row_rel_err(host(cts.apply_ranked(*a, dev(rk))),
+                       oracle_mod.apply_ranked(w.x, w.adapter_id, w.cluster_of, w.W, w.U, w.Vt, w.Sigma,
+                                               rk)) <= TOL["bf16"]
+    assert row_rel_err(host(cts.apply_uncompressed(a[0], a[1], a[3], dev(w.A), dev(w.B))),
+                       oracle_mod.apply_uncompressed(w.x, w.adapter_id, w.W, w.A, w.B)) <= TOL["bf16"]
+    # the same module twice and a narrow one in one call: from the ids and from
+    # a bucketing, rows of the packed output longer than the modules
+    Ws, Us, Ss = [a[3], a[3][:8], a[3]], [a[4], a[4][:, :8].contiguous(), a[4]], [a[6]] * 3
+    if r > 8:
+        Ws[1], Us[1] = a[3][:8].contiguous(), a[4][:, :8].contiguous()
+    Vt = torch.cat([a[5]] * 3, 1).contiguous()
+    out = torch.full((T, 2 * d_out + 16), 7.0, dtype=torch.bfloat16, device="cuda")
+    cts.apply_multi_packed(a[0], Ws, Us, Vt, Ss, adapter_id=a[1], cluster_of=a[2], out=out)
+    got = host(out)
+    for lo, hi, want in ((0, d_out, ref), (d_out, d_out + 8, ref[:, :8]), (d_out + 8, 2 * d_out + 8, ref)):
+        den = np.abs(ref).max(axis=1)
+        assert (np.abs(got[:, lo:hi] - want).max(axis=1) / den).max() <= TOL["bf16"]
+    assert (got[:, 2 * d_out + 8:] == 7.0).all()
+    perm, _, buck = cts.sort_by_cluster(a[1], a[2], w.n, K, bucketing=True)
+    out2 = torch.full_like(out, 7.0)
+    cts.apply_multi_packed(a[0], Ws, Us, Vt, Ss, perm=perm, bucketing=buck, out=out2)
+    assert torch.equal(out, out2)
