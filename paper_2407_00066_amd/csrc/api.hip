@@ -49,28 +49,25 @@ constexpr uint64_t kMaxOperandBytes = 0x7fffffffull;   // buffer-load offsets ar
 
 int ceil_div(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }
 
-// The bf16 shrink's split along d_in follows the tile count on the device:
-// `target` workgroups, at least `kmin` k-tiles each.  Alone it takes 512 (256
-// where every workgroup buckets the tokens itself); beside the dense product
-// it has that product's time to finish in, so fewer, longer pieces (q/k/v of 33
-// tokens: 36.4 us a call at 128 and 8, 40.8 at 256, 42.6 at 64).
+// The shrink's split along d_in follows the tile count on the device: `target`
+// workgroups, at least `kmin` k-tiles each.  Alone it takes 512 (256 where every
+// workgroup buckets the tokens itself); beside the dense product it has that
+// product's time to finish in, so fewer, longer pieces (q/k/v of 33 tokens:
+// 36.4 us a call at 128 and 8, 40.8 at 256, 42.6 at 64).
 struct ShrinkSplit { int target, kmin; };
-ShrinkSplit shrink_rule(int T, bool small) {
+ShrinkSplit shrink_rule(int dtype, int T, bool small) {
   if (small) return {128, 8};
+  if (dtype == CTS_F32) return {512, 2};
   return T > cts::kFuseSortMaxT ? ShrinkSplit{512, 8} : ShrinkSplit{256, 2};
 }
 
-// The most pieces the shrink may split `rank` rank rows into: for the bf16
-// tile the split for the fewest tiles, ceil(T / 64); for fp32, which is not
-// chosen on the device, 512 workgroups over an estimate of the tiles (token
-// tiles plus half of the possible segment starts), at least 2 k-tiles each.
-int shrink_split_of(int T, int rank, int nseg, int d_in, Tile t, bool small) {
+// The most pieces the shrink may split `rank` rank rows into: the split for
+// the fewest tiles, ceil(T / 64).
+int shrink_split_of(int dtype, int T, int rank, int d_in, Tile t, bool small) {
   int BM, BN, BK;
   cts::tile_dims(t, &BM, &BN, &BK);
-  const bool f32 = t == Tile::F32;
-  const ShrinkSplit rule = f32 ? ShrinkSplit{512, 2} : shrink_rule(T, small);
-  const int expect = ceil_div(std::max(T, 1), BN) + (f32 ? std::min(nseg, std::max(T, 1)) / 2 : 0);
-  const int tiles = ceil_div(rank, BM) * std::max(expect, 1);
+  const ShrinkSplit rule = shrink_rule(dtype, T, small);
+  const int tiles = ceil_div(rank, BM) * ceil_div(std::max(T, 1), BN);
   const int nk = ceil_div(d_in, BK);
   return std::max(1, std::min(std::min(ceil_div(rule.target, tiles), std::max(1, nk / rule.kmin)), 64));
 }
@@ -163,7 +160,11 @@ int plan_piece(const cts_problem* p, bool compressed, Plan* pl) {
   };
   int max_split = 1;
   if (p->dtype == CTS_F32) {
+    // 64x64 tiles, three to a compute unit: split up to one round of 768 (500
+    // tokens, 1024 -> 2816, 352 tiles: 70 us a call unsplit, 63 in two pieces; 64
+    // tokens, 2048 -> 2048, 32 tiles: 83 and 33 in eight)
     pl->main_tile = Tile::F32;
+    max_split = 8;
   } else if (T >= 2048 && p->d_in >= 128) {       // (its prologue loads four whole 32-deep k-tiles)
     pl->main_tile = Tile::Large;
   } else if (T > 64 && (tiles_of(Tile::Wide) >= 192 || p->d_in >= 8192)) {
@@ -184,7 +185,8 @@ int plan_piece(const cts_problem* p, bool compressed, Plan* pl) {
     const int tiles = tiles_of(pl->main_tile);
     const int nk = ceil_div(p->d_in, BK);
     // no more workgroups than one round over the compute units
-    const int s = std::min(std::min(std::max(1, 256 / tiles), max_split), std::max(1, nk / 4));
+    const int round = p->dtype == CTS_F32 ? 768 : 256;
+    const int s = std::min(std::min(std::max(1, round / tiles), max_split), std::max(1, nk / 4));
     pl->main_split = std::max(1, s);
   }
   pl->small_split = small_split_of(p->dtype, T, ceil_div(p->d_out, 64), p->d_in);
@@ -192,7 +194,7 @@ int plan_piece(const cts_problem* p, bool compressed, Plan* pl) {
   // 64 rank rows, piece of d_in); the Sigma stage sums the pieces' partials
   pl->shrink_tile = (p->dtype == CTS_F32) ? Tile::F32 : Tile::Shrink;
   pl->max_ctiles = cts::max_seg_tiles(T, pl->nseg);
-  pl->shrink_split = shrink_split_of(T, pl->rank, pl->nseg, p->d_in, pl->shrink_tile, pl->small_split > 0);
+  pl->shrink_split = shrink_split_of(p->dtype, T, pl->rank, p->d_in, pl->shrink_tile, pl->small_split > 0);
   pl->max_items = cts::max_sigma_items(T, p->n_adapters);
 
   // every operand a kernel reads through a buffer resource must stay below 2^31 bytes
@@ -338,11 +340,8 @@ int run_layer(const cts_problem* p, const Plan& pl, bool compressed, const void*
   g.perm = perm; g.sorted_seg = sseg;
   g.ksplit = pl.shrink_split; g.part = zpart;
   g.tile_start = ctiles; g.n_tiles = n_ctiles; g.max_tiles = pl.max_ctiles; g.tile_seg = cseg;
-  int32_t* ssplit = nullptr;
-  if (pl.shrink_tile == Tile::Shrink) {
-    ssplit = reinterpret_cast<int32_t*>(ws + pl.off_ssplit);
-    g.split_target = shrink_rule(T, pl.small_split > 0).target; g.split_out = ssplit;
-  }
+  int32_t* ssplit = reinterpret_cast<int32_t*>(ws + pl.off_ssplit);
+  g.split_target = shrink_rule(p->dtype, T, pl.small_split > 0).target; g.split_out = ssplit;
   if (fuse_sort) {
     g.tile_start = nullptr; g.n_tiles = nullptr; g.tile_seg = nullptr;
     g.fs_item_aid = iaid;
@@ -627,7 +626,7 @@ int multi_plan_piece(const cts_problem* p, int M, const int32_t* d_out, MultiPla
   const int small = small_split_of(p->dtype, T, row_tiles, p->d_in);
   mp->small = small > 0;
   // shrink over the stacked rank: as for one module, with M r rank rows
-  mp->shrink_split = shrink_split_of(T, mp->rtot, p0.nseg, p->d_in, p0.shrink_tile, mp->small);
+  mp->shrink_split = shrink_split_of(p->dtype, T, mp->rtot, p->d_in, p0.shrink_tile, mp->small);
   size_t off = p0.off_zpart;                        // the shared sort arrays of module 0's layout
   mp->off_zpart = off; off = align_up(off + 4ull * mp->shrink_split * T * mp->rtot);
   mp->off_zp = off;    off = align_up(off + static_cast<size_t>(p0.elt) * T * mp->rtot);
@@ -751,11 +750,8 @@ int run_multi(const cts_problem* p, const MultiPlan& mp, const int32_t* d_out, c
   g.perm = perm; g.sorted_seg = sseg;
   g.ksplit = mp.shrink_split; g.part = zpart;
   g.tile_start = ctiles; g.n_tiles = n_ctiles; g.max_tiles = pl.max_ctiles; g.tile_seg = cseg;
-  int32_t* ssplit = nullptr;
-  if (pl.shrink_tile == Tile::Shrink) {
-    ssplit = reinterpret_cast<int32_t*>(ws + pl.off_ssplit);
-    g.split_target = shrink_rule(T, mp.small).target; g.split_out = ssplit;
-  }
+  int32_t* ssplit = reinterpret_cast<int32_t*>(ws + pl.off_ssplit);
+  g.split_target = shrink_rule(p->dtype, T, mp.small).target; g.split_out = ssplit;
   if (fuse_sort) {
     g.tile_start = nullptr; g.n_tiles = nullptr; g.tile_seg = nullptr;
     g.fs_item_aid = iaid;

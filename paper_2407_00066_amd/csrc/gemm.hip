@@ -12,16 +12,12 @@
 // k-split, then, for every cluster segment that intersects its token columns,
 // the k-tiles of that segment's basis with the other columns masked to zero.
 //
-// Global loads are raw buffer loads of 16 bytes: a row or k chunk outside
-// the operand gets an out-of-range offset and reads as zero, so the loads
-// carry no branches and all of a k-tile's loads are in flight together while
-// earlier k-tiles are multiplied out of LDS (two register stages and two LDS
-// buffers: each load has two k-tiles of compute to arrive; one barrier per
-// k-tile).  LDS rows are padded by 16 bytes, which
-// makes the 16-byte fragment reads of one MFMA conflict-free.
+// Global loads are raw buffer loads of 16 bytes straight into LDS: a row or k
+// chunk outside the operand gets an out-of-range offset and reads as zero, so
+// the loads carry no branches.
 //
-// Matrix cores: v_mfma_f32_32x32x16_bf16 or v_mfma_f32_16x16x32_bf16 (bf16
-// in, fp32 accumulate), v_mfma_f32_16x16x4_f32 for fp32 inputs.  Both
+// Matrix cores: v_mfma_f32_16x16x32_bf16 (bf16 in, fp32 accumulate),
+// v_mfma_f32_16x16x4_f32 for fp32 inputs.  Both
 // operands of a product use the same per-lane k assignment, so the hardware's
 // internal k order does not matter; only the accumulator layout (acc_row) is
 // fixed by the instruction.
@@ -31,35 +27,24 @@
 namespace cts {
 namespace {
 
-// MFMA shapes.  MB x MB output block per instruction; each lane holds KG
-// consecutive k of one row (A) or column (B): lane l -> row/column l % MB,
-// k group l / MB.
+// MFMA shapes.  MB x MB output block per step of KS k; each lane holds the KG
+// consecutive k of one 16-byte chunk of one row (A) or column (B): lane l ->
+// row/column l % MB, chunk l / MB.
 template <typename TI, int MB> struct MfmaTraits;
 template <> struct MfmaTraits<bf16_t, 16> {      // v_mfma_f32_16x16x32_bf16
-  static constexpr int EPC = 8, KS = 32, KG = 8, NACC = 4;
-  typedef bf16x8 frag;
+  static constexpr int KS = 32, KG = 8, NACC = 4, NI = 1;
   typedef f32x4 accv;
-  __device__ static __forceinline__ frag ld(const bf16_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
-  __device__ static __forceinline__ accv mma(frag a, frag b, accv c) {
+  __device__ static __forceinline__ accv mma(bf16x8 a, bf16x8 b, accv c, int = 0) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
 };
-template <> struct MfmaTraits<bf16_t, 32> {      // v_mfma_f32_32x32x16_bf16
-  static constexpr int EPC = 8, KS = 16, KG = 8, NACC = 16;
-  typedef bf16x8 frag;
-  typedef f32x16 accv;
-  __device__ static __forceinline__ frag ld(const bf16_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
-  __device__ static __forceinline__ accv mma(frag a, frag b, accv c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
-};
-template <> struct MfmaTraits<float, 16> {       // v_mfma_f32_16x16x4_f32
-  static constexpr int EPC = 4, KS = 4, KG = 1, NACC = 4;
-  typedef float frag;
+template <> struct MfmaTraits<float, 16> {       // 4 x v_mfma_f32_16x16x4_f32
+  // NI instructions a step; number e takes every lane's e-th value of its chunk
+  static constexpr int KS = 16, KG = 4, NACC = 4, NI = 4;
   typedef f32x4 accv;
-  __device__ static __forceinline__ frag ld(const float* p) { return *p; }
-  __device__ static __forceinline__ accv mma(frag a, frag b, accv c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  __device__ static __forceinline__ accv mma(bf16x8 a, bf16x8 b, accv c, int e) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f32x4, a)[e], __builtin_bit_cast(f32x4, b)[e], c, 0,
+                                                0, 0);
   }
 };
 
@@ -68,26 +53,6 @@ template <> struct MfmaTraits<float, 16> {       // v_mfma_f32_16x16x4_f32
 template <int MB> __device__ __forceinline__ int acc_row(int lane, int v) {
   return MB == 16 ? 4 * (lane >> 4) + v : 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
 }
-
-template <typename TI, int BM, int BN, int BK, int WM, int WN, int MB>
-struct Cfg {
-  static constexpr int NT = WM * WN * 64;
-  static constexpr int EPC = MfmaTraits<TI, MB>::EPC;
-  static constexpr int KS = MfmaTraits<TI, MB>::KS;
-  static constexpr int CPR = BK / EPC;                // 16-byte chunks per tile row
-  static constexpr int RPP = NT / CPR;                // tile rows covered per pass
-  static constexpr int LDS_ROW = BK + EPC;            // padded row, elements
-  static constexpr int CA = BM / RPP;                 // A chunks per thread
-  static constexpr int CB = BN / RPP;
-  static constexpr int WTM = BM / WM, WTN = BN / WN;
-  static constexpr int FM = WTM / MB, FN = WTN / MB;
-  static constexpr int AB_BYTES = 2 * (BM + BN) * LDS_ROW * (int)sizeof(TI);
-  static constexpr int ST_ROW = BM + 4;               // staged fp32 row (per token)
-  static constexpr int ST_BYTES = BN * ST_ROW * 4;
-  static constexpr int SMEM = AB_BYTES > ST_BYTES ? AB_BYTES : ST_BYTES;
-  static_assert(NT % CPR == 0 && BM % RPP == 0 && BN % RPP == 0, "chunk split");
-  static_assert(WTM % MB == 0 && WTN % MB == 0 && BK % KS == 0, "tile shape");
-};
 
 __device__ __forceinline__ int split_lo(int n, int ks, int S) { return (int)((int64_t)n * ks / S); }
 
@@ -133,266 +98,8 @@ int xcd_group_m(int gm, int gn, int S) {
   return kGroupM;
 }
 
-// STAGES: register stages of global loads in flight; OCC: waves per SIMD the
-// register allocation must allow; MB: MFMA block (16 or 32).
-template <typename TI, int BM, int BN, int BK, int WM, int WN, int STAGES, int OCC, int MB>
-__global__ __launch_bounds__(WM * WN * 64, OCC) void seg_gemm_kernel(const GemmParams p) {
-  using C = Cfg<TI, BM, BN, BK, WM, WN, MB>;
-  using MT = MfmaTraits<TI, MB>;
-  typedef typename MT::accv accv;
-  typedef typename MT::frag frag;
-  constexpr uint32_t ELT = sizeof(TI);
-  const int gn = p.tile_start ? p.max_tiles : (p.N + BN - 1) / BN;
-
-  __shared__ __attribute__((aligned(16))) char smem[C::SMEM];
-  __shared__ int32_t t_perm[BN];
-  __shared__ int32_t t_seg[BN];
-  __shared__ int32_t run_start[BN + 1];
-  __shared__ int32_t wave_runs[C::NT / 64];
-
-  TI* smA = reinterpret_cast<TI*>(smem);
-  TI* smB = smA + 2 * BM * C::LDS_ROW;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int mt, nt, ks;
-  tile_of_block((p.M + BM - 1) / BM, gn, &mt, &nt, &ks, blockIdx.x, gridDim.x);
-  if (p.tile_start && nt >= p.n_tiles[0]) return;    // whole workgroup: no tile
-  const int m0 = mt * BM;
-  const int j0 = p.tile_start ? p.tile_start[nt] : nt * BN;
-  const int S = p.ksplit;
-  const int jn = p.tile_start ? (p.tile_start[nt + 1] - j0) : min(BN, p.N - j0);   // valid columns
-
-  // ---- token columns of this tile: perm, segment, and segment runs -------
-  for (int i = tid; i < BN; i += C::NT) {
-    t_perm[i] = (i < jn) ? p.perm[j0 + i] : 0;
-    t_seg[i] = (i < jn && p.sorted_seg) ? p.sorted_seg[j0 + i] : 0;
-  }
-  __syncthreads();
-  int n_runs = 0;
-  for (int base = 0; base < BN; base += C::NT) {
-    const int i = base + tid;
-    const bool st = (i < jn) && (i == 0 || t_seg[i] != t_seg[i - 1]);
-    const uint64_t bal = __ballot(st);
-    if (lane == 0) wave_runs[wave] = __popcll(bal);
-    __syncthreads();
-    int before = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < C::NT / 64; ++w) {
-      const int c = wave_runs[w];
-      before += (w < wave) ? c : 0;
-      total += c;
-    }
-    if (st) {
-      const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-      run_start[n_runs + before + __popcll(bal & lt)] = i;
-    }
-    n_runs += total;
-    __syncthreads();
-  }
-  if (!(p.sorted_seg && p.K1 > 0)) n_runs = 0;
-  if (tid == 0) run_start[n_runs] = jn;
-  __syncthreads();
-
-  // ---- k-tile schedule ----------------------------------------------------
-  const int nk0 = (p.K0 > 0) ? (p.K0 + BK - 1) / BK : 0;
-  const int nk1 = (p.K1 > 0) ? (p.K1 + BK - 1) / BK : 0;
-  int d_lo = 0, d_hi = 0, s_lo = 0, s_hi = 0;
-  if (nk0 > 0) {
-    d_lo = split_lo(nk0, ks, S); d_hi = split_lo(nk0, ks + 1, S);
-    if (ks == 0) { s_lo = 0; s_hi = nk1; }
-  } else {
-    s_lo = split_lo(nk1, ks, S); s_hi = split_lo(nk1, ks + 1, S);
-  }
-  const int nd = d_hi - d_lo, ns = s_hi - s_lo;
-  const int ntiles = nd + n_runs * ns;
-
-  // ---- per-thread load coordinates (fixed for the whole kernel) ------------
-  const int kc = tid % C::CPR;               // 16-byte chunk within a tile row
-  const int row0 = tid / C::CPR;             // first tile row, then + RPP each
-
-  const __amdgpu_buffer_rsrc_t rA0 = make_rsrc(p.A0, p.a0_bytes);
-  const __amdgpu_buffer_rsrc_t rB0 = make_rsrc(p.B0, p.b0_bytes);
-  const __amdgpu_buffer_rsrc_t rB1 = make_rsrc(p.B1, p.b1_bytes);
-
-  // byte offsets of this thread's rows in each phase (kOob: outside the operand)
-  uint32_t a0_row[C::CA], a1_row[C::CA], b0_row[C::CB], b1_row[C::CB];
-  int b_jl[C::CB];
-#pragma unroll
-  for (int i = 0; i < C::CA; ++i) {
-    const int m = m0 + row0 + i * C::RPP;
-    const bool ok = m < p.M;
-    a0_row[i] = ok ? static_cast<uint32_t>(m) * static_cast<uint32_t>(p.lda0) * ELT : kOob;
-    a1_row[i] = ok ? static_cast<uint32_t>(m) * static_cast<uint32_t>(p.lda1) * ELT : kOob;
-  }
-#pragma unroll
-  for (int i = 0; i < C::CB; ++i) {
-    const int jl = row0 + i * C::RPP;
-    const uint32_t tok = static_cast<uint32_t>(t_perm[jl]);
-    const uint32_t r1 = p.b1_gather ? tok : static_cast<uint32_t>(j0 + jl);
-    b_jl[i] = jl;
-    b0_row[i] = tok * static_cast<uint32_t>(p.ldb0) * ELT;
-    b1_row[i] = r1 * static_cast<uint32_t>(p.ldb1) * ELT;
-  }
-
-  // register stages of global loads: with S stages the loads of k-tile t+S are
-  // issued while k-tile t is multiplied out of LDS
-  u32x4 ra[STAGES][C::CA], rb[STAGES][C::CB];
-
-  // load cursor: tiles are loaded strictly in order, so the position in the
-  // schedule advances incrementally (no division per tile)
-  int lt = 0;          // next k-tile to load
-  int lq = 0;          // its segment run (segment phase)
-  int lkt = s_lo;      // its k-tile within the segment phase
-
-  // issue the loads of the next k-tile; past the end every load is out of
-  // range and reads zeros, so the code has no data-dependent branches
-  auto load_next = [&](u32x4 (&a)[C::CA], u32x4 (&b)[C::CB]) __attribute__((always_inline)) {
-    const bool valid = lt < ntiles;
-    const bool dense = lt < nd;
-    const int q = min(lq, max(n_runs - 1, 0));
-    const int lo = dense ? 0 : run_start[q];
-    const int hi = dense ? jn : run_start[q + 1];
-    const int seg = __builtin_amdgcn_readfirstlane(t_seg[lo]);
-    const __amdgpu_buffer_rsrc_t rA =
-        dense ? rA0
-              : make_rsrc(static_cast<const char*>(p.A1) + static_cast<int64_t>(seg) * p.a1_seg_bytes,
-                          p.a1_seg_bytes);
-    const __amdgpu_buffer_rsrc_t rB = dense ? rB0 : rB1;
-    const int kt = dense ? d_lo + lt : lkt;
-    const uint32_t k = static_cast<uint32_t>(kt * BK) + kc * C::EPC;
-    const int klim = dense ? p.K0 : (p.seg_rank ? seg_rank_of(p.seg_rank, seg, p.K1) : p.K1);
-    // out-of-range chunks get bit 31 set (every operand is < 2^31 bytes)
-    const uint32_t kmask = (valid && k < static_cast<uint32_t>(klim)) ? 0u : kOob;
-    const uint32_t kb = k * ELT;
-    const uint32_t span = static_cast<uint32_t>(hi - lo);
-    const uint32_t dsel = dense ? 0xffffffffu : 0u;   // phase select by mask arithmetic
-#pragma unroll
-    for (int i = 0; i < C::CA; ++i) a[i] = load16(rA, ((a1_row[i] ^ ((a0_row[i] ^ a1_row[i]) & dsel)) + kb) | kmask);
-#pragma unroll
-    for (int i = 0; i < C::CB; ++i) {
-      const uint32_t jmask = (static_cast<uint32_t>(b_jl[i] - lo) < span) ? 0u : kOob;
-      b[i] = load16(rB, ((b1_row[i] ^ ((b0_row[i] ^ b1_row[i]) & dsel)) + kb) | kmask | jmask);
-    }
-    if (!dense) {
-      ++lkt;
-      if (lkt >= s_hi) { lkt = s_lo; ++lq; }
-    }
-    ++lt;
-  };
-  auto store_tile = [&](const u32x4 (&a)[C::CA], const u32x4 (&b)[C::CB], int buf) __attribute__((always_inline)) {
-    TI* da = smA + buf * BM * C::LDS_ROW + row0 * C::LDS_ROW + kc * C::EPC;
-    TI* db = smB + buf * BN * C::LDS_ROW + row0 * C::LDS_ROW + kc * C::EPC;
-#pragma unroll
-    for (int i = 0; i < C::CA; ++i) *reinterpret_cast<u32x4*>(da + i * C::RPP * C::LDS_ROW) = a[i];
-#pragma unroll
-    for (int i = 0; i < C::CB; ++i) *reinterpret_cast<u32x4*>(db + i * C::RPP * C::LDS_ROW) = b[i];
-  };
-
-  const int wm = wave / WN, wn = wave % WN;
-  accv acc[C::FM][C::FN];
-#pragma unroll
-  for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-    for (int j = 0; j < C::FN; ++j)
-#pragma unroll
-      for (int v = 0; v < MT::NACC; ++v) acc[i][j][v] = 0.f;
-
-  const int frow = lane % MB, fk = (lane / MB) * MT::KG;
-  auto compute = [&](int buf) __attribute__((always_inline)) {
-    const TI* a = smA + buf * BM * C::LDS_ROW + (wm * C::WTM + frow) * C::LDS_ROW + fk;
-    const TI* b = smB + buf * BN * C::LDS_ROW + (wn * C::WTN + frow) * C::LDS_ROW + fk;
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += C::KS) {
-      frag fa[C::FM], fb[C::FN];
-#pragma unroll
-      for (int i = 0; i < C::FM; ++i) fa[i] = MT::ld(a + i * MB * C::LDS_ROW + kk);
-#pragma unroll
-      for (int j = 0; j < C::FN; ++j) fb[j] = MT::ld(b + j * MB * C::LDS_ROW + kk);
-#pragma unroll
-      for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j) acc[i][j] = MT::mma(fa[i], fb[j], acc[i][j]);
-    }
-  };
-
-  // prologue: k-tiles 0..STAGES-1 in flight, k-tile 0 staged in LDS buffer 0
-#pragma unroll
-  for (int s = 0; s < STAGES; ++s) load_next(ra[s], rb[s]);
-  store_tile(ra[0], rb[0], 0);
-  __syncthreads();
-  // k-tile u sits in register stage u % STAGES until it is stored to LDS
-  // buffer u % 2 at the end of step u-1; the loop is unrolled so that both
-  // indices are compile-time constants
-  constexpr int U = (STAGES % 2 == 0) ? STAGES : 2 * STAGES;
-  for (int t = 0; t < ntiles; t += U) {
-#pragma unroll
-    for (int s = 0; s < U; ++s) {
-      if (t + s >= ntiles) break;
-      load_next(ra[s % STAGES], rb[s % STAGES]);                      // k-tile t+s+STAGES
-      compute(s % 2);                                                  // k-tile t+s
-      store_tile(ra[(s + 1) % STAGES], rb[(s + 1) % STAGES], (s + 1) % 2);  // k-tile t+s+1
-      __syncthreads();
-    }
-  }
-
-  // ---- epilogue: stage fp32 tile as [token][row], then 16-byte stores ------
-  float* st = reinterpret_cast<float*>(smem);
-#pragma unroll
-  for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-    for (int j = 0; j < C::FN; ++j) {
-      const int col = wn * C::WTN + j * MB + lane % MB;
-      const int row = wm * C::WTM + i * MB;
-#pragma unroll
-      for (int v = 0; v < MT::NACC; v += 4)   // 4 consecutive rows per group
-        *reinterpret_cast<f32x4*>(st + col * C::ST_ROW + row + acc_row<MB>(lane, v)) =
-            f32x4{acc[i][j][v], acc[i][j][v + 1], acc[i][j][v + 2], acc[i][j][v + 3]};
-    }
-  __syncthreads();
-
-  if (p.part) {
-    float* part = p.part + static_cast<int64_t>(ks) * p.N * p.M;
-    constexpr int CPRO = BM / 4;
-    for (int c = tid; c < BN * CPRO; c += C::NT) {
-      const int jl = c / CPRO, mc = (c % CPRO) * 4;
-      if (jl < jn && m0 + mc < p.M)
-        *reinterpret_cast<f32x4*>(part + static_cast<int64_t>(j0 + jl) * p.M + m0 + mc) =
-            *reinterpret_cast<const f32x4*>(st + jl * C::ST_ROW + mc);
-    }
-  } else if (p.out_dtype == 1) {  // bf16 out, 8 values per 16-byte store
-    constexpr int CPRO = BM / 8;
-    uint16_t* out = static_cast<uint16_t*>(p.out);
-    for (int c = tid; c < BN * CPRO; c += C::NT) {
-      const int jl = c / CPRO, mc = (c % CPRO) * 8;
-      if (jl < jn && m0 + mc < p.M) {
-        const float* s = st + jl * C::ST_ROW + mc;
-        const f32x4 lo = *reinterpret_cast<const f32x4*>(s);
-        const f32x4 hi = *reinterpret_cast<const f32x4*>(s + 4);
-        uint4 v;
-        v.x = f32_to_bf16_pair(lo[0], lo[1]);
-        v.y = f32_to_bf16_pair(lo[2], lo[3]);
-        v.z = f32_to_bf16_pair(hi[0], hi[1]);
-        v.w = f32_to_bf16_pair(hi[2], hi[3]);
-        const int64_t row = p.out_perm ? t_perm[jl] : static_cast<int64_t>(j0 + jl);
-        *reinterpret_cast<uint4*>(out + row * p.ldo + m0 + mc) = v;
-      }
-    }
-  } else {  // fp32 out
-    constexpr int CPRO = BM / 4;
-    float* out = static_cast<float*>(p.out);
-    for (int c = tid; c < BN * CPRO; c += C::NT) {
-      const int jl = c / CPRO, mc = (c % CPRO) * 4;
-      if (jl < jn && m0 + mc < p.M) {
-        const int64_t row = p.out_perm ? t_perm[jl] : static_cast<int64_t>(j0 + jl);
-        *reinterpret_cast<f32x4*>(out + row * p.ldo + m0 + mc) =
-            *reinterpret_cast<const f32x4*>(st + jl * C::ST_ROW + mc);
-      }
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
-// bf16 variant with the k-tiles loaded straight into LDS.
+// The segmented GEMM on a ring of LDS stages (every shape but the prefill's).
 //
 // Each 16-byte buffer load writes its lane's chunk directly into LDS
 // (buffer_load_dwordx4 ... lds): one wave instruction fills 1 KB, i.e. 8 tile
@@ -413,49 +120,49 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void seg_gemm_kernel(const GemmP
 // flight), and the fragment reads are issued as ds_read_b128 in inline
 // assembly, so the compiler's blanket wait for LDS-writing loads before any
 // LDS read does not apply.
-template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT>
+template <typename TI, int BM, int BN, int BK, int WM, int WN, int MB, int P>
 struct DmaCfg {
   static constexpr int NT = WM * WN * 64, NW = WM * WN;
-  static constexpr int ROWB = BK * 2;                     // bytes per tile row
-  static constexpr int CH = BK / 8;                       // 16-byte chunks per row
+  static constexpr int ELT = sizeof(TI), EPC = 16 / ELT;  // elements per 16-byte chunk
+  static constexpr int ROWB = BK * ELT;                   // bytes per tile row
+  static constexpr int CH = ROWB / 16;                    // 16-byte chunks per row
   static constexpr int RPI = 1024 / ROWB;                 // rows per 1 KB load
   static constexpr int SB = (BM + BN) * ROWB;             // bytes per stage
   static constexpr int QA = BM / RPI / NW, QB = BN / RPI / NW; // 1 KB loads per wave per k-tile
   static constexpr int LPT = QA + QB;                     // loads per thread per k-tile
   static constexpr int WTM = BM / WM, WTN = BN / WN;
   static constexpr int FM = WTM / MB, FN = WTN / MB;
-  static constexpr int KS = (MB == 32) ? 16 : 32;         // k per MFMA
+  static constexpr int KS = MfmaTraits<TI, MB>::KS;       // k per multiply step
   static constexpr int NKS = BK / KS;
-  static constexpr int ST_ROW = BM + 4;
-  static constexpr int ST_BYTES = BN * ST_ROW * 4;
-  static constexpr int SMEM = (DIRECT || P * SB > ST_BYTES) ? P * SB : ST_BYTES;
+  static constexpr int SMEM = P * SB;
+  static constexpr int MAXE = (128 + BK - 1) / BK;        // adapter k-tiles per run: rank <= 128
   static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "load split");
   static_assert(WTM % MB == 0 && WTN % MB == 0 && BK % KS == 0, "wave tile");
-  static_assert(BK == 32 || BK == 64 || BK == 128, "row width");
+  static_assert(ROWB == 64 || ROWB == 128 || ROWB == 256, "row width");
   static_assert((P - 2) * LPT < 64, "vmcnt range");
 };
 
-// DIRECT: the epilogue writes straight from the accumulators (4 consecutive
-// output features of one token per lane) instead of staging the tile in LDS;
-// used when the fp32 tile does not fit in LDS.
+// The epilogue writes straight from the accumulators (4 consecutive output
+// features of one token per lane).
 // MODS: the launch may hold several modules (p.n_mod > 0).
 // DENSE: a shrink launch whose last p.d_blocks workgroups compute W x.
 // Both roles read their operands at once and neither waits for the other: at
 // 64 tokens, 4096 x 4096, 8.2 us for what took a shrink of 4.3 and a fused GEMM
 // of 9.3 us and the gap between them.  Four stages: at six and eight the longer
 // prologue costs more than the deeper ring gives (8.9 and 9.7 us).
-template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT, int FSORT = 0, int MODS = 0,
+template <typename TI, int BM, int BN, int BK, int WM, int WN, int MB, int P, int FSORT = 0, int MODS = 0,
           int DENSE = 0>
 __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const GemmParams p) {
-  using C = DmaCfg<BM, BN, BK, WM, WN, MB, P, DIRECT>;
-  using MT = MfmaTraits<bf16_t, MB>;
+  using C = DmaCfg<TI, BM, BN, BK, WM, WN, MB, P>;
+  using MT = MfmaTraits<TI, MB>;
   typedef typename MT::accv accv;
-  constexpr uint32_t ELT = 2;
+  constexpr uint32_t ELT = C::ELT;
+  constexpr int KEYW = C::ROWB / 2;                        // the swizzle's row width
 
   __shared__ __attribute__((aligned(1024))) char smem[C::SMEM];
   __shared__ int32_t t_perm[BN];
-  // adapter k-tiles (K1 <= 2 BK) closed by an entry of rank 0, and their number
-  __shared__ __attribute__((aligned(8))) uint64_t sched[2 * BN + 1];
+  // adapter k-tiles closed by an entry of rank 0, and their number
+  __shared__ __attribute__((aligned(8))) uint64_t sched[C::MAXE * BN + 1];
   __shared__ uint32_t n_sched_s;
   constexpr int FS = FSORT ? kFuseSortMaxT : 1;
   __shared__ uint64_t fs_raw[FS];                          // (key << 8) | token, in token order
@@ -555,8 +262,8 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   int mt, nt, ks;
   int s_pieces = p.ksplit;
   // the split along k follows the tile count only in the shrink's tile shape
-  // (64 x 64 x 64); the other shapes keep the straight mapping
-  constexpr bool kAdaptive = BM == 64 && BN == 64 && BK == 64;
+  // (64 x 64, 128-byte rows); the other shapes keep the straight mapping
+  constexpr bool kAdaptive = BM == 64 && BN == 64 && C::ROWB == 128;
   if (kAdaptive && tlist && p.split_target > 0) {
     // workgroups [0, gm n S) take the (row tile, tile, piece) triples, the
     // rest exit (whole workgroup, after every barrier above)
@@ -648,9 +355,9 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   // the key depends on the tile row modulo 16 only, and every wave's rows
   // start at a multiple of 16 plus RPI * wave
   static_assert((C::RPI * C::NW) % 16 == 0, "swizzle period");
-  const int lchunk = (lane % C::CH) ^ swz_key<BK>(C::RPI * wave + lrow);
+  const int lchunk = (lane % C::CH) ^ swz_key<KEYW>(C::RPI * wave + lrow);
   const uint32_t cbytes = static_cast<uint32_t>(lchunk * 16);
-  const uint32_t celem = static_cast<uint32_t>(lchunk * 8);
+  const uint32_t celem = static_cast<uint32_t>(lchunk * C::EPC);
   // Per-lane byte offsets of this lane's chunk at k = 0, for the dense (0)
   // and adapter (1) operands; kOob marks a row outside the operand (and, for
   // the dense token operand, a column outside the tile).  A k-tile adds its
@@ -784,16 +491,17 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
         const bool mine = ((start[q] >> lane) & 1ull) && run >= q_first &&
                           (q_step == 1 || (run - q_first) % q_step == 0);
         const int kl = min(max(v_rank[q], 0), K1);
-        const int c = mine ? max(0, min(s_hi, (kl + BK - 1) / BK) - s_lo) : 0;   // 0, 1 or 2
-        const uint64_t b0 = __ballot(c & 1), b1 = __ballot(c & 2);
-        const uint32_t at = tot + __popcll(b0 & lt_mask) + 2 * __popcll(b1 & lt_mask);
+        const int c = mine ? max(0, min(s_hi, (kl + BK - 1) / BK) - s_lo) : 0;   // at most MAXE <= 4
+        const uint64_t b0 = __ballot(c & 1), b1 = __ballot(c & 2), b2 = __ballot(c & 4);
+        const uint32_t at =
+            tot + __popcll(b0 & lt_mask) + 2 * __popcll(b1 & lt_mask) + 4 * __popcll(b2 & lt_mask);
         const uint32_t ex = static_cast<uint32_t>(lo) | (static_cast<uint32_t>(hi - lo) << 9);
         const uint64_t ey =
             static_cast<uint64_t>(static_cast<uint32_t>(v_seg[q]) | (static_cast<uint32_t>(kl) << 16)) << 32;
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < C::MAXE; ++i)
           if (i < c) lds_write8(sched_addr + 8u * (at + i), ey | (ex | (static_cast<uint32_t>(s_lo + i) << 18)));
-        tot += __popcll(b0) + 2 * __popcll(b1);
+        tot += __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
         run0 += __popcll(start[q]);
       }
     }
@@ -895,8 +603,8 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   uint32_t slot[C::NKS];                                    // swizzled chunk slot per k-step
 #pragma unroll
   for (int s2 = 0; s2 < C::NKS; ++s2) {
-    const int chunk = s2 * (C::KS / 8) + fg * (MT::KG / 8);
-    slot[s2] = static_cast<uint32_t>(((chunk ^ swz_key<BK>(fr)) * 16));
+    const int chunk = s2 * (C::KS / C::EPC) + fg * (MT::KG / C::EPC);
+    slot[s2] = static_cast<uint32_t>(((chunk ^ swz_key<KEYW>(fr)) * 16));
   }
 
   accv acc[C::FM][C::FN];
@@ -920,7 +628,8 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   // So no multiply step waits on fragment-read latency, and the barrier sits
   // behind MFMAs already issued.
   static_assert(C::NKS % 2 == 0, "fragment buffers alternate across k-tiles");
-  constexpr int NM = C::FM * C::FN;                          // MFMAs per step
+  constexpr int NBL = C::FM * C::FN;                         // blocks of the wave
+  constexpr int NM = NBL * MT::NI;                           // MFMAs per step, all blocks' first ones first
   constexpr int NR = C::FM + C::FN;                          // fragment reads per step
   constexpr int NLG = C::NKS > 2 ? C::NKS / 2 : 1;           // steps that issue loads
   constexpr int GPS = (C::LPT + NLG - 1) / NLG;              // loads per such step
@@ -934,8 +643,8 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
     else lds_read16(fb[buf][r - C::FM], sb + sl + (r - C::FM) * MB * C::ROWB);
   };
   auto mma = [&](int buf, int m) __attribute__((always_inline)) {
-    const int i = m / C::FN, j = m % C::FN;
-    acc[i][j] = MT::mma(fa[buf][i], fb[buf][j], acc[i][j]);
+    const int i = m % NBL / C::FN, j = m % C::FN;
+    acc[i][j] = MT::mma(fa[buf][i], fb[buf][j], acc[i][j], m / NBL);
   };
 
   lt = P - 1;
@@ -1031,88 +740,30 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   wait_vmcnt<0>();
   __syncthreads();
 
-  if (DIRECT) {
-    // ---- epilogue from registers: lane holds rows acc_row(v..v+3) of column l%MB
+  // ---- epilogue from registers: lane holds rows acc_row(v..v+3) of column l%MB
 #pragma unroll
-    for (int j = 0; j < C::FN; ++j) {
-      const int jl = wn * C::WTN + j * MB + lane % MB;
-      const bool jok = jl < jn;
-      const int64_t orow = p.out_perm ? t_perm[jl] : static_cast<int64_t>(j0 + jl);
+  for (int j = 0; j < C::FN; ++j) {
+    const int jl = wn * C::WTN + j * MB + lane % MB;
+    const bool jok = jl < jn;
+    const int64_t orow = p.out_perm ? t_perm[jl] : static_cast<int64_t>(j0 + jl);
 #pragma unroll
-      for (int i = 0; i < C::FM; ++i)
+    for (int i = 0; i < C::FM; ++i)
 #pragma unroll
-        for (int v = 0; v < MT::NACC; v += 4) {
-          const int m = m0 + wm * C::WTM + i * MB + acc_row<MB>(lane, v);
-          if (!jok || m >= Mv) continue;
-          const f32x4 val = f32x4{acc[i][j][v], acc[i][j][v + 1], acc[i][j][v + 2], acc[i][j][v + 3]};
-          if (partv) {
-            *reinterpret_cast<f32x4*>(partv + (static_cast<int64_t>(ks) * p.N + j0 + jl) * part_ld + m) = val;
-          } else if (p.out_dtype == 1) {
-            uint2 w;
-            w.x = f32_to_bf16_pair(val[0], val[1]);
-            w.y = f32_to_bf16_pair(val[2], val[3]);
-            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(outv) + orow * ldov + m) = w;
-          } else {
-            *reinterpret_cast<f32x4*>(static_cast<float*>(outv) + orow * ldov + m) = val;
-          }
+      for (int v = 0; v < MT::NACC; v += 4) {
+        const int m = m0 + wm * C::WTM + i * MB + acc_row<MB>(lane, v);
+        if (!jok || m >= Mv) continue;
+        const f32x4 val = f32x4{acc[i][j][v], acc[i][j][v + 1], acc[i][j][v + 2], acc[i][j][v + 3]};
+        if (partv) {
+          *reinterpret_cast<f32x4*>(partv + (static_cast<int64_t>(ks) * p.N + j0 + jl) * part_ld + m) = val;
+        } else if (p.out_dtype == 1) {
+          uint2 w;
+          w.x = f32_to_bf16_pair(val[0], val[1]);
+          w.y = f32_to_bf16_pair(val[2], val[3]);
+          *reinterpret_cast<uint2*>(static_cast<uint16_t*>(outv) + orow * ldov + m) = w;
+        } else {
+          *reinterpret_cast<f32x4*>(static_cast<float*>(outv) + orow * ldov + m) = val;
         }
-    }
-    return;
-  }
-
-  // ---- epilogue: stage fp32 tile as [token][row], then 16-byte stores ------
-  float* stg = reinterpret_cast<float*>(smem);
-#pragma unroll
-  for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-    for (int j = 0; j < C::FN; ++j) {
-      const int col = wn * C::WTN + j * MB + lane % MB;
-      const int row = wm * C::WTM + i * MB;
-#pragma unroll
-      for (int v = 0; v < MT::NACC; v += 4)
-        *reinterpret_cast<f32x4*>(stg + col * C::ST_ROW + row + acc_row<MB>(lane, v)) =
-            f32x4{acc[i][j][v], acc[i][j][v + 1], acc[i][j][v + 2], acc[i][j][v + 3]};
-    }
-  __syncthreads();
-
-  if (partv) {
-    float* part = partv + static_cast<int64_t>(ks) * p.N * part_ld;
-    constexpr int CPRO = BM / 4;
-    for (int c = tid; c < BN * CPRO; c += C::NT) {
-      const int jl = c / CPRO, mc = (c % CPRO) * 4;
-      if (jl < jn && m0 + mc < Mv)
-        *reinterpret_cast<f32x4*>(part + static_cast<int64_t>(j0 + jl) * part_ld + m0 + mc) =
-            *reinterpret_cast<const f32x4*>(stg + jl * C::ST_ROW + mc);
-    }
-  } else if (p.out_dtype == 1) {
-    constexpr int CPRO = BM / 8;
-    uint16_t* out = static_cast<uint16_t*>(outv);
-    for (int c = tid; c < BN * CPRO; c += C::NT) {
-      const int jl = c / CPRO, mc = (c % CPRO) * 8;
-      if (jl < jn && m0 + mc < Mv) {
-        const float* s = stg + jl * C::ST_ROW + mc;
-        const f32x4 lo = *reinterpret_cast<const f32x4*>(s);
-        const f32x4 hi = *reinterpret_cast<const f32x4*>(s + 4);
-        uint4 v;
-        v.x = f32_to_bf16_pair(lo[0], lo[1]);
-        v.y = f32_to_bf16_pair(lo[2], lo[3]);
-        v.z = f32_to_bf16_pair(hi[0], hi[1]);
-        v.w = f32_to_bf16_pair(hi[2], hi[3]);
-        const int64_t row = p.out_perm ? t_perm[jl] : static_cast<int64_t>(j0 + jl);
-        *reinterpret_cast<uint4*>(out + row * ldov + m0 + mc) = v;
       }
-    }
-  } else {
-    constexpr int CPRO = BM / 4;
-    float* out = static_cast<float*>(outv);
-    for (int c = tid; c < BN * CPRO; c += C::NT) {
-      const int jl = c / CPRO, mc = (c % CPRO) * 4;
-      if (jl < jn && m0 + mc < Mv) {
-        const int64_t row = p.out_perm ? t_perm[jl] : static_cast<int64_t>(j0 + jl);
-        *reinterpret_cast<f32x4*>(out + row * ldov + m0 + mc) =
-            *reinterpret_cast<const f32x4*>(stg + jl * C::ST_ROW + mc);
-      }
-    }
   }
 }
 
@@ -1507,7 +1158,7 @@ hipError_t launch_prefill(const GemmParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT = 0, int FSORT = 0, int MODS = 0,
+template <typename TI, int BM, int BN, int BK, int WM, int WN, int MB, int P, int FSORT = 0, int MODS = 0,
           int DENSE = 0>
 hipError_t launch_dma1(const GemmParams& p, hipStream_t stream) {
   const int gn = (p.tile_start || FSORT) ? p.max_tiles : (p.N + BN - 1) / BN;
@@ -1523,7 +1174,7 @@ hipError_t launch_dma1(const GemmParams& p, hipStream_t stream) {
   const int gm = mods ? p.mod_rt[p.n_mod] : (p.M + BM - 1) / BM;
   dim3 grid(gm * gn * p.ksplit);
   if ((p.tile_start || FSORT) && p.split_target > 0) {
-    if (!(BM == 64 && BN == 64 && BK == 64)) return hipErrorInvalidValue;   // no adaptive split here
+    if (!(BM == 64 && BN == 64 && BK * sizeof(TI) == 128)) return hipErrorInvalidValue;   // no adaptive split here
     // gm n S workgroups are used: fewer than gm max_tiles + split_target, and
     // at most gm max_tiles ksplit
     const int64_t gmt = (p.M + BM - 1) / BM;
@@ -1545,33 +1196,25 @@ hipError_t launch_dma1(const GemmParams& p, hipStream_t stream) {
     q.group_m = xcd_group_m(dgm, dgn, p.d_split);
     grid.x += q.d_blocks;
   }
-  hipLaunchKernelGGL((seg_gemm_dma_kernel<BM, BN, BK, WM, WN, MB, P, DIRECT, FSORT, MODS, DENSE>),
+  hipLaunchKernelGGL((seg_gemm_dma_kernel<TI, BM, BN, BK, WM, WN, MB, P, FSORT, MODS, DENSE>),
                      grid, dim3(WM * WN * 64), 0, stream, q);
   return hipGetLastError();
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int MB, int P, int DIRECT = 0, int FSORT = 0>
+template <typename TI, int BM, int BN, int BK, int WM, int WN, int MB, int P, int FSORT = 0>
 hipError_t launch_dma(const GemmParams& p, hipStream_t stream) {
-  // the list of adapter k-tiles holds at most two per cluster run
-  if (!(p.tile_start || FSORT) && p.K1 > 2 * BK) return hipErrorInvalidValue;
+  // the list of adapter k-tiles has room for ranks of at most 128
+  if (!(p.tile_start || FSORT) && p.K1 > 128) return hipErrorInvalidValue;
   // (token tiles keep no output row numbers: they write partials only)
   if ((p.tile_start || FSORT) && !p.part) return hipErrorInvalidValue;
   if (p.seg_rank && !p.sorted_rank && !(p.tile_start || FSORT)) return hipErrorInvalidValue;
   if (p.n_mod > 0) {
     if (p.seg_rank || p.tile_start || FSORT) return hipErrorInvalidValue;
-    if constexpr (FSORT == 0) return launch_dma1<BM, BN, BK, WM, WN, MB, P, DIRECT, 0, 1>(p, stream);
+    if constexpr (FSORT == 0 && sizeof(TI) == 2)
+      return launch_dma1<TI, BM, BN, BK, WM, WN, MB, P, 0, 1>(p, stream);
+    return hipErrorInvalidValue;
   }
-  return launch_dma1<BM, BN, BK, WM, WN, MB, P, DIRECT, FSORT>(p, stream);
-}
-
-template <typename TI, int BM, int BN, int BK, int WM, int WN, int STAGES, int OCC, int MB = 16>
-hipError_t launch_cfg(const GemmParams& p, hipStream_t stream) {
-  // one linear dimension over (m-tile, n-tile, k-split), remapped in-kernel
-  const int gn = p.tile_start ? p.max_tiles : (p.N + BN - 1) / BN;
-  dim3 grid(((p.M + BM - 1) / BM) * gn * p.ksplit);
-  hipLaunchKernelGGL((seg_gemm_kernel<TI, BM, BN, BK, WM, WN, STAGES, OCC, MB>), grid,
-                     dim3(WM * WN * 64), 0, stream, p);
-  return hipGetLastError();
+  return launch_dma1<TI, BM, BN, BK, WM, WN, MB, P, FSORT>(p, stream);
 }
 
 }  // namespace
@@ -1584,8 +1227,7 @@ hipError_t launch_cfg(const GemmParams& p, hipStream_t stream) {
 //   Narrow  128 x  64 x 128, 4 waves, 3 stages     other T > 64
 //   Decode   64 x  64 x 128, 4 waves, 4 stages     T <= 64
 //   Shrink   64 x  64 x  64, 4 waves, 3 stages     the V_k^T X products
-//   Small    64 x  64 x  64, register-staged (bf16)
-//   F32      64 x  64 x  32, register-staged, fp32 inputs
+//   F32      64 x  64 x  32, 4 waves, 3 stages     fp32 inputs: every product
 void tile_dims(Tile tile, int* BM, int* BN, int* BK) {
   switch (tile) {
     case Tile::Large: *BM = 256; *BN = 256; *BK = 32; return;
@@ -1594,7 +1236,6 @@ void tile_dims(Tile tile, int* BM, int* BN, int* BK) {
     case Tile::Decode: *BM = 64; *BN = 64; *BK = 128; return;
     case Tile::Shrink: *BM = 64; *BN = 64; *BK = 64; return;
     case Tile::Mid: *BM = 128; *BN = 128; *BK = 64; return;
-    case Tile::Small: *BM = 64; *BN = 64; *BK = 64; return;
     case Tile::F32: *BM = 64; *BN = 64; *BK = 32; return;
   }
 }
@@ -1602,35 +1243,36 @@ void tile_dims(Tile tile, int* BM, int* BN, int* BK) {
 hipError_t launch_seg_gemm(const GemmParams& p, int in_dtype, Tile tile, hipStream_t stream) {
   // several modules in one launch: the LDS-ring tiles only, without token
   // tiles (but those of a shrink that holds the modules' dense product)
-  if (p.n_mod > 0 && (in_dtype == 0 || tile == Tile::Small || ((p.tile_start || p.fs_adapter) && !p.d_blocks)))
+  if (p.n_mod > 0 && (in_dtype == 0 || ((p.tile_start || p.fs_adapter) && !p.d_blocks)))
     return hipErrorInvalidValue;
   // the dense product rides with the bf16 shrink's token tiles only
   if (p.d_blocks > 0 && (in_dtype == 0 || tile != Tile::Shrink || !(p.tile_start || p.fs_adapter) || !p.part))
     return hipErrorInvalidValue;
   // explicit token tiles (at most kSegTile columns) only with the 64-wide tiles
   if (p.tile_start &&
-      !(tile == Tile::Decode || tile == Tile::Shrink || tile == Tile::Small || tile == Tile::F32))
+      !(tile == Tile::Decode || tile == Tile::Shrink || tile == Tile::F32))
     return hipErrorInvalidValue;
-  // the split chosen on the device exists in the bf16 shrink tile only
-  if (p.split_target > 0 && (in_dtype == 0 || tile != Tile::Shrink)) return hipErrorInvalidValue;
+  // the split chosen on the device exists in the shrinks' tiles only
+  if (p.split_target > 0 && tile != Tile::Shrink && tile != Tile::F32) return hipErrorInvalidValue;
   // in-kernel bucketing exists in the bf16 shrink tile only
   if (p.fs_adapter && (in_dtype == 0 || tile != Tile::Shrink || p.N > kFuseSortMaxT || p.tile_start))
     return hipErrorInvalidValue;
-  if (in_dtype == 0) return launch_cfg<float, 64, 64, 32, 2, 2, 1, 2, 16>(p, stream);
+  if ((in_dtype == 0) != (tile == Tile::F32)) return hipErrorInvalidValue;
   switch (tile) {
     case Tile::Large: return launch_prefill(p, stream);
-    case Tile::Wide: return launch_dma<256, 128, 64, 4, 2, 16, 3, 1>(p, stream);
-    case Tile::Narrow: return launch_dma<128, 64, 128, 4, 1, 16, 3, 1>(p, stream);
-    case Tile::Decode: return launch_dma<64, 64, 128, 2, 2, 16, 4, 1>(p, stream);
+    case Tile::Wide: return launch_dma<bf16_t, 256, 128, 64, 4, 2, 16, 3>(p, stream);
+    case Tile::Narrow: return launch_dma<bf16_t, 128, 64, 128, 4, 1, 16, 3>(p, stream);
+    case Tile::Decode: return launch_dma<bf16_t, 64, 64, 128, 2, 2, 16, 4>(p, stream);
     case Tile::Shrink:
       if (p.d_blocks > 0)
-        return p.fs_adapter ? launch_dma1<64, 64, 64, 2, 2, 16, 4, 1, 1, 0, 1>(p, stream)
-                            : launch_dma1<64, 64, 64, 2, 2, 16, 4, 1, 0, 0, 1>(p, stream);
-      if (p.fs_adapter) return launch_dma<64, 64, 64, 2, 2, 16, 3, 1, 1>(p, stream);
-      return launch_dma<64, 64, 64, 2, 2, 16, 3, 1>(p, stream);
-    case Tile::Mid: return launch_dma<128, 128, 64, 4, 2, 16, 4, 1>(p, stream);
-    default: return launch_cfg<bf16_t, 64, 64, 64, 2, 2, 2, 2, 32>(p, stream);
+        return p.fs_adapter ? launch_dma1<bf16_t, 64, 64, 64, 2, 2, 16, 4, 1, 0, 1>(p, stream)
+                            : launch_dma1<bf16_t, 64, 64, 64, 2, 2, 16, 4, 0, 0, 1>(p, stream);
+      if (p.fs_adapter) return launch_dma<bf16_t, 64, 64, 64, 2, 2, 16, 3, 1>(p, stream);
+      return launch_dma<bf16_t, 64, 64, 64, 2, 2, 16, 3>(p, stream);
+    case Tile::Mid: return launch_dma<bf16_t, 128, 128, 64, 4, 2, 16, 4>(p, stream);
+    case Tile::F32: return launch_dma<float, 64, 64, 32, 2, 2, 16, 3>(p, stream);
   }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace cts

@@ -141,3 +141,26 @@ def test_small_batch_edges(oracle_mod, T, d_in, d_out, r, K):
     out2 = torch.full_like(out, 7.0)
     cts.apply_multi_packed(a[0], Ws, Us, Vt, Ss, perm=perm, bucketing=buck, out=out2)
     assert torch.equal(out, out2)
+
+
+@pytest.mark.parametrize("T,d_in,d_out,r,K,r_l", [
+    (1, 8, 8, 8, 1, 4),           # a quarter of one k-tile; a rank of one chunk
+    (64, 40, 72, 40, 9, 12),      # fewer dense k-tiles than ring stages
+    (65, 2048, 64, 128, 30, 128), # four adapter k-tiles per run; the largest split
+    (500, 264, 1032, 64, 8, 64),
+    (1000, 136, 3208, 24, 3, 36), # 816 tiles: past one round, unsplit
+])
+def test_fp32_edges(oracle_mod, T, d_in, d_out, r, K, r_l):
+    r = min(r, d_in, d_out)
+    w = wl.synthetic("f32", cfg=4900 + T + d_in, T=T, d_in=d_in, d_out=d_out, r=r, n=max(K, 20), K=K, r_l=r_l,
+                     dtype="f32", ids="zipf")
+    rk = wl.mixed_ranks(4900 + T, K, r, lo=8)
+    say("fp32 T=%d %dx%d r=%d K=%d" % (T, d_in, d_out, r, K))
+    a = [dev(v) for v in (w.x, w.adapter_id, w.cluster_of, w.W, w.U, w.Vt, w.Sigma)]
+    assert row_rel_err(host(cts.apply(*a)), oracle_mod.apply(w.x, w.adapter_id, w.cluster_of, w.W, w.U, w.Vt,
+                                                             w.Sigma)) <= TOL["f32"]
+    assert row_rel_err(host(cts.apply_ranked(*a, dev(rk))),
+                       oracle_mod.apply_ranked(w.x, w.adapter_id, w.cluster_of, w.W, w.U, w.Vt, w.Sigma,
+                                               rk)) <= TOL["f32"]
+    assert row_rel_err(host(cts.apply_uncompressed(a[0], a[1], a[3], dev(w.A), dev(w.B))),
+                       oracle_mod.apply_uncompressed(w.x, w.adapter_id, w.W, w.A, w.B)) <= TOL["f32"]
