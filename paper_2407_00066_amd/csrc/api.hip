@@ -72,6 +72,48 @@ int shrink_split_of(int dtype, int T, int rank, int d_in, Tile t, bool small) {
   return std::max(1, std::min(std::min(ceil_div(rule.target, tiles), std::max(1, nk / rule.kmin)), 64));
 }
 
+int tile_split(Tile t, int T, int d_in, int d_out, int round, int cap) {
+  int BM, BN, BK;
+  cts::tile_dims(t, &BM, &BN, &BK);
+  const int tiles = ceil_div(d_out, BM) * ceil_div(std::max(T, 1), BN);
+  return std::max(1, std::min(std::min(round / tiles, cap), ceil_div(d_in, BK) / 4));
+}
+
+// The fused GEMM's tile for bf16 batches of more than 64 tokens is the one
+// whose rounds over the 256 compute units are estimated shortest.  A round
+// takes `fixed` us (setup and output) and `per64` us for 64 of the reduction
+// with every compute unit busy, down to 0.7 of that with few; a cluster run
+// costs a workgroup ceil(r / 64) such steps, and a prefill has few runs (its
+// tokens come in requests).  A split adds its partials' way through memory.
+// From a sweep of every tile over 45 shapes (T 192 .. 4096 of 4096 -> 1024,
+// 4096, 6144, 14336, 28672, 14336 -> 4096, 2048 -> 2048, 8192): the choice is
+// the fastest tile or within 5% of it.  Lines drawn by batch size alone took
+// 256x256 from 2048 tokens on: 4096 tokens, 4096 -> 1024 79 us against 37 with
+// 128x128; 2048 tokens, 14336 -> 4096 328 against 211 with 256x128.
+struct TileCost { Tile tile; int max_split; double fixed, per64; };
+constexpr TileCost kTileCosts[] = {
+    {Tile::Large, 1, 8.0, 1.50}, {Tile::Wide, 8, 6.0, 0.83}, {Tile::Mid, 8, 5.0, 0.52}, {Tile::Narrow, 8, 4.0, 0.45}};
+constexpr int kPrefillT = 2048;
+
+// 0: the tile does not take this reduction
+double tile_us(const TileCost& tc, int T, int d_in, int d_out, int rank, int nseg, int* split) {
+  if (tc.tile == Tile::Large && d_in < 128) return 0.0;   // its setup loads four whole 32-deep k-tiles
+  int BM, BN, BK;
+  cts::tile_dims(tc.tile, &BM, &BN, &BK);
+  const int nt = ceil_div(T, BN);
+  const int64_t tiles = static_cast<int64_t>(ceil_div(d_out, BM)) * nt;
+  const int s = tile_split(tc.tile, T, d_in, d_out, 256, tc.max_split);
+  *split = s;
+  const int64_t wgs = tiles * s, rounds = (wgs + 255) / 256;
+  const double fill = static_cast<double>(wgs) / static_cast<double>(256 * rounds);
+  const double runs = T < kPrefillT ? 1.0 + static_cast<double>(std::min(nseg, T)) / nt : 0.0;
+  // (256x256 multiplies only the 64-column parts that a run touches)
+  const double steps = (d_in / 64.0 + (tc.tile == Tile::Large ? 0.85 : 1.0) * runs * rank / 64.0) / s;
+  double us = rounds * (tc.fixed + tc.per64 * (0.7 + 0.3 * fill) * steps);
+  if (s > 1) us += 3.0 + 8.0 * s * T * d_out / 5e6;       // written and read once at 5 TB/s
+  return us;
+}
+
 // Pieces of d_in when the dense product W X rides with the shrink, 0 when it
 // does not.  It does for bf16 batches that the shrink can bucket itself and
 // whose 64 x 64 tiles fit one round of 256 compute units (4096 -> 14336: at 64
@@ -145,49 +187,28 @@ int plan_piece(const cts_problem* p, bool compressed, Plan* pl) {
   }
 
   const int T = p->T;
-  int BM, BN, BK;
-  // fused GEMM tile and k split.  Prefill-sized batches: 256x256 tiles.
-  // Smaller batches are bound by the weight stream and by how often each
-  // compute unit re-reads its operands from L2: 256x128 tiles when they alone
-  // give most compute units work or the reduction is long, else 128x128
-  // tiles while they still give at least 128 tiles, else 128x64 tiles, and
-  // 64x64 for decode batches; each split along k up to one round of 256
-  // workgroups (partials summed afterwards).
-  auto tiles_of = [&](Tile t) {
-    int bm, bn, bk;
-    cts::tile_dims(t, &bm, &bn, &bk);
-    return ceil_div(p->d_out, bm) * ceil_div(std::max(T, 1), bn);
-  };
-  int max_split = 1;
+  // fused GEMM tile and k split: up to one round of workgroups over the compute
+  // units, at least four k-tiles each (partials summed afterwards)
   if (p->dtype == CTS_F32) {
-    // 64x64 tiles, three to a compute unit: split up to one round of 768 (500
-    // tokens, 1024 -> 2816, 352 tiles: 70 us a call unsplit, 63 in two pieces; 64
-    // tokens, 2048 -> 2048, 32 tiles: 83 and 33 in eight)
+    // 64x64 tiles, three to a compute unit: a round of 768 (500 tokens, 1024 ->
+    // 2816, 352 tiles: 70 us a call unsplit, 63 in two pieces; 64 tokens, 2048 ->
+    // 2048, 32 tiles: 83 and 33 in eight)
     pl->main_tile = Tile::F32;
-    max_split = 8;
-  } else if (T >= 2048 && p->d_in >= 128) {       // (its prologue loads four whole 32-deep k-tiles)
-    pl->main_tile = Tile::Large;
-  } else if (T > 64 && (tiles_of(Tile::Wide) >= 192 || p->d_in >= 8192)) {
-    pl->main_tile = Tile::Wide;
-    max_split = 8;
-  } else if (T > 64 && tiles_of(Tile::Mid) >= 128) {
-    pl->main_tile = Tile::Mid;
-    max_split = 4;
-  } else if (T > 64) {
-    pl->main_tile = Tile::Narrow;
-    max_split = 4;
-  } else {
+    pl->main_split = tile_split(Tile::F32, T, p->d_in, p->d_out, 768, 8);
+  } else if (T <= 64) {
     pl->main_tile = Tile::Decode;
-    max_split = 4;
-  }
-  cts::tile_dims(pl->main_tile, &BM, &BN, &BK);
-  {
-    const int tiles = tiles_of(pl->main_tile);
-    const int nk = ceil_div(p->d_in, BK);
-    // no more workgroups than one round over the compute units
-    const int round = p->dtype == CTS_F32 ? 768 : 256;
-    const int s = std::min(std::min(std::max(1, round / tiles), max_split), std::max(1, nk / 4));
-    pl->main_split = std::max(1, s);
+    pl->main_split = tile_split(Tile::Decode, T, p->d_in, p->d_out, 256, 4);
+  } else {
+    double best = 0.0;
+    for (const TileCost& tc : kTileCosts) {
+      int s = 1;
+      const double us = tile_us(tc, T, p->d_in, p->d_out, pl->rank, pl->nseg, &s);
+      if (us > 0.0 && (best == 0.0 || us < best)) {
+        best = us;
+        pl->main_tile = tc.tile;
+        pl->main_split = s;
+      }
+    }
   }
   pl->small_split = small_split_of(p->dtype, T, ceil_div(p->d_out, 64), p->d_in);
   // shrink: one workgroup per (cluster segment tile of <= kSegTile tokens,
@@ -635,8 +656,8 @@ int multi_plan_piece(const cts_problem* p, int M, const int32_t* d_out, MultiPla
   for (int m = 0; m < M; ++m) mp->d_sum += d_out[m];
   // grouped when the one launch fits one round of workgroups over the
   // compute units (q/k/v at T = 512: 192 workgroups instead of three launches
-  // and three split-K sums); two launches of a round each are kept apart
-  // (gate/up at T = 512: 448 grouped workgroups were slower than 2 x 224)
+  // and three split-K sums; gate/up at T = 512: 224 of 256x256, 152 us for two
+  // launches of 81); more workgroups than a round are left to their own launches
   mp->grouped = false;
   if (mp->small) {
     mp->g_split = small;

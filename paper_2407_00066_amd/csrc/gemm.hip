@@ -284,7 +284,6 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   }
   // the operands of this workgroup's module: with several modules in the
   // launch, row tiles [mod_rt[m], mod_rt[m+1]) are module m's
-  const int mt_grid = mt;
   int Mv = p.M;
   const void* A0v = p.A0;
   const void* A1v = p.A1;
@@ -391,7 +390,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   } else {
     s_lo = split_lo(nk1, ks, S); s_hi = split_lo(nk1, ks + 1, S);
   }
-  const int nd = d_hi - d_lo, ns = s_hi - s_lo;
+  const int nd = d_hi - d_lo;
   // dense k-tiles that cover a whole BK slice: d_lo .. d_lo + nd_full - 1
   const int nd_full = nd - ((nd > 0 && d_hi * BK > K0) ? 1 : 0);
   auto dk = [&](int i) __attribute__((always_inline)) { return d_lo + i; };   // dense k-tile at position i
@@ -793,9 +792,9 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
 // T = 4096, 4096 x 4096, 17 clusters of rank 64: 124 -> 112 us a launch; the
 // two-stage 64-deep ring it replaces ran at 1315 cycles a unit, this at 1220.
 struct PrefillCfg {
-  static constexpr int BM = 256, BN = 256, BK = 32, NW = 8, NT = 512, P = 4;
+  static constexpr int BM = 256, BN = 256, BK = 32, NT = 512, P = 4;   // eight waves, 4 x 2
   static constexpr int ROWB = BK * 2, SB = (BM + BN) * ROWB;
-  static constexpr int WM = 4, WTM = 64, WTN = 128;   // waves 4 x 2
+  static constexpr int WTM = 64, WTN = 128;
   static constexpr int ST_ROWB = BM * 2 + 16;         // staged bf16 output row (bytes)
   static constexpr int SMEM = P * SB > BN * ST_ROWB ? P * SB : BN * ST_ROWB;
   static constexpr int MAXU = 4;                      // adapter units per run: rank <= 128
@@ -940,6 +939,7 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
   struct UnitLoad {
     __amdgpu_buffer_rsrc_t rA, rB;
     uint32_t av[2], bv[2];
+    uint32_t halves;                                  // the halves of this wave's columns that the unit has
   };
   int n_sched = 0;                                    // read after the first barrier
   auto read_entry = [&](int u, uint64_t& e) __attribute__((always_inline)) {
@@ -950,6 +950,7 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
     UnitLoad L;
     if (u < nd) {
       L.rA = rA0; L.rB = rB0;
+      L.halves = 3u;
       const uint32_t k = static_cast<uint32_t>(u * C::BK);
       const uint32_t mask = k + lchunk * 8 < static_cast<uint32_t>(K0) ? 0u : kOob;
 #pragma unroll
@@ -966,6 +967,8 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
       const uint32_t mask = k + lchunk * 8 < (ey >> 16) ? 0u : kOob;
       L.rA = make_rsrc(static_cast<const char*>(A1v) + seg * a1_seg_bytes, a1_seg_bytes);
       L.rB = rB1;
+      const int c0 = (wave & 1) * C::WTN, hi = lo + static_cast<int>(span);
+      L.halves = (lo < c0 + 64 && hi > c0 ? 1u : 0u) | (lo < c0 + 128 && hi > c0 + 64 ? 2u : 0u);
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const int m = m0 + lrow + 128 * j, jl = lrow + 128 * j;
@@ -1027,6 +1030,7 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
   n_sched = __builtin_amdgcn_readfirstlane(n_sched_v);
   const int ntot = nd + n_sched;
   UnitLoad L;
+  uint32_t ring_halves = 0xffu;                       // two bits for each unit in the ring, the next one lowest
 
   // unit u in slot S (= u % 4).  Its first half issues the token loads of unit
   // u + 3 (whose weight loads went out in the unit before), its second half
@@ -1060,6 +1064,7 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
     if (!FAST) {
       pin(entry);
       L = prep(u + C::P, entry);
+      ring_halves = (ring_halves >> 2) | (L.halves << 6);
     }
     if (S == 0 && u == 0) wait_vmcnt<4>();            // the prologue's order: weights, then tokens
     else if (S == 1 && u == 1) wait_vmcnt<6>();
@@ -1087,16 +1092,60 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
     unit(integral_constant<int, 2>{}, FastT{}, u + 2);
     unit(integral_constant<int, 3>{}, FastT{}, u + 3);
   }
-  L = prep(u + C::P - 1, 0);                          // a whole dense unit
-  while (u < ntot) {
+  L = prep(u + C::P - 1, 0);                          // a whole dense unit, as all four in the ring
+  // Few adapter units are long runs (a prefill's requests): interleaved like the
+  // dense ones.  Many are short runs: the loop below.  (T = 4096, 17 clusters,
+  // up to 6 units a tile: 148.8 us a call through the loop below, 145.3 here;
+  // T = 512, 4096 -> 28672, 50 clusters, some 50 units a tile: 151 us a launch
+  // through the loop, 154 here.)
+  const int n_inter = n_sched <= 16 ? ntot : nd;
+  while (u < n_inter) {
     unit(integral_constant<int, 0>{}, AnyT{}, u);
-    if (++u >= ntot) break;
+    if (++u >= n_inter) break;
     unit(integral_constant<int, 1>{}, AnyT{}, u);
-    if (++u >= ntot) break;
+    if (++u >= n_inter) break;
     unit(integral_constant<int, 2>{}, AnyT{}, u);
-    if (++u >= ntot) break;
+    if (++u >= n_inter) break;
     unit(integral_constant<int, 3>{}, AnyT{}, u);
     ++u;
+  }
+  // Adapter units.  A run has few of the tile's columns, so a wave multiplies
+  // only the halves of its columns that the unit's run touches and most waves
+  // only load and read: the fragments are read a unit at a time (the first ones
+  // again), and nothing is interleaved.
+  for (; u < ntot; ++u) {
+    const uint32_t so = static_cast<uint32_t>((u & 1) * C::SB);
+    const uint32_t aa = a_addr[0] + static_cast<uint32_t>((u & 2) * C::SB) + so;
+    const uint32_t ba = b_addr[0] + static_cast<uint32_t>((u & 2) * C::SB) + so;
+    const int slot = u & 3, prev = (u + 3) & 3;
+    uint64_t entry = 0;
+    wait_lgkmcnt<0>();
+    read_entry(u + C::P, entry);
+    unrolled<4>([&](auto i_c) __attribute__((always_inline)) {
+      constexpr int I = decltype(i_c)::value;
+      lds_read16_at<I * 16 * C::ROWB>(fa[0][I], aa);
+      lds_read16_at<I * 16 * C::ROWB>(fb[0][I], ba);
+      lds_read16_at<(4 + I) * 16 * C::ROWB>(fb[1][I], ba);
+    });
+    issue(L, prev, 2);
+    issue(L, prev, 3);
+    wait_lgkmcnt<0>();
+    pin(entry);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { pin(fa[0][i]); pin(fb[0][i]); pin(fb[1][i]); }
+    const uint32_t halves = ring_halves;
+    L = prep(u + C::P, entry);
+    ring_halves = (ring_halves >> 2) | (L.halves << 6);
+    wait_vmcnt<8>();
+    __builtin_amdgcn_s_barrier();
+    issue(L, slot, 0);
+    issue(L, slot, 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (halves & (1u << h))
+#pragma unroll
+        for (int m = 0; m < 16; ++m)
+          acc[m >> 2][4 * h + (m & 3)] = MT::mma(fa[0][m >> 2], fb[h][m & 3], acc[m >> 2][4 * h + (m & 3)]);
   }
   wait_lgkmcnt<0>();
   wait_vmcnt<0>();

@@ -164,3 +164,27 @@ def test_fp32_edges(oracle_mod, T, d_in, d_out, r, K, r_l):
                                                rk)) <= TOL["f32"]
     assert row_rel_err(host(cts.apply_uncompressed(a[0], a[1], a[3], dev(w.A), dev(w.B))),
                        oracle_mod.apply_uncompressed(w.x, w.adapter_id, w.W, w.A, w.B)) <= TOL["f32"]
+
+
+def test_grouped_prefill_tile():
+    """Two modules of one call in one launch of 256 x 256 tiles (224 of them),
+    against the same modules in calls of their own: the same products, summed
+    in another order, both rounded to bf16."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    T, d_in, d_out, r, n, K = 512, 4096, 14336, 16, 40, 4
+
+    def draw(*shape, s=1.0):
+        return (torch.randn(shape, generator=g, device="cuda") * s).to(torch.bfloat16)
+
+    x = draw(T, d_in)
+    aid = torch.randint(0, n, (T,), generator=g, device="cuda", dtype=torch.int32)
+    cof = torch.arange(n, device="cuda", dtype=torch.int32) % K
+    Ws, Us, Ss = ([draw(*sh, s=s) for _ in range(2)] for sh, s in
+                  (((d_out, d_in), 1 / 64), ((K, d_out, r), 1 / 8), ((n, r, r), 1 / 4)))
+    Vt = draw(K, 2 * r, d_in, s=1 / 64)
+    say("grouped prefill tile")
+    ys = cts.apply_multi(x, aid, cof, Ws, Us, Vt, Ss)
+    for m in range(2):
+        one = cts.apply(x, aid, cof, Ws[m], Us[m], Vt[:, m * r:(m + 1) * r].contiguous(), Ss[m], out_dtype=torch.float32)
+        assert row_rel_err(host(ys[m]), host(one)) <= TOL["bf16"]
