@@ -41,7 +41,7 @@ struct Plan {
   int main_split, shrink_split;
   int small_split;                // > 0: W X rides with the shrink in that many pieces
   int max_items, max_ctiles;
-  size_t off_perm, off_seg, off_aid, off_srank, off_offs, off_items, off_nitems, off_ctiles, off_nctiles,
+  size_t off_perm, off_seg, off_aid, off_srank, off_items, off_nitems, off_ctiles, off_nctiles,
       off_iaid, off_cseg, off_ssplit, off_zpart, off_zp, off_ypart, total;
 };
 
@@ -232,7 +232,6 @@ int plan_piece(const cts_problem* p, bool compressed, Plan* pl) {
   pl->off_seg = off;   off = align_up(off + 4ull * T);
   pl->off_aid = off;   off = align_up(off + 4ull * T);
   pl->off_srank = off; off = align_up(off + 4ull * T);
-  pl->off_offs = off;  off = align_up(off + 4ull * (pl->nseg + 1));
   pl->off_items = off; off = align_up(off + 4ull * (pl->max_items + 1));
   pl->off_nitems = off; off = align_up(off + 4);
   pl->off_ctiles = off; off = align_up(off + 4ull * (pl->max_ctiles + 1));
@@ -327,7 +326,6 @@ int run_layer(const cts_problem* p, const Plan& pl, bool compressed, const void*
   int32_t* sseg = reinterpret_cast<int32_t*>(ws + pl.off_seg);
   int32_t* said = reinterpret_cast<int32_t*>(ws + pl.off_aid);
   int32_t* srank = reinterpret_cast<int32_t*>(ws + pl.off_srank);
-  int32_t* offs = reinterpret_cast<int32_t*>(ws + pl.off_offs);
   int32_t* items = reinterpret_cast<int32_t*>(ws + pl.off_items);
   int32_t* n_items = reinterpret_cast<int32_t*>(ws + pl.off_nitems);
   int32_t* ctiles = reinterpret_cast<int32_t*>(ws + pl.off_ctiles);
@@ -345,7 +343,7 @@ int run_layer(const cts_problem* p, const Plan& pl, bool compressed, const void*
   const bool fuse_sort = T <= cts::kFuseSortMaxT && pl.shrink_tile == Tile::Shrink;
   if (!fuse_sort) {
     e = cts::launch_sort(adapter_id, compressed ? cluster_of : nullptr, T, p->n_adapters,
-                         pl.nseg, perm, offs, sseg, said, items, n_items, ctiles, n_ctiles, stream, iaid, cseg);
+                         pl.nseg, perm, nullptr, sseg, said, items, n_items, ctiles, n_ctiles, stream, iaid, cseg);
     if (e != hipSuccess) return CTS_ERR_HIP;
   }
   if (mark(1, stream) != hipSuccess) return CTS_ERR_HIP;
@@ -381,8 +379,11 @@ int run_layer(const cts_problem* p, const Plan& pl, bool compressed, const void*
   e = cts::launch_seg_gemm(g, p->dtype, pl.shrink_tile, stream);
   if (e != hipSuccess || mark(2, stream) != hipSuccess) return CTS_ERR_HIP;
 
-  e = cts::launch_sigma(zpart, pl.shrink_split, T, rank, said, p->n_adapters, items, n_items,
-                        pl.max_items, compressed ? Sigma : nullptr, zp, p->dtype, stream, sigma_diag,
+  // without a full core, a small batch's last kernel takes the shrink's pieces itself
+  const bool fold = pl.small_split > 0 && (!compressed || sigma_diag);
+  if (!fold)
+    e = cts::launch_sigma(zpart, pl.shrink_split, T, rank, said, p->n_adapters, items, n_items,
+                          pl.max_items, compressed ? Sigma : nullptr, zp, p->dtype, stream, sigma_diag,
                         sseg, seg_rank, seg_rank ? srank : nullptr, 0, ssplit, nullptr, 0, iaid);
   if (e != hipSuccess || mark(3, stream) != hipSuccess) return CTS_ERR_HIP;
 
@@ -392,6 +393,11 @@ int run_layer(const cts_problem* p, const Plan& pl, bool compressed, const void*
     x.part = ypart; x.part_ld = p->d_out;
     x.perm = perm; x.sorted_seg = sseg; x.sorted_rank = seg_rank ? srank : nullptr;
     x.zp = zp; x.zp_bytes = static_cast<uint32_t>(static_cast<uint64_t>(T) * rank * pl.elt);
+    if (fold) {
+      x.zpart = zpart; x.zS = pl.shrink_split; x.zsplit = ssplit;
+      x.sdiag = compressed ? Sigma : nullptr; x.sorted_aid = said; x.n_adapters = p->n_adapters;
+      x.seg_rank = seg_rank;
+    }
     x.out_dtype = p->out_dtype;
     x.n_mod = 1; x.rb[1] = ceil_div(p->d_out, 64); x.M[0] = p->d_out;
     x.U[0] = Ubasis;
@@ -722,7 +728,6 @@ int run_multi(const cts_problem* p, const MultiPlan& mp, const int32_t* d_out, c
   int32_t* perm = reinterpret_cast<int32_t*>(ws + pl.off_perm);
   int32_t* sseg = reinterpret_cast<int32_t*>(ws + pl.off_seg);
   int32_t* said = reinterpret_cast<int32_t*>(ws + pl.off_aid);
-  int32_t* offs = reinterpret_cast<int32_t*>(ws + pl.off_offs);
   int32_t* items = reinterpret_cast<int32_t*>(ws + pl.off_items);
   int32_t* n_items = reinterpret_cast<int32_t*>(ws + pl.off_nitems);
   int32_t* ctiles = reinterpret_cast<int32_t*>(ws + pl.off_ctiles);
@@ -753,7 +758,7 @@ int run_multi(const cts_problem* p, const MultiPlan& mp, const int32_t* d_out, c
   if (e != hipSuccess) return CTS_ERR_HIP;
   const bool fuse_sort = !ext && T <= cts::kFuseSortMaxT && pl.shrink_tile == Tile::Shrink;
   if (!fuse_sort && !ext) {
-    e = cts::launch_sort(adapter_id, cluster_of, T, p->n_adapters, pl.nseg, perm, offs, sseg, said, items, n_items,
+    e = cts::launch_sort(adapter_id, cluster_of, T, p->n_adapters, pl.nseg, perm, nullptr, sseg, said, items, n_items,
                          ctiles, n_ctiles, stream, iaid, cseg);
     if (e != hipSuccess) return CTS_ERR_HIP;
   }

@@ -58,7 +58,7 @@ inline int max_seg_tiles(int T, int nseg) {
 // are the sorted positions where a run of one adapter starts or crosses a
 // multiple of kSigmaChunk, items[c] = T, and n_items[0] = c; likewise the
 // segment tiles ctiles/n_ctiles for runs of one cluster and kSegTile.
-// Optionally item_aid[i] (the adapter of item i) and ctile_seg[i] (the
+// (offs may be null.)  Optionally item_aid[i] (the adapter of item i) and ctile_seg[i] (the
 // cluster of tile i), so that the later stages need not look them up
 // through the sorted positions.
 // cluster_of may be null (every adapter its own cluster, K == n).
@@ -194,6 +194,12 @@ struct ExpandParams {
   const int32_t* perm; const int32_t* sorted_seg;
   const int32_t* sorted_rank;      // optional
   const void* zp; uint32_t zp_bytes;
+  // instead of zp (zpart != null): z' = sigma_i z (elementwise, sdiag [n][r]) or
+  // z itself (sdiag null), z the sum of the shrink's zsplit[0] <= zS pieces
+  // zpart[s][j][ldz], rounded as zp; ranks from seg_rank (optional)
+  const float* zpart; int zS; const int32_t* zsplit;
+  const void* sdiag; const int32_t* sorted_aid; int n_adapters;
+  const int32_t* seg_rank;
   int out_dtype;
   int n_mod;
   int rb[kMaxGemmModules + 1];     // 64-row blocks before module q's

@@ -287,7 +287,9 @@ __global__ __launch_bounds__(kSigThreads) void sigma_kernel(const float* __restr
 // of a whole token tile, 48 runs of one adapter each ran one after the other).
 // 64 tokens, 4096 x 4096: 3.3 us at rank 64 with one cluster, 4.4 us with 48
 // rank-16 LoRAs (with the partial sum it replaces, 13 us of the fused GEMM).
-template <int KK>
+// FOLD: there is no full core, so z' is formed here from the shrink's pieces
+// (one launch less: 19.9 -> 18.1 us a call at 64 tokens over 100 rank-16 LoRAs).
+template <int KK, int FOLD>
 __global__ __launch_bounds__(256) void expand_kernel(const ExpandParams p) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   const int nrb = p.rb[p.n_mod];
@@ -303,14 +305,55 @@ __global__ __launch_bounds__(256) void expand_kernel(const ExpandParams p) {
   const int jc = lane & 15, g = lane >> 4;
   const int j = j0 + min(jc, jn - 1);                  // (columns past the last repeat it; never stored)
   const int tok = p.perm[j], seg = p.sorted_seg[j];
-  const int rk = p.sorted_rank ? p.sorted_rank[j] : p.r;
-  // z' of column jc, k = 32 i + 8 g ..
-  const __amdgpu_buffer_rsrc_t rZ = make_rsrc(p.zp, p.zp_bytes);
-  u32x4 z[KK];
+  int rk = p.r;
+  u32x4 z[KK];                                         // z' of column jc, k = 32 i + 8 g ..
+  if constexpr (!FOLD) {
+    if (p.sorted_rank) rk = p.sorted_rank[j];
+    const __amdgpu_buffer_rsrc_t rZ = make_rsrc(p.zp, p.zp_bytes);
 #pragma unroll
-  for (int i = 0; i < KK; ++i) {
-    const int k = 32 * i + 8 * g;
-    z[i] = load16(rZ, k < p.r ? static_cast<uint32_t>((j * p.ldz + p.zoff[q] + k) * 2) : kOob);
+    for (int i = 0; i < KK; ++i) {
+      const int k = 32 * i + 8 * g;
+      z[i] = load16(rZ, k < p.r ? static_cast<uint32_t>((j * p.ldz + p.zoff[q] + k) * 2) : kOob);
+    }
+  } else {
+    const int S = min(p.zsplit[0], p.zS);
+    int a = p.sdiag ? p.sorted_aid[j] : 0;
+    a = min(max(a, 0), p.n_adapters - 1);
+    if (p.seg_rank) rk = seg_rank_of(p.seg_rank, seg, p.r);
+    // pieces summed in order, four pieces' loads in flight; k past the rank is
+    // not read (a rank is a multiple of 8)
+#pragma unroll
+    for (int i = 0; i < KK; ++i) {
+      const int k = 32 * i + 8 * g;
+      const bool in = k < rk;
+      const float* src = p.zpart + static_cast<int64_t>(j) * p.ldz + (in ? k : 0);
+      const int64_t step = static_cast<int64_t>(p.T) * p.ldz;
+      f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+      for (int s = 0; s < S; s += 4) {
+        f32x4 x[4][2];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          if (s + b < S) {
+            x[b][0] = *reinterpret_cast<const f32x4*>(src + (s + b) * step);
+            x[b][1] = *reinterpret_cast<const f32x4*>(src + (s + b) * step + 4);
+          }
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          if (s + b < S) { lo += x[b][0]; hi += x[b][1]; }
+      }
+      if (p.sdiag) {
+        const uint4 v = *reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(p.sdiag) +
+                                                        static_cast<int64_t>(a) * p.r + (in ? k : 0));
+        float w[8];
+        Vec16<bf16_t>::widen(v, w);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { lo[e] *= w[e]; hi[e] *= w[4 + e]; }
+      }
+      z[i] = u32x4{f32_to_bf16_pair(lo[0], lo[1]), f32_to_bf16_pair(lo[2], lo[3]), f32_to_bf16_pair(hi[0], hi[1]),
+                   f32_to_bf16_pair(hi[2], hi[3])};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z[i][e] = in ? z[i][e] : 0u;
+    }
   }
   // the partials of rows m0 + 4 g .. + 3 (M is a multiple of 8: all or none of them exist)
   const int mrow = m0 + 4 * g;
@@ -503,12 +546,18 @@ hipError_t launch_expand(const ExpandParams& p, hipStream_t stream) {
   for (int q = 0; q < p.n_mod; ++q)
     if (p.M[q] % 8 || p.rb[q + 1] - p.rb[q] != (p.M[q] + 63) / 64) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(p.rb[p.n_mod]) * static_cast<unsigned>((p.T + 15) / 16));
+  if (p.zpart && (!p.zsplit || p.zS < 1 || p.n_mod != 1 || p.zoff[0] != 0 || (p.sdiag && !p.sorted_aid)))
+    return hipErrorInvalidValue;
+#define CTS_EXPAND_LAUNCH(KK_)                                                                 \
+  if (p.zpart) hipLaunchKernelGGL((expand_kernel<KK_, 1>), grid, dim3(256), 0, stream, p);     \
+  else hipLaunchKernelGGL((expand_kernel<KK_, 0>), grid, dim3(256), 0, stream, p)
   switch ((p.r + 31) / 32) {
-    case 1: hipLaunchKernelGGL(expand_kernel<1>, grid, dim3(256), 0, stream, p); break;
-    case 2: hipLaunchKernelGGL(expand_kernel<2>, grid, dim3(256), 0, stream, p); break;
-    case 3: hipLaunchKernelGGL(expand_kernel<3>, grid, dim3(256), 0, stream, p); break;
-    default: hipLaunchKernelGGL(expand_kernel<4>, grid, dim3(256), 0, stream, p); break;
+    case 1: CTS_EXPAND_LAUNCH(1); break;
+    case 2: CTS_EXPAND_LAUNCH(2); break;
+    case 3: CTS_EXPAND_LAUNCH(3); break;
+    default: CTS_EXPAND_LAUNCH(4); break;
   }
+#undef CTS_EXPAND_LAUNCH
   return hipGetLastError();
 }
 

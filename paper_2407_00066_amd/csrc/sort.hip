@@ -346,7 +346,7 @@ __global__ __launch_bounds__(NT) void sort_kernel(
   }
 
   // cluster offsets: first sorted position whose cluster is >= k
-  for (int k = tid; k <= K; k += NT) {
+  for (int k = tid; offs && k <= K; k += NT) {
     int lo = 0, hi = T;
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;

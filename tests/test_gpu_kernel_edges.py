@@ -188,3 +188,15 @@ def test_grouped_prefill_tile():
     for m in range(2):
         one = cts.apply(x, aid, cof, Ws[m], Us[m], Vt[:, m * r:(m + 1) * r].contiguous(), Ss[m], out_dtype=torch.float32)
         assert row_rel_err(host(ys[m]), host(one)) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("T,d_in,d_out,r,K,n", [(1, 64, 8, 8, 1, 1), (33, 14408, 72, 128, 6, 30), (128, 520, 136, 40, 9, 9)])
+def test_small_diagonal_edges(oracle_mod, T, d_in, d_out, r, K, n):
+    """Diagonal cores of small batches: one piece of the shrink, many (d_in past
+    14336), a rank past three 32-deep steps."""
+    r = min(r, d_in, d_out)
+    w = wl.synthetic("sdiag", cfg=5100 + T, T=T, d_in=d_in, d_out=d_out, r=r, n=n, K=K, ids="uniform", with_lora=False)
+    sg = wl.sigma_diagonals(5100 + T, n, r, "bf16")
+    say("small diag T=%d %dx%d r=%d" % (T, d_in, d_out, r))
+    y = host(cts.apply_diag(*[dev(v) for v in (w.x, w.adapter_id, w.cluster_of, w.W, w.U, w.Vt)], dev(sg)))
+    assert row_rel_err(y, oracle_mod.apply_diag(w.x, w.adapter_id, w.cluster_of, w.W, w.U, w.Vt, sg)) <= TOL["bf16"]
