@@ -248,6 +248,262 @@ __device__ __forceinline__ void acc_to_lds(const f32x4 (&acc)[NB], float* dst) {
     for (int v = 0; v < 4; ++v) dst[(16 * wave + 4 * fk + v) * kEpLd + 16 * nb + fr] = acc[nb][v];
 }
 
+// ------------------------------------------------------------ r x r systems
+// chol_body, one workgroup per z: G = sum_b gp[z][b] (fixed order).  chol = 0: writes G
+// to out[z].  chol = 1: G = R^T R (R upper, positive diagonal), writes R^-1.
+// chol = 2 (G symmetric positive definite): writes G^-1 = R^-1 R^-T.
+// chol = 3 (one workgroup): G = (sum_b gp[0][b]) o (sum_b gp[1][b]), the
+// elementwise product of two Gram matrices (positive definite when both
+// are), and writes G^-1 to out.
+// The columns are equilibrated first (G' = E G E, E = diag(G)^(-1/2), R =
+// R' E^-1): the columns of X = M U scale with M's eigenvalues, and without it
+// the fp32 Cholesky of a nearly converged basis breaks down.  A pivot below
+// 1e-12 (relative to the unit diagonal of G') is taken as 1e-12.
+// Blocked in 16 x 16 tiles so that the workgroup meets few barriers.  Per
+// block column J: wave 0 alone factors the diagonal tile in registers (lane c
+// holds column c; the entries other lanes need are read with readlane, at
+// constant lane indices) and inverts it the same way; then the waves form the
+// block row R'_J,c = R'_JJ^-T G'_J,c as products with that inverse, and every
+// thread updates the trailing triangle.  R'^-1 is built from the diagonal
+// tiles' inverses outward, one block diagonal at a time, and G'^-1 = R'^-1
+// R'^-T with an NB x NB register block of outputs per thread.
+__device__ __forceinline__ float lane_val(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+struct CholArgs { const float* gp; int nblk; int mode; float* out; int nblk1; };
+// LDS floats it needs at rank 16 NB
+template <int NB> __host__ __device__ constexpr int chol_floats() { return 2 * 16 * NB * (16 * NB + 1) + 16 * NB; }
+
+template <int NB>
+__device__ __forceinline__ void chol_body(float* lds, const CholArgs& a, int z) {
+  const float* gp = a.gp;
+  const int nblk = a.nblk, chol = a.mode, nblk1 = a.nblk1;
+  float* out = a.out;
+  constexpr int r = 16 * NB;
+  constexpr int ld = r + 1;
+  constexpr int rr = r * r;
+  float* const g = lds;
+  float* const inv = g + r * ld;
+  float* const esc = inv + r * ld;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  constexpr int NU = (rr + kJT - 1) / kJT;
+  // partials summed in block order, four blocks' loads in flight
+  auto sum_partials = [&](const float* src, int cnt, float (&acc)[NU]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) acc[u] = 0.f;
+    int b = 0;
+    for (; b + 4 <= cnt; b += 4) {
+      float v[4][NU];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+          v[q][u] = (tid + u * kJT < rr) ? src[static_cast<int64_t>(b + q) * rr + tid + u * kJT] : 0.f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int u = 0; u < NU; ++u) acc[u] += v[q][u];
+    }
+    for (; b < cnt; ++b)
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+        if (tid + u * kJT < rr) acc[u] += src[static_cast<int64_t>(b) * rr + tid + u * kJT];
+  };
+  float acc[NU];
+  sum_partials(gp + static_cast<int64_t>(z) * nblk * rr, nblk, acc);
+  if (chol == 3) {
+    // the second set's partials are nblk apart too, but only its first
+    // nblk1 blocks hold rows
+    float acc1[NU];
+    sum_partials(gp + static_cast<int64_t>(nblk) * rr, nblk1, acc1);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) acc[u] *= acc1[u];
+  }
+  float* dst = out + static_cast<int64_t>(z) * rr;
+  if (!chol) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if (tid + u * kJT < rr) dst[tid + u * kJT] = acc[u];
+    return;
+  }
+  // diagonal first (lane e % (r + 1) == 0 of the sums), then G' = E G E in place
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int e = tid + u * kJT;
+    if (e < rr && e % (r + 1) == 0) esc[e / (r + 1)] = acc[u] > 0.f ? 1.f / sqrtf(acc[u]) : 1.f;
+  }
+  for (int e = tid; e < r * ld; e += kJT) inv[e] = 0.f;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int e = tid + u * kJT;
+    if (e < rr) g[(e / r) * ld + e % r] = acc[u] * esc[e / r] * esc[e % r];
+  }
+  __syncthreads();
+
+  // ---- blocked right-looking Cholesky of G' (R' in the upper triangle of g,
+  // the diagonal tiles of R'^-1 in inv)
+#pragma unroll
+  for (int J = 0; J < NB; ++J) {
+    const int o = 16 * J;
+    if (wave == 0) {
+      // Lanes 16..63 repeat lanes 0..15.  Entries below the diagonal (i > c)
+      // are updated too, with values nothing reads: that saves the selects.
+      const int c = lane & 15;
+      float col[16], rdg[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) col[i] = g[(o + i) * ld + o + c];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const float dk = fmaxf(lane_val(col[k], k), 1e-12f);
+        const float rp = __builtin_amdgcn_rsqf(dk);      // 1 / R'[k][k]
+        rdg[k] = rp;
+        col[k] = (c == k) ? dk * rp : col[k] * rp;
+#pragma unroll
+        for (int i = k + 1; i < 16; ++i) col[i] = fmaf(-lane_val(col[k], i), col[k], col[i]);
+      }
+      // column c of R'_JJ^-1 by back substitution; R'[i][k] from lane k
+      float x[16];
+#pragma unroll
+      for (int i = 15; i >= 0; --i) {
+        float s = (i == c) ? 1.f : 0.f;
+#pragma unroll
+        for (int k = i + 1; k < 16; ++k) s = fmaf(-lane_val(col[i], k), x[k], s);
+        x[i] = (i <= c) ? s * rdg[i] : 0.f;
+      }
+      if (lane < 16)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          if (i <= c) g[(o + i) * ld + o + c] = col[i];
+          inv[(o + i) * ld + o + c] = x[i];
+        }
+    }
+    if (J + 1 == NB) break;
+    __syncthreads();
+    // block row: R'[o+i][cc] = sum_{k <= i} (R'_JJ^-1)[k][i] G'[o+k][cc] for
+    // cc >= o + 16.  Wave q takes columns o + 16 + 16 q + (lane % 16), lane / 16
+    // picks four rows.  Each column belongs to one wave, and no lane of it
+    // writes before every lane has read the whole column: each written value
+    // depends on all sixteen reads, and a wave executes in lockstep.
+    {
+      const int w = r - o - 16;
+      for (int cb = 16 * wave; cb < w; cb += 16 * (kJT / 64)) {
+        const int cc = o + 16 + cb + (lane & 15);
+        const int i0 = 4 * (lane >> 4);
+        float gk[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) gk[k] = g[(o + k) * ld + cc];
+        float y[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          y[q] = 0.f;
+#pragma unroll
+          for (int k = 0; k < 16; ++k) y[q] = fmaf(inv[(o + k) * ld + o + i0 + q], gk[k], y[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g[(o + i0 + q) * ld + cc] = y[q];
+      }
+    }
+    __syncthreads();
+    // trailing triangle: G'[i][c] -= sum_k R'[o+k][i] R'[o+k][c], o+16 <= i <= c
+    {
+      const int w = r - o - 16;
+      for (int e = tid; e < w * w; e += kJT) {
+        const int i = o + 16 + e / w, c = o + 16 + e % w;
+        if (c >= i) {
+          float s = g[i * ld + c];
+#pragma unroll
+          for (int k = 0; k < 16; ++k) s = fmaf(-g[(o + k) * ld + i], g[(o + k) * ld + c], s);
+          g[i * ld + c] = s;
+        }
+      }
+    }
+    __syncthreads();
+  }
+  __syncthreads();
+
+  // off-diagonal tiles of R'^-1 by distance d: X_IJ = -X_II sum_{K=I+1..J} R'_IK X_KJ.
+  // T_IJ is kept transposed in tile JI of g's strict lower triangle, which
+  // nothing reads after the factorization.
+#pragma unroll
+  for (int d = 1; d < NB; ++d) {
+    for (int e = tid; e < (NB - d) * 256; e += kJT) {
+      const int I = e / 256, a = (e % 256) / 16, bcol = e % 16;
+      const int J = I + d;
+      float s = 0.f;
+      for (int K = I + 1; K <= J; ++K)
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+          s = fmaf(g[(16 * I + a) * ld + 16 * K + k], inv[(16 * K + k) * ld + 16 * J + bcol], s);
+      g[(16 * J + bcol) * ld + 16 * I + a] = s;
+    }
+    __syncthreads();
+    for (int e = tid; e < (NB - d) * 256; e += kJT) {
+      const int I = e / 256, a = (e % 256) / 16, bcol = e % 16;
+      const int J = I + d;
+      float s = 0.f;
+#pragma unroll
+      for (int k = 0; k < 16; ++k)
+        s = fmaf(inv[(16 * I + a) * ld + 16 * I + k], g[(16 * J + bcol) * ld + 16 * I + k], s);
+      inv[(16 * I + a) * ld + 16 * J + bcol] = -s;
+    }
+    __syncthreads();
+  }
+  if (chol == 1) {
+    // R^-1 = E R'^-1
+    for (int e = tid; e < rr; e += kJT) dst[e] = inv[(e / r) * ld + e % r] * esc[e / r];
+    return;
+  }
+  // G^-1 = E R'^-1 R'^-T E; R'^-1 is upper triangular with explicit zeros
+  // below the diagonal, so every product runs over all r terms.  Thread
+  // (ti, tc) owns rows ti + 16 a and columns tc + 16 b (a, b < NB).
+  {
+    const int ti = tid >> 4, tc = tid & 15;
+    float accm[NB][NB];
+#pragma unroll
+    for (int a = 0; a < NB; ++a)
+#pragma unroll
+      for (int bb = 0; bb < NB; ++bb) accm[a][bb] = 0.f;
+    for (int k = 0; k < r; ++k) {
+      float ra[NB], rb[NB];
+#pragma unroll
+      for (int a = 0; a < NB; ++a) ra[a] = inv[(ti + 16 * a) * ld + k];
+#pragma unroll
+      for (int bb = 0; bb < NB; ++bb) rb[bb] = inv[(tc + 16 * bb) * ld + k];
+#pragma unroll
+      for (int a = 0; a < NB; ++a)
+#pragma unroll
+        for (int bb = 0; bb < NB; ++bb) accm[a][bb] = fmaf(ra[a], rb[bb], accm[a][bb]);
+    }
+#pragma unroll
+    for (int a = 0; a < NB; ++a)
+#pragma unroll
+      for (int bb = 0; bb < NB; ++bb) {
+        const int i = ti + 16 * a, c = tc + 16 * bb;
+        dst[i * r + c] = accm[a][bb] * esc[i] * esc[c];
+      }
+  }
+}
+
+template <int NB>
+__global__ __launch_bounds__(kJT) void jd_chol_kernel(const CholArgs a) {
+  __shared__ float lds[chol_floats<NB>()];
+  chol_body<NB>(lds, a, blockIdx.x);
+}
+
+// JD-Diag's systems need nothing of the projection or expansion beside them,
+// so for r <= 64, where their LDS fits those kernels' own, they are solved by
+// the first workgroup of that launch (CH = 1: blockIdx.x = 0 is the system's)
+// and not by a launch of one workgroup in between.  300 LoRAs, 2048 -> 5632, r =
+// 64: 34 us of every 400 us sweep for each of three systems;
+// 2036 -> 1499 us for five sweeps.
+__host__ __device__ constexpr bool chol_rides(int r) { return r <= 64; }
+template <int NB> __host__ __device__ constexpr int ride_floats() {
+  return 2 * stage_floats<NB>() > chol_floats<NB>() ? 2 * stage_floats<NB>() : chol_floats<NB>();
+}
+
 // ------------------------------------------------------------ project kernels
 // jd_pq_kernel: partial P or Q rows of a group of 64 / r_l LoRAs over one
 // half of the reduction; jd_combine_kernel: sums the halves and forms the
@@ -262,12 +518,16 @@ struct PqArgs {
   int zbase;                    // blockIdx.y + zbase: 0 = P, 1 = Q
 };
 
-template <int NB>
-__global__ __launch_bounds__(kJT) void jd_pq_kernel(const PqArgs a) {
-  __shared__ __attribute__((aligned(16))) float smem[2 * stage_floats<NB>()];
+template <int NB, int CH = 0>
+__global__ __launch_bounds__(kJT) void jd_pq_kernel(const PqArgs a, const CholArgs ch) {
+  __shared__ __attribute__((aligned(16))) float smem[CH ? ride_floats<NB>() : 2 * stage_floats<NB>()];
+  if (CH && blockIdx.x == 0) {                       // (whole workgroup)
+    if (blockIdx.y == 0 && blockIdx.z == 0) chol_body<NB>(smem, ch, 0);
+    return;
+  }
   constexpr int r = 16 * NB;
   const int lpw = kTM / a.r_l;
-  const int q0 = blockIdx.x * lpw;
+  const int q0 = (static_cast<int>(blockIdx.x) - CH) * lpw;
   const int nq = min(lpw, a.m - q0);
   if (nq <= 0) return;
   const bool isq = blockIdx.y + a.zbase == 1;
@@ -521,13 +781,17 @@ struct ExpArgs {
   int zbase;                    // blockIdx.z + zbase: 0 = U', 1 = V'
 };
 
-template <int NB>
-__global__ __launch_bounds__(kJT) void jd_expand_kernel(const ExpArgs a) {
-  __shared__ __attribute__((aligned(16))) float smem[2 * stage_floats<NB>()];
+template <int NB, int CH = 0>
+__global__ __launch_bounds__(kJT) void jd_expand_kernel(const ExpArgs a, const CholArgs ch) {
+  __shared__ __attribute__((aligned(16))) float smem[CH ? ride_floats<NB>() : 2 * stage_floats<NB>()];
+  if (CH && blockIdx.x == 0) {                       // (whole workgroup)
+    if (blockIdx.y == 0 && blockIdx.z == 0) chol_body<NB>(smem, ch, 0);
+    return;
+  }
   constexpr int r = 16 * NB;
   const bool isv = blockIdx.z + a.zbase == 1;
   const int d = isv ? a.d_in : a.d_out;
-  const int row0 = blockIdx.x * kTM;
+  const int row0 = (static_cast<int>(blockIdx.x) - CH) * kTM;
   if (row0 >= d) return;
   const int fk_total = a.m * a.r_l;
   const int ntile = (fk_total + kBK - 1) / kBK;
@@ -638,238 +902,6 @@ __global__ __launch_bounds__(kJT) void jd_gram_kernel(const float* X0, const flo
       const int x = a0 + 16 * wave + 4 * fq + v;
       if (x < r) out[x * r + 16 * nb + fr] = acc[nb][v];
     }
-}
-
-// One workgroup per z: G = sum_b gp[z][b] (fixed order).  chol = 0: writes G
-// to out[z].  chol = 1: G = R^T R (R upper, positive diagonal), writes R^-1.
-// chol = 2 (G symmetric positive definite): writes G^-1 = R^-1 R^-T.
-// chol = 3 (one workgroup): G = (sum_b gp[0][b]) o (sum_b gp[1][b]), the
-// elementwise product of two Gram matrices (positive definite when both
-// are), and writes G^-1 to out.
-// The columns are equilibrated first (G' = E G E, E = diag(G)^(-1/2), R =
-// R' E^-1): the columns of X = M U scale with M's eigenvalues, and without it
-// the fp32 Cholesky of a nearly converged basis breaks down.  A pivot below
-// 1e-12 (relative to the unit diagonal of G') is taken as 1e-12.
-// Blocked in 16 x 16 tiles so that the workgroup meets few barriers.  Per
-// block column J: wave 0 alone factors the diagonal tile in registers (lane c
-// holds column c; the entries other lanes need are read with readlane, at
-// constant lane indices) and inverts it the same way; then the waves form the
-// block row R'_J,c = R'_JJ^-T G'_J,c as products with that inverse, and every
-// thread updates the trailing triangle.  R'^-1 is built from the diagonal
-// tiles' inverses outward, one block diagonal at a time, and G'^-1 = R'^-1
-// R'^-T with an NB x NB register block of outputs per thread.
-__device__ __forceinline__ float lane_val(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-
-template <int NB>
-__global__ __launch_bounds__(kJT) void jd_chol_kernel(const float* gp, int nblk, int chol, float* out,
-                                                      int nblk1) {
-  constexpr int r = 16 * NB;
-  constexpr int ld = r + 1;
-  constexpr int rr = r * r;
-  __shared__ float g[r * ld];
-  __shared__ float inv[r * ld];
-  __shared__ float esc[r];
-  const int z = blockIdx.x, tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  constexpr int NU = (rr + kJT - 1) / kJT;
-  // partials summed in block order, four blocks' loads in flight
-  auto sum_partials = [&](const float* src, int cnt, float (&acc)[NU]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < NU; ++u) acc[u] = 0.f;
-    int b = 0;
-    for (; b + 4 <= cnt; b += 4) {
-      float v[4][NU];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int u = 0; u < NU; ++u)
-          v[q][u] = (tid + u * kJT < rr) ? src[static_cast<int64_t>(b + q) * rr + tid + u * kJT] : 0.f;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int u = 0; u < NU; ++u) acc[u] += v[q][u];
-    }
-    for (; b < cnt; ++b)
-#pragma unroll
-      for (int u = 0; u < NU; ++u)
-        if (tid + u * kJT < rr) acc[u] += src[static_cast<int64_t>(b) * rr + tid + u * kJT];
-  };
-  float acc[NU];
-  sum_partials(gp + static_cast<int64_t>(z) * nblk * rr, nblk, acc);
-  if (chol == 3) {
-    // the second set's partials are nblk apart too, but only its first
-    // nblk1 blocks hold rows
-    float acc1[NU];
-    sum_partials(gp + static_cast<int64_t>(nblk) * rr, nblk1, acc1);
-#pragma unroll
-    for (int u = 0; u < NU; ++u) acc[u] *= acc1[u];
-  }
-  float* dst = out + static_cast<int64_t>(z) * rr;
-  if (!chol) {
-#pragma unroll
-    for (int u = 0; u < NU; ++u)
-      if (tid + u * kJT < rr) dst[tid + u * kJT] = acc[u];
-    return;
-  }
-  // diagonal first (lane e % (r + 1) == 0 of the sums), then G' = E G E in place
-#pragma unroll
-  for (int u = 0; u < NU; ++u) {
-    const int e = tid + u * kJT;
-    if (e < rr && e % (r + 1) == 0) esc[e / (r + 1)] = acc[u] > 0.f ? 1.f / sqrtf(acc[u]) : 1.f;
-  }
-  for (int e = tid; e < r * ld; e += kJT) inv[e] = 0.f;
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < NU; ++u) {
-    const int e = tid + u * kJT;
-    if (e < rr) g[(e / r) * ld + e % r] = acc[u] * esc[e / r] * esc[e % r];
-  }
-  __syncthreads();
-
-  // ---- blocked right-looking Cholesky of G' (R' in the upper triangle of g,
-  // the diagonal tiles of R'^-1 in inv)
-#pragma unroll
-  for (int J = 0; J < NB; ++J) {
-    const int o = 16 * J;
-    if (wave == 0) {
-      // Lanes 16..63 repeat lanes 0..15.  Entries below the diagonal (i > c)
-      // are updated too, with values nothing reads: that saves the selects.
-      const int c = lane & 15;
-      float col[16], rdg[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) col[i] = g[(o + i) * ld + o + c];
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const float dk = fmaxf(lane_val(col[k], k), 1e-12f);
-        const float rp = __builtin_amdgcn_rsqf(dk);      // 1 / R'[k][k]
-        rdg[k] = rp;
-        col[k] = (c == k) ? dk * rp : col[k] * rp;
-#pragma unroll
-        for (int i = k + 1; i < 16; ++i) col[i] = fmaf(-lane_val(col[k], i), col[k], col[i]);
-      }
-      // column c of R'_JJ^-1 by back substitution; R'[i][k] from lane k
-      float x[16];
-#pragma unroll
-      for (int i = 15; i >= 0; --i) {
-        float s = (i == c) ? 1.f : 0.f;
-#pragma unroll
-        for (int k = i + 1; k < 16; ++k) s = fmaf(-lane_val(col[i], k), x[k], s);
-        x[i] = (i <= c) ? s * rdg[i] : 0.f;
-      }
-      if (lane < 16)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          if (i <= c) g[(o + i) * ld + o + c] = col[i];
-          inv[(o + i) * ld + o + c] = x[i];
-        }
-    }
-    if (J + 1 == NB) break;
-    __syncthreads();
-    // block row: R'[o+i][cc] = sum_{k <= i} (R'_JJ^-1)[k][i] G'[o+k][cc] for
-    // cc >= o + 16.  Wave q takes columns o + 16 + 16 q + (lane % 16), lane / 16
-    // picks four rows.  Each column belongs to one wave, and no lane of it
-    // writes before every lane has read the whole column: each written value
-    // depends on all sixteen reads, and a wave executes in lockstep.
-    {
-      const int w = r - o - 16;
-      for (int cb = 16 * wave; cb < w; cb += 16 * (kJT / 64)) {
-        const int cc = o + 16 + cb + (lane & 15);
-        const int i0 = 4 * (lane >> 4);
-        float gk[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) gk[k] = g[(o + k) * ld + cc];
-        float y[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          y[q] = 0.f;
-#pragma unroll
-          for (int k = 0; k < 16; ++k) y[q] = fmaf(inv[(o + k) * ld + o + i0 + q], gk[k], y[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) g[(o + i0 + q) * ld + cc] = y[q];
-      }
-    }
-    __syncthreads();
-    // trailing triangle: G'[i][c] -= sum_k R'[o+k][i] R'[o+k][c], o+16 <= i <= c
-    {
-      const int w = r - o - 16;
-      for (int e = tid; e < w * w; e += kJT) {
-        const int i = o + 16 + e / w, c = o + 16 + e % w;
-        if (c >= i) {
-          float s = g[i * ld + c];
-#pragma unroll
-          for (int k = 0; k < 16; ++k) s = fmaf(-g[(o + k) * ld + i], g[(o + k) * ld + c], s);
-          g[i * ld + c] = s;
-        }
-      }
-    }
-    __syncthreads();
-  }
-  __syncthreads();
-
-  // off-diagonal tiles of R'^-1 by distance d: X_IJ = -X_II sum_{K=I+1..J} R'_IK X_KJ.
-  // T_IJ is kept transposed in tile JI of g's strict lower triangle, which
-  // nothing reads after the factorization.
-#pragma unroll
-  for (int d = 1; d < NB; ++d) {
-    for (int e = tid; e < (NB - d) * 256; e += kJT) {
-      const int I = e / 256, a = (e % 256) / 16, bcol = e % 16;
-      const int J = I + d;
-      float s = 0.f;
-      for (int K = I + 1; K <= J; ++K)
-#pragma unroll
-        for (int k = 0; k < 16; ++k)
-          s = fmaf(g[(16 * I + a) * ld + 16 * K + k], inv[(16 * K + k) * ld + 16 * J + bcol], s);
-      g[(16 * J + bcol) * ld + 16 * I + a] = s;
-    }
-    __syncthreads();
-    for (int e = tid; e < (NB - d) * 256; e += kJT) {
-      const int I = e / 256, a = (e % 256) / 16, bcol = e % 16;
-      const int J = I + d;
-      float s = 0.f;
-#pragma unroll
-      for (int k = 0; k < 16; ++k)
-        s = fmaf(inv[(16 * I + a) * ld + 16 * I + k], g[(16 * J + bcol) * ld + 16 * I + k], s);
-      inv[(16 * I + a) * ld + 16 * J + bcol] = -s;
-    }
-    __syncthreads();
-  }
-  if (chol == 1) {
-    // R^-1 = E R'^-1
-    for (int e = tid; e < rr; e += kJT) dst[e] = inv[(e / r) * ld + e % r] * esc[e / r];
-    return;
-  }
-  // G^-1 = E R'^-1 R'^-T E; R'^-1 is upper triangular with explicit zeros
-  // below the diagonal, so every product runs over all r terms.  Thread
-  // (ti, tc) owns rows ti + 16 a and columns tc + 16 b (a, b < NB).
-  {
-    const int ti = tid >> 4, tc = tid & 15;
-    float accm[NB][NB];
-#pragma unroll
-    for (int a = 0; a < NB; ++a)
-#pragma unroll
-      for (int bb = 0; bb < NB; ++bb) accm[a][bb] = 0.f;
-    for (int k = 0; k < r; ++k) {
-      float ra[NB], rb[NB];
-#pragma unroll
-      for (int a = 0; a < NB; ++a) ra[a] = inv[(ti + 16 * a) * ld + k];
-#pragma unroll
-      for (int bb = 0; bb < NB; ++bb) rb[bb] = inv[(tc + 16 * bb) * ld + k];
-#pragma unroll
-      for (int a = 0; a < NB; ++a)
-#pragma unroll
-        for (int bb = 0; bb < NB; ++bb) accm[a][bb] = fmaf(ra[a], rb[bb], accm[a][bb]);
-    }
-#pragma unroll
-    for (int a = 0; a < NB; ++a)
-#pragma unroll
-      for (int bb = 0; bb < NB; ++bb) {
-        const int i = ti + 16 * a, c = tc + 16 * bb;
-        dst[i * r + c] = accm[a][bb] * esc[i] * esc[c];
-      }
-  }
 }
 
 // X_z[row][:] <- X_z[row][:] Rinv_z (64 rows per workgroup, in place: a
@@ -1441,7 +1473,8 @@ struct Jd {
 hipError_t launch_project(const Jd& j, const float* A, const float* B, const float* V, const float* U,
                           const int32_t* lidx, int m, int mode, const float* w2, const float* sscale,
                           float* Sigma, float* score, int ld_score, int score_col, int zbase = 0,
-                          int zcount = 2, const float* sdiag = nullptr, float* wout = nullptr) {
+                          int zcount = 2, const float* sdiag = nullptr, float* wout = nullptr,
+                          const CholArgs* ride = nullptr) {
   const cts_jd_problem* p = j.p;
   float* part = j.at<float>(j.pl.off_pq);
   PqArgs pa{A, B, V, U, lidx, m, p->r_lora, p->d_in, p->d_out, part, j.pl.pq_split, zbase};
@@ -1451,8 +1484,18 @@ hipError_t launch_project(const Jd& j, const float* A, const float* B, const flo
   const unsigned groups = static_cast<unsigned>((m + lpw - 1) / lpw);
   return with_nb(p->r, [&](auto c) {
     if (zcount > 0) {
-      hipLaunchKernelGGL(jd_pq_kernel<decltype(c)::value>, dim3(groups, zcount, j.pl.pq_split), dim3(kJT), 0, j.st,
-                         pa);
+      constexpr int NB = decltype(c)::value;
+      if constexpr (chol_rides(16 * NB)) {
+        if (ride)
+          hipLaunchKernelGGL((jd_pq_kernel<NB, 1>), dim3(groups + 1, zcount, j.pl.pq_split), dim3(kJT), 0, j.st, pa,
+                             *ride);
+        else
+          hipLaunchKernelGGL((jd_pq_kernel<NB, 0>), dim3(groups, zcount, j.pl.pq_split), dim3(kJT), 0, j.st, pa,
+                             CholArgs{});
+      } else {
+        hipLaunchKernelGGL((jd_pq_kernel<NB, 0>), dim3(groups, zcount, j.pl.pq_split), dim3(kJT), 0, j.st, pa,
+                           CholArgs{});
+      }
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
@@ -1488,8 +1531,8 @@ hipError_t orthonormalize(Jd& j, float* Un, float* Vn) {
   for (int pass = 0; pass < 2; ++pass) {
     if ((e = gram_pair(j, Un, Vn, nullptr, nullptr)) != hipSuccess) return e;
     e = with_nb(r, [&](auto c) {
-      hipLaunchKernelGGL(jd_chol_kernel<decltype(c)::value>, dim3(2), dim3(kJT), 0, j.st, gp, j.pl.nblk, 1, mat,
-                         j.pl.nblk);
+      hipLaunchKernelGGL(jd_chol_kernel<decltype(c)::value>, dim3(2), dim3(kJT), 0, j.st,
+                         CholArgs{gp, j.pl.nblk, 1, mat, j.pl.nblk});
       return hipGetLastError();
     });
     if (e != hipSuccess) return e;
@@ -1538,7 +1581,8 @@ hipError_t jd_step(Jd& j, const float* A, const float* B, const int32_t* lidx, i
   ExpArgs ea{A, B, lidx, m, p->r_lora, p->d_in, p->d_out, j.at<float>(j.pl.off_C),
              j.at<float>(j.pl.off_D), split, j.at<float>(j.pl.off_pU), j.at<float>(j.pl.off_pV), 0};
   e = with_nb(r, [&](auto c) {
-    hipLaunchKernelGGL(jd_expand_kernel<decltype(c)::value>, dim3(rowt, split, 2), dim3(kJT), 0, j.st, ea);
+    hipLaunchKernelGGL((jd_expand_kernel<decltype(c)::value, 0>), dim3(rowt, split, 2), dim3(kJT), 0, j.st, ea,
+                       CholArgs{});
     return hipGetLastError();
   });
   if (e != hipSuccess || (e = stage_mark(3, j.st)) != hipSuccess) return e;
@@ -1554,8 +1598,8 @@ hipError_t jd_step(Jd& j, const float* A, const float* B, const int32_t* lidx, i
   const int nrb = (std::max(p->d_out, p->d_in) + 63) / 64;
   if ((e = gram_pair(j, U, V, Un, Vn)) != hipSuccess) return e;
   e = with_nb(r, [&](auto c) {
-    hipLaunchKernelGGL(jd_chol_kernel<decltype(c)::value>, dim3(2), dim3(kJT), 0, j.st, gp, j.pl.nblk, 0, mat,
-                       j.pl.nblk);
+    hipLaunchKernelGGL(jd_chol_kernel<decltype(c)::value>, dim3(2), dim3(kJT), 0, j.st,
+                       CholArgs{gp, j.pl.nblk, 0, mat, j.pl.nblk});
     return hipGetLastError();
   });
   if (e != hipSuccess) return e;
@@ -1628,18 +1672,20 @@ int run_jd(Jd& j, const float* A, const float* B, const int32_t* lidx, int m, co
 // ---- JD-Diag by alternating least squares (App. A.1 case 2)
 // out = (X0^T X0 o X1^T X1)^-1 (X0: d0 rows, X1: d1 rows, r columns each);
 // the elementwise product of the two Gram matrices is positive definite
-// when both are
-hipError_t gram_hadamard_inverse(Jd& j, const float* X0, int d0, const float* X1, int d1, float* out) {
+// when both are.  The Gram partials are formed here; the system itself is
+// solved here too, or, where it can ride with the projection or expansion that
+// follows (chol_rides), left in *ride for that launch.
+hipError_t gram_hadamard_inverse(Jd& j, const float* X0, int d0, const float* X1, int d1, float* out, CholArgs* ride) {
   const int r = j.p->r;
   const int nb = (std::max(d0, d1) + kGramRows - 1) / kGramRows;
   float* gp = j.at<float>(j.pl.off_gp);
+  *ride = CholArgs{gp, nb, 3, out, (d1 + kGramRows - 1) / kGramRows};
   return with_nb(r, [&](auto c) {
     hipLaunchKernelGGL(jd_gram_kernel<decltype(c)::value>, dim3(nb, 2, (r + kTM - 1) / kTM), dim3(kJT), 0, j.st,
                        X0, X1, nullptr, nullptr, d0, d1, nb, gp);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(jd_chol_kernel<decltype(c)::value>, dim3(1), dim3(kJT), 0, j.st, gp, nb, 3, out,
-                       (d1 + kGramRows - 1) / kGramRows);
+    if (e != hipSuccess || chol_rides(r)) return e;
+    hipLaunchKernelGGL(jd_chol_kernel<decltype(c)::value>, dim3(1), dim3(kJT), 0, j.st, *ride);
     return hipGetLastError();
   });
 }
@@ -1658,7 +1704,7 @@ hipError_t apply_one(Jd& j, float* X, int d, int z, const float* M2) {
 // mark > 0 records that profiling event between the expansion kernel and the
 // sum of its pieces
 hipError_t expand_one(Jd& j, const float* A, const float* B, const int32_t* lidx, int m, int z, float* out,
-                      int mark = 0) {
+                      int mark = 0, const CholArgs* ride = nullptr) {
   const cts_jd_problem* p = j.p;
   const int r = p->r;
   const int64_t ntile = (static_cast<int64_t>(m) * p->r_lora + kBK - 1) / kBK;
@@ -1668,8 +1714,16 @@ hipError_t expand_one(Jd& j, const float* A, const float* B, const int32_t* lidx
   ExpArgs ea{A, B, lidx, m, p->r_lora, p->d_in, p->d_out, j.at<float>(j.pl.off_C), j.at<float>(j.pl.off_D),
              split, j.at<float>(j.pl.off_pU), j.at<float>(j.pl.off_pV), z};
   hipError_t e = with_nb(r, [&](auto c) {
-    hipLaunchKernelGGL(jd_expand_kernel<decltype(c)::value>, dim3((d + kTM - 1) / kTM, split, 1), dim3(kJT), 0, j.st,
-                       ea);
+    constexpr int NB = decltype(c)::value;
+    if constexpr (chol_rides(16 * NB)) {
+      if (ride) {
+        hipLaunchKernelGGL((jd_expand_kernel<NB, 1>), dim3((d + kTM - 1) / kTM + 1, split, 1), dim3(kJT), 0, j.st, ea,
+                           *ride);
+        return hipGetLastError();
+      }
+    }
+    hipLaunchKernelGGL((jd_expand_kernel<NB, 0>), dim3((d + kTM - 1) / kTM, split, 1), dim3(kJT), 0, j.st, ea,
+                       CholArgs{});
     return hipGetLastError();
   });
   if (e != hipSuccess || (mark > 0 && (e = stage_mark(mark, j.st)) != hipSuccess)) return e;
@@ -1691,11 +1745,13 @@ hipError_t als_sigma(Jd& j, const float* A, const float* B, const int32_t* lidx,
   float* sd = j.at<float>(j.pl.off_sd);
   float* w = j.at<float>(j.pl.off_wv);
   float* m = j.at<float>(j.pl.off_m);            // [3]: (U^T U o V^T V)^-1
-  hipError_t e = launch_project(j, A, B, V, U, lidx, p->n, 5, nullptr, nullptr, nullptr, nullptr, 0, 0,
-                                fresh ? 0 : 0, fresh ? 2 : 1, nullptr, w);
-  if (e != hipSuccess) return e;
   const int64_t rr = static_cast<int64_t>(r) * r;
-  if ((e = gram_hadamard_inverse(j, U, p->d_out, V, p->d_in, m + 3 * rr)) != hipSuccess) return e;
+  CholArgs sys;
+  hipError_t e = gram_hadamard_inverse(j, U, p->d_out, V, p->d_in, m + 3 * rr, &sys);
+  if (e != hipSuccess) return e;
+  e = launch_project(j, A, B, V, U, lidx, p->n, 5, nullptr, nullptr, nullptr, nullptr, 0, 0, 0, fresh ? 2 : 1, nullptr,
+                     w, chol_rides(r) ? &sys : nullptr);
+  if (e != hipSuccess) return e;
   const int64_t tot = static_cast<int64_t>(p->n) * r;
   return with_nb(r, [&](auto c) {
     hipLaunchKernelGGL(jd_diag_solve_kernel<decltype(c)::value>,
@@ -1716,19 +1772,21 @@ hipError_t als_sweep(Jd& j, const float* A, const float* B, const int32_t* lidx,
   const int64_t rr = static_cast<int64_t>(r) * r;
   float* sd = j.at<float>(j.pl.off_sd);
   float* m = j.at<float>(j.pl.off_m);
+  CholArgs sys;
+  const CholArgs* ride = chol_rides(r) ? &sys : nullptr;
   hipError_t e;
   // U = (sum_i B_i A_i V S_i)(V^T V o S2)^-1, S2 = sum_i s_i s_i^T
   {
     float* U = j.at<float>(j.pl.off_U);
     float* V = j.at<float>(j.pl.off_V);
     float* Un = j.at<float>(j.pl.off_Uo);
+    if ((e = gram_hadamard_inverse(j, V, p->d_in, sd, p->n, m + 4 * rr, &sys)) != hipSuccess) return e;
     if ((e = stage_mark(1, j.st)) != hipSuccess) return e;
     if ((e = launch_project(j, A, B, V, U, lidx, p->n, 3, nullptr, nullptr, nullptr, nullptr, 0, 0, 0,
                             p_current ? 0 : 1, sd, nullptr)) != hipSuccess)
       return e;
     if ((e = stage_mark(2, j.st)) != hipSuccess) return e;
-    if ((e = expand_one(j, A, B, lidx, p->n, 0, Un, 3)) != hipSuccess) return e;
-    if ((e = gram_hadamard_inverse(j, V, p->d_in, sd, p->n, m + 4 * rr)) != hipSuccess) return e;
+    if ((e = expand_one(j, A, B, lidx, p->n, 0, Un, 3, ride)) != hipSuccess) return e;
     if ((e = apply_one(j, Un, p->d_out, 0, m + 4 * rr)) != hipSuccess) return e;
     std::swap(j.pl.off_U, j.pl.off_Uo);
   }
@@ -1737,11 +1795,11 @@ hipError_t als_sweep(Jd& j, const float* A, const float* B, const int32_t* lidx,
     float* U = j.at<float>(j.pl.off_U);
     float* V = j.at<float>(j.pl.off_V);
     float* Vn = j.at<float>(j.pl.off_Vo);
-    if ((e = launch_project(j, A, B, V, U, lidx, p->n, 4, nullptr, nullptr, nullptr, nullptr, 0, 0, 1, 1, sd,
-                            nullptr)) != hipSuccess)
+    if ((e = gram_hadamard_inverse(j, U, p->d_out, sd, p->n, m + 5 * rr, &sys)) != hipSuccess) return e;
+    if ((e = launch_project(j, A, B, V, U, lidx, p->n, 4, nullptr, nullptr, nullptr, nullptr, 0, 0, 1, 1, sd, nullptr,
+                            ride)) != hipSuccess)
       return e;
     if ((e = expand_one(j, A, B, lidx, p->n, 1, Vn)) != hipSuccess) return e;
-    if ((e = gram_hadamard_inverse(j, U, p->d_out, sd, p->n, m + 5 * rr)) != hipSuccess) return e;
     if ((e = apply_one(j, Vn, p->d_in, 1, m + 4 * rr)) != hipSuccess) return e;   // slot 1 = m + 5 rr
     std::swap(j.pl.off_V, j.pl.off_Vo);
   }
