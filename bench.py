@@ -262,6 +262,8 @@ def time_launches(fn, sets, args, torch, one_call=False):
     return eager, chain, single
 
 
+# (of a small bf16 batch "shrink" holds the dense product too, and "fused_gemm"
+# is the kernel that adds U_k Z' to its partials)
 STAGES = ["sort", "shrink", "sigma", "fused_gemm", "splitk_reduce"]
 
 
@@ -284,16 +286,25 @@ def stage_times(fn, sets, steps, torch, cts):
     return out
 
 
-def gemm_times(fn, sets, steps, warmup, torch, cts):
+def rides_with_shrink(w):
+    """The dense product of a small bf16 batch runs in the shrink's launch and
+    the last kernel adds U_k Z' to its partials (the rule of csrc/api.hip)."""
+    return w.dtype == "bf16" and w.T <= 128 and -(-w.d_out // 64) * -(-w.T // 64) <= 256
+
+
+def gemm_times(fn, sets, steps, warmup, torch, cts, ride=False):
     """Mean duration (us) of the fused GEMM with the steps run back to back
     as in the timed region, but with only two events around the GEMM, less
     the marker cost: the interval of two events recorded back to back after
-    each step.  Returns (gemm interval, marker interval)."""
+    each step.  Returns (gemm interval, marker interval).  ride: the launch
+    that holds the dense product beside the shrink and the kernel that adds
+    U_k Z' to it, each between two events of its own, their sum (and two
+    markers)."""
     n = warmup + steps
-    evs = [[torch.cuda.Event(enable_timing=True) for _ in range(4)] for _ in range(n)]
+    evs = [[torch.cuda.Event(enable_timing=True) for _ in range(6 if ride else 4)] for _ in range(n)]
     for i in range(n):
-        e3, e4, ea, eb = evs[i]
-        cts.set_stage_events([None, None, None, e3, e4, None])
+        e3, e4, ea, eb = evs[i][:4]
+        cts.set_stage_events([None, evs[i][4], evs[i][5], e3, e4, None] if ride else [None, None, None, e3, e4, None])
         fn(sets[i % len(sets)])
         ea.record()
         eb.record()
@@ -302,6 +313,9 @@ def gemm_times(fn, sets, steps, warmup, torch, cts):
     m = evs[warmup:]
     g = 1e3 * sum(e[0].elapsed_time(e[1]) for e in m) / steps
     mk = 1e3 * sum(e[2].elapsed_time(e[3]) for e in m) / steps
+    if ride:
+        g += 1e3 * sum(e[4].elapsed_time(e[5]) for e in m) / steps
+        mk *= 2
     return g, mk
 
 
@@ -536,7 +550,8 @@ def bench_layer(args, torch, np, cts, B, wl, device):
         (n_sets, set_bytes / 1e6, args.warmup, args.steps))
     ms, ms_g, ms_g1 = time_launches(step, sets, args, torch, one_call=True)
     stages = stage_times(step, sets, args.steps, torch, B)
-    g_int, g_mark = gemm_times(step, sets, args.steps, args.warmup, torch, B)
+    ride = rides_with_shrink(w)
+    g_int, g_mark = gemm_times(step, sets, args.steps, args.warmup, torch, B, ride)
 
     # one adapter: the same batch, every token on LoRA 0 of cluster 0
     aid1 = torch.zeros_like(aid)
@@ -574,8 +589,12 @@ def bench_layer(args, torch, np, cts, B, wl, device):
     gemm_us = g_int - g_mark
     roof = roofline_of(flops, nbytes, gemm_us * 1e-6, w.dtype)
     roof["traffic"] = traffic_from_profile(args.workload)
-    gemm_kernel = "seg_gemm_dma_kernel" if w.dtype == "bf16" else "seg_gemm_kernel"
-    roof.update({"kernel": gemm_kernel + " (fused W X + U_k Z')", "mean_us": round(gemm_us, 2),
+    if ride:
+        gemm_kernel = "seg_gemm_dma_kernel (W X beside V_k^T X) + expand_kernel (U_k Z' added to its partials)"
+    else:
+        gemm_kernel = ("prefill_gemm_kernel" if args.workload == "prefill_mix" else "seg_gemm_dma_kernel") + \
+            " (fused W X + U_k Z')"
+    roof.update({"kernel": gemm_kernel, "mean_us": round(gemm_us, 2),
                  "event_interval_us": round(g_int, 2), "marker_us": round(g_mark, 2),
                  "algorithmic_flops": flops, "algorithmic_bytes": nbytes})
 
