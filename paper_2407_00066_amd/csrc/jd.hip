@@ -49,9 +49,16 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
 }
 
 // ---------------------------------------------------------------- loaders
-// A loader fills slot e (0 <= e < 512: 64 x 32 floats as float4) of the A tile
-// at k0 and gives its LDS offset; a B loader fills slot e (< 8 r) of the
-// 32 x r B tile.  Out-of-range slots read zeros.
+// A loader gives the address that slot e (0 <= e < 512: 64 x 32 floats as
+// float4) of the A tile at k0 is read from, and its LDS offset; a B loader that
+// of slot e (< 8 r) of the 32 x r B tile.  Out-of-range slots, and any at
+// k0 = kNoTile, read kZeros: no load sits behind a branch, so a wait for one
+// k-tile's loads leaves the later ones in flight.
+__device__ float4 kZeros;               // never written
+constexpr int kNoTile = 0x7fffff00;     // past every reduction (slots add < 32)
+__device__ __forceinline__ const float* zeros_unless(bool ok, const float* p) {
+  return ok ? p : reinterpret_cast<const float*>(&kZeros);
+}
 
 // A loader is called as la(u, e, k0, off) with e = threadIdx.x + u * kJT.
 static_assert(kTM * kBK / 4 / kJT == 2, "two A slots per thread");
@@ -74,10 +81,9 @@ struct LoadLoraRowsP {
       p[u] = (q < nq) ? A + (static_cast<int64_t>(lidx[q0 + q]) * r_l + l) * d_in + 4 * kq : nullptr;
     }
   }
-  __device__ float4 operator()(int u, int, int k0, int& o) const {
+  __device__ const float* operator()(int u, int, int k0, int& o) const {
     o = off[u];
-    if (!p[u] || k0 + kq4[u] >= d_in) return float4{0.f, 0.f, 0.f, 0.f};
-    return *reinterpret_cast<const float4*>(p[u] + k0);
+    return zeros_unless(p[u] && k0 + kq4[u] < d_in, p[u] + k0);
   }
 };
 
@@ -100,10 +106,9 @@ struct LoadLoraBtP {
                       : nullptr;
     }
   }
-  __device__ float4 operator()(int u, int, int k0, int& o) const {
+  __device__ const float* operator()(int u, int, int k0, int& o) const {
     o = off[u];
-    if (!p[u] || k0 + kk[u] >= d_out) return float4{0.f, 0.f, 0.f, 0.f};
-    return *reinterpret_cast<const float4*>(p[u] + static_cast<int64_t>(k0) * r_l);
+    return zeros_unless(p[u] && k0 + kk[u] < d_out, p[u] + static_cast<int64_t>(k0) * r_l);
   }
 };
 
@@ -121,17 +126,16 @@ __device__ __forceinline__ int list_id(const int32_t* ids, int i) {
 template <bool kLds>
 struct LoadExpandB {
   const float* B; const int32_t* ids; int id0, lg, r_l, d_out, o0, f_end;
-  __device__ float4 operator()(int, int e, int k0, int& off) const {
+  __device__ const float* operator()(int, int e, int k0, int& off) const {
     const int w = r_l < kBK ? r_l : kBK;
     const int w4 = w >> 2;
     const int j4 = e % w4, m = (e / w4) & (kTM - 1), qq = e / (w4 * kTM);
     off = m * kALD + qq * w + 4 * j4;
     const int f = k0 + qq * w + 4 * j4;       // k0: flat index of the tile
     const int o = o0 + m;
-    if (f >= f_end || o >= d_out) return float4{0.f, 0.f, 0.f, 0.f};
-    const int q = f >> lg, l = f & (r_l - 1);
+    const int q = min(f, f_end - 1) >> lg, l = f & (r_l - 1);    // (a LoRA of the list either way)
     const int64_t base = static_cast<int64_t>(list_id<kLds>(ids, q - id0)) * d_out * r_l;
-    return *reinterpret_cast<const float4*>(B + base + static_cast<int64_t>(o) * r_l + l);
+    return zeros_unless(f < f_end && o < d_out, B + base + static_cast<int64_t>(o) * r_l + l);
   }
 };
 
@@ -139,27 +143,25 @@ struct LoadExpandB {
 template <bool kLds>
 struct LoadExpandA {
   const float* A; const int32_t* ids; int id0, lg, r_l, d_in, c0, f_end;
-  __device__ float4 operator()(int, int e, int k0, int& off) const {
+  __device__ const float* operator()(int, int e, int k0, int& off) const {
     const int kk = e >> 4, m4 = e & 15;
     off = kk * kAML + 4 * m4;
     const int f = k0 + kk, c = c0 + 4 * m4;
-    if (f >= f_end || c >= d_in) return float4{0.f, 0.f, 0.f, 0.f};
-    const int q = f >> lg, l = f & (r_l - 1);
+    const int q = min(f, f_end - 1) >> lg, l = f & (r_l - 1);    // (a LoRA of the list either way)
     const int64_t row = static_cast<int64_t>(list_id<kLds>(ids, q - id0)) * r_l + l;
-    return *reinterpret_cast<const float4*>(A + row * d_in + c);
+    return zeros_unless(f < f_end && c < d_in, A + row * d_in + c);
   }
 };
 
 // B tile: rows k of an [K][r] array (a basis, or C / D rows).
 struct LoadRowsR {
   const float* X; int r, K;
-  __device__ float4 operator()(int, int e, int k0, int& off) const {
+  __device__ const float* operator()(int, int e, int k0, int& off) const {
     const int r4 = r >> 2;
     const int kk = e / r4, n = 4 * (e - kk * r4);
     off = kk * b_ld(r) + n;
     const int k = k0 + kk;
-    if (k >= K) return float4{0.f, 0.f, 0.f, 0.f};
-    return *reinterpret_cast<const float4*>(X + static_cast<int64_t>(k) * r + n);
+    return zeros_unless(k < K, X + static_cast<int64_t>(k) * r + n);
   }
 };
 
@@ -167,6 +169,11 @@ struct LoadRowsR {
 // k_end), tiles of 32 double-buffered through registers; NB = r / 16 column
 // blocks.  Lane l of wave w holds rows 16 w + 4 (l / 16) + v, column
 // 16 nb + l % 16 of block nb.
+// What bounds it is how long the matrix cores wait for operands.  With the
+// out-of-range slots behind branches every wait for k-tile t+1's loads was one
+// for t+2's too, and each LDS read was waited for at once; now neither is (1000
+// rank-16 LoRAs of 4096 x 4096, r = 64: projection 169 -> 158 us, expansion 171 ->
+// 153, of 107 at the fp32 rate; three or four projection pieces: 159 and 161).
 template <int NB, bool AKM, typename LA, typename LB>
 __device__ void tile_gemm(float* smem, int k_begin, int k_end, const LA& la, const LB& lb, f32x4 (&acc)[NB]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -177,52 +184,64 @@ __device__ void tile_gemm(float* smem, int k_begin, int k_end, const LA& la, con
   constexpr int NBQ = (NBS + kJT - 1) / kJT;              // 1..4 B slots per thread
   // two register sets: while k-tile t is multiplied from LDS, the loads of
   // k-tiles t+1 (issued one step earlier) and t+2 are in flight
-  float4 ra[2][NAQ], rb[2][NBQ];
+  f32x4 ra[2][NAQ], rb[2][NBQ];
   int oa[2][NAQ], ob[2][NBQ];
   const int nt = (k_end - k_begin + kBK - 1) / kBK;
-  auto fetch = [&](int t, float4 (&ra_)[NAQ], float4 (&rb_)[NBQ], int (&oa_)[NAQ], int (&ob_)[NBQ]) {
-    const int k0 = k_begin + t * kBK;
+  auto fetch = [&](int t, f32x4 (&ra_)[NAQ], f32x4 (&rb_)[NBQ], int (&oa_)[NAQ], int (&ob_)[NBQ])
+      __attribute__((always_inline)) {
+    const int k0 = t < nt ? k_begin + t * kBK : kNoTile;
 #pragma unroll
-    for (int u = 0; u < NAQ; ++u) ra_[u] = la(u, tid + u * kJT, k0, oa_[u]);
+    for (int u = 0; u < NAQ; ++u) ra_[u] = *reinterpret_cast<const f32x4*>(la(u, tid + u * kJT, k0, oa_[u]));
 #pragma unroll
     for (int u = 0; u < NBQ; ++u)
-      if (NBS % kJT == 0 || tid + u * kJT < NBS) rb_[u] = lb(u, tid + u * kJT, k0, ob_[u]);
+      if (NBS % kJT == 0 || tid + u * kJT < NBS) rb_[u] = *reinterpret_cast<const f32x4*>(lb(u, tid + u * kJT, k0, ob_[u]));
   };
-  auto stash = [&](int buf, const float4 (&ra_)[NAQ], const float4 (&rb_)[NBQ], const int (&oa_)[NAQ],
-                   const int (&ob_)[NBQ]) {
+  auto stash = [&](int buf, const f32x4 (&ra_)[NAQ], const f32x4 (&rb_)[NBQ], const int (&oa_)[NAQ],
+                   const int (&ob_)[NBQ]) __attribute__((always_inline)) {
     float* As = smem + buf * stage_floats<NB>();
     float* Bs = As + kAS;
 #pragma unroll
-    for (int u = 0; u < NAQ; ++u) *reinterpret_cast<float4*>(As + oa_[u]) = ra_[u];
+    for (int u = 0; u < NAQ; ++u) *reinterpret_cast<f32x4*>(As + oa_[u]) = ra_[u];
 #pragma unroll
     for (int u = 0; u < NBQ; ++u)
-      if (NBS % kJT == 0 || tid + u * kJT < NBS) *reinterpret_cast<float4*>(Bs + ob_[u]) = rb_[u];
+      if (NBS % kJT == 0 || tid + u * kJT < NBS) *reinterpret_cast<f32x4*>(Bs + ob_[u]) = rb_[u];
   };
   if (nt <= 0) return;
   const int m = 16 * wave + fr;
-  auto multiply = [&](int buf) {
+  // 4-k step s + 1's fragment reads are issued before step s's MFMAs
+  auto multiply = [&](int buf) __attribute__((always_inline)) {
     const float* As = smem + buf * stage_floats<NB>();
     const float* Bs = As + kAS;
+    float fa[2], fb[2][NB];
+    auto frags = [&](int s) __attribute__((always_inline)) {
+      const int k = 4 * s + fk;
+      fa[s & 1] = AKM ? As[k * kAML + m] : As[m * kALD + k];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) fb[s & 1][nb] = Bs[k * b_ld(R) + 16 * nb + fr];
+    };
+    frags(0);
 #pragma unroll
     for (int s = 0; s < kBK / 4; ++s) {
-      const int k = 4 * s + fk;
-      const float a = AKM ? As[k * kAML + m] : As[m * kALD + k];
+      if (s + 1 < kBK / 4) frags(s + 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma4(a, Bs[k * b_ld(R) + 16 * nb + fr], acc[nb]);
+      for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma4(fa[s & 1], fb[s & 1][nb], acc[nb]);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
   fetch(0, ra[0], rb[0], oa[0], ob[0]);
-  if (nt > 1) fetch(1, ra[1], rb[1], oa[1], ob[1]);
+  fetch(1, ra[1], rb[1], oa[1], ob[1]);
   stash(0, ra[0], rb[0], oa[0], ob[0]);
   __syncthreads();
   // step t (parity P = t & 1): loads of t+2 into set P (stashed at step t-1),
   // multiply k-tile t from LDS buffer P, stash set 1-P (k-tile t+1) into
   // buffer 1-P.  Unrolled by two so that the register sets are static.
-  auto step = [&](int t, float4 (&raP)[NAQ], float4 (&rbP)[NBQ], int (&oaP)[NAQ], int (&obP)[NBQ],
-                  float4 (&raQ)[NAQ], float4 (&rbQ)[NBQ], int (&oaQ)[NAQ], int (&obQ)[NBQ], int bufP) {
-    if (t + 2 < nt) fetch(t + 2, raP, rbP, oaP, obP);
+  auto step = [&](int t, f32x4 (&raP)[NAQ], f32x4 (&rbP)[NBQ], int (&oaP)[NAQ], int (&obP)[NBQ],
+                  f32x4 (&raQ)[NAQ], f32x4 (&rbQ)[NBQ], int (&oaQ)[NAQ], int (&obQ)[NBQ], int bufP)
+      __attribute__((always_inline)) {
+    fetch(t + 2, raP, rbP, oaP, obP);
     multiply(bufP);
-    if (t + 1 < nt) stash(bufP ^ 1, raQ, rbQ, oaQ, obQ);
+    stash(bufP ^ 1, raQ, rbQ, oaQ, obQ);
     __syncthreads();
   };
   for (int t = 0; t < nt; t += 2) {
@@ -854,24 +873,22 @@ __global__ __launch_bounds__(kJT) void jd_reduce_kernel(const float* partU, cons
 // Rows of a basis X [d][r] as the A operand (m = row, k = column).
 struct LoadBasisRows {
   const float* X; int r, row0, d;
-  __device__ float4 operator()(int, int e, int k0, int& off) const {
+  __device__ const float* operator()(int, int e, int k0, int& off) const {
     const int m = e >> 3, kq = e & 7;
     off = m * kALD + 4 * kq;
     const int row = row0 + m, k = k0 + 4 * kq;
-    if (row >= d || k >= r) return float4{0.f, 0.f, 0.f, 0.f};
-    return *reinterpret_cast<const float4*>(X + static_cast<int64_t>(row) * r + k);
+    return zeros_unless(row < d && k < r, X + static_cast<int64_t>(row) * r + k);
   }
 };
 
 // X^T as the A operand (m = column a of X, k = row of X): k-major.
 struct LoadBasisT {
   const float* X; int r, a0, k_end;
-  __device__ float4 operator()(int, int e, int k0, int& off) const {
+  __device__ const float* operator()(int, int e, int k0, int& off) const {
     const int kk = e >> 4, m4 = e & 15;
     off = kk * kAML + 4 * m4;
     const int row = k0 + kk, col = a0 + 4 * m4;
-    if (row >= k_end || col >= r) return float4{0.f, 0.f, 0.f, 0.f};
-    return *reinterpret_cast<const float4*>(X + static_cast<int64_t>(row) * r + col);
+    return zeros_unless(row < k_end && col < r, X + static_cast<int64_t>(row) * r + col);
   }
 };
 

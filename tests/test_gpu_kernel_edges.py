@@ -200,3 +200,33 @@ def test_small_diagonal_edges(oracle_mod, T, d_in, d_out, r, K, n):
     say("small diag T=%d %dx%d r=%d" % (T, d_in, d_out, r))
     y = host(cts.apply_diag(*[dev(v) for v in (w.x, w.adapter_id, w.cluster_of, w.W, w.U, w.Vt)], dev(sg)))
     assert row_rel_err(y, oracle_mod.apply_diag(w.x, w.adapter_id, w.cluster_of, w.W, w.U, w.Vt, sg)) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("n,r_l,d_out,d_in,r", [
+    (16, 4, 32, 28, 16),          # one k-tile of the projections, whole and part; two of the expansion
+    (21, 4, 64, 68, 16),          # two and three; three of the expansion, the last one part
+    (9, 16, 132, 100, 32),        # five and four; five
+    (8, 4, 100, 164, 16),         # one of the expansion
+    (7, 32, 1028, 516, 48),       # two pieces of the projections, a last k-tile of four
+])
+def test_jd_k_tile_counts(n, r_l, d_out, d_in, r):
+    """The compressor's products at the k-tile counts where the two tiles loaded
+    ahead run past the reduction: one sweep and the cores.  The sweep's r x r
+    systems turn a relative change of 1e-7 of the inputs into less than 5e-7 here;
+    the fp32 sums of up to 1028 products leave up to 20 times that."""
+    rs = np.random.default_rng(6000 + n + d_in)
+    A = rs.standard_normal((n, r_l, d_in)).astype(np.float32) / np.float32(np.sqrt(d_in))
+    B = rs.standard_normal((n, d_out, r_l)).astype(np.float32) / np.float32(np.sqrt(r_l))
+    U = rs.standard_normal((d_out, r)).astype(np.float32) / np.float32(np.sqrt(d_out))
+    V = rs.standard_normal((d_in, r)).astype(np.float32) / np.float32(np.sqrt(d_in))
+    say("jd k-tiles n=%d r_l=%d %dx%d r=%d" % (n, r_l, d_out, d_in, r))
+
+    def rel(got, want):
+        return np.linalg.norm(got.cpu().numpy().astype(np.float64) - want) / np.linalg.norm(want)
+
+    a = [_f32(v) for v in (A, B, U, V.T)]
+    assert rel(GC.jd_sigma(*a), OC.sigma_star(U.astype(np.float64), V.astype(np.float64), A, B)) <= 1e-5
+    got = GC.jd_diag(*a, sweeps=1)
+    Uo, Vo, so, _ = OC.jd_diag_als(A, B, r, U, V, sweeps=1)
+    for g, w in zip(got, (Uo, Vo.T, so)):
+        assert rel(g, w) <= 1e-5
