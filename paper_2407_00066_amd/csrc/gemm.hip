@@ -780,8 +780,9 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
 //                columns
 //   wait         those reads (after which this wave is done with the unit's
 //                slot) and this wave's loads of unit u + 1; then the barrier
-//   second part  the other 20; under them the fragment reads of unit u + 1  Fragments take 64 registers (a unit's rows and half its columns,
-// twice) beside the 128 accumulators, so nothing spills.
+//   second part  the other 20; under them the fragment reads of unit u + 1
+// Fragments take 64 registers (a unit's rows and half its columns, twice) beside
+// the 128 accumulators, so nothing spills.
 // The adapter phase is a list of (run, unit) entries in LDS, uniform or mixed
 // ranks alike: one 8-byte read per unit, a unit ahead of its loads.
 // The waits and the barrier leave 16% of the matrix-core slots unused; the
@@ -1268,12 +1269,13 @@ hipError_t launch_dma(const GemmParams& p, hipStream_t stream) {
 
 }  // namespace
 
-// Tile shapes (BM x BN x BK: d_out rows x tokens x k; chosen by the plan from
-// measurements on MI355X).  The ring tiles use 16x16x32 MFMA:
-//   Large   256 x 256 x  32, 8 waves, 4-unit ring (prefill kernel)    T >= 2048
-//   Wide    256 x 128 x  64, 8 waves, 3 stages     many row tiles or d_in >= 8192
-//   Mid     128 x 128 x  64, 8 waves, 4 stages     >= 128 tiles
-//   Narrow  128 x  64 x 128, 4 waves, 3 stages     other T > 64
+// Tile shapes (BM x BN x BK: d_out rows x tokens x k).  The bf16 tiles use
+// 16x16x32 MFMA; for T > 64 the plan takes the one whose rounds over the
+// compute units it estimates shortest:
+//   Large   256 x 256 x  32, 8 waves, 4-unit ring (prefill kernel)
+//   Wide    256 x 128 x  64, 8 waves, 3 stages
+//   Mid     128 x 128 x  64, 8 waves, 4 stages
+//   Narrow  128 x  64 x 128, 4 waves, 3 stages
 //   Decode   64 x  64 x 128, 4 waves, 4 stages     T <= 64
 //   Shrink   64 x  64 x  64, 4 waves, 3 stages     the V_k^T X products
 //   F32      64 x  64 x  32, 4 waves, 3 stages     fp32 inputs: every product
