@@ -315,6 +315,14 @@ __global__ __launch_bounds__(256) void expand_kernel(const ExpandParams p) {
       const int k = 32 * i + 8 * g;
       z[i] = load16(rZ, k < p.r ? static_cast<uint32_t>((j * p.ldz + p.zoff[q] + k) * 2) : kOob);
     }
+    // z' past the rank is 0 z, NaN where z overflowed: it meets U's masked
+    // zeros as a zero (a rank is a multiple of 8)
+    if (p.sorted_rank) {
+#pragma unroll
+      for (int i = 0; i < KK; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[i][e] = 32 * i + 8 * g < rk ? z[i][e] : 0u;
+    }
   } else {
     const int S = min(p.zsplit[0], p.zS);
     int a = p.sdiag ? p.sorted_aid[j] : 0;

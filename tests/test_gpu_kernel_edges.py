@@ -230,3 +230,21 @@ def test_jd_k_tile_counts(n, r_l, d_out, d_in, r):
     Uo, Vo, so, _ = OC.jd_diag_als(A, B, r, U, V, sweeps=1)
     for g, w in zip(got, (Uo, Vo.T, so)):
         assert rel(g, w) <= 1e-5
+
+
+@pytest.mark.parametrize("T", [5, 128, 200])
+def test_overflow_below_the_rank_stays_an_infinity(T):
+    """Ranks 8 of 64 with V^T x past the fp32 range for token 1: U_k's positive
+    columns times its infinite z' are infinite, not NaN, whichever kernel adds
+    them (in a small batch's last kernel z' past the rank is 0 times infinity)."""
+    d_in, d_out, r, n, K = 64, 72, 64, 6, 2
+    x = torch.full((T, d_in), 2.0 ** -6, device="cuda", dtype=torch.bfloat16)
+    x[1] = 3e38
+    aid, cof = [torch.arange(m, device="cuda", dtype=torch.int32) % q for m, q in ((T, n), (n, K))]
+    W = torch.zeros(d_out, d_in, device="cuda", dtype=torch.bfloat16)
+    U, Vt, S = [torch.ones(sh, device="cuda", dtype=torch.bfloat16) for sh in ((K, d_out, r), (K, r, d_in), (n, r, r))]
+    rk = torch.full((K,), 8, device="cuda", dtype=torch.int32)
+    say("overflow below the rank T=%d" % T)
+    y = host(cts.apply_ranked(x, aid, cof, W, U, Vt, S, rk))
+    assert np.isposinf(y[1]).all()
+    assert (np.delete(y, 1, 0) == 64.0).all()      # V^T x = 1, Sigma z = 8, U z' = 64, all exact
