@@ -101,7 +101,10 @@ typedef struct {
 /* Human-readable name of a status code (static storage, never NULL). */
 const char* cts_status_string(int status);
 
-/* Bytes of device workspace cts_apply needs for `p` (0 if p is invalid). */
+/* Bytes of device workspace cts_apply needs for `p` (0 if p is invalid).  The
+ * sizes (this one and those of the other layer calls) grow with T up to 8192
+ * tokens: a workspace sized for a batch serves every smaller batch of the same
+ * layer. */
 size_t cts_workspace_size(const cts_problem* p);
 
 /* Bytes of device workspace cts_apply_uncompressed needs for `p`. */

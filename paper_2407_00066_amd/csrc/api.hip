@@ -54,6 +54,7 @@ int ceil_div(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }
 // workgroup buckets the tokens itself); beside the dense product it has that
 // product's time to finish in, so fewer, longer pieces (q/k/v of 33 tokens:
 // 36.4 us a call at 128 and 8, 40.8 at 256, 42.6 at 64).
+constexpr int kShrinkMaxSplit = 64;
 struct ShrinkSplit { int target, kmin; };
 ShrinkSplit shrink_rule(int dtype, int T, bool small) {
   if (small) return {128, 8};
@@ -69,7 +70,7 @@ int shrink_split_of(int dtype, int T, int rank, int d_in, Tile t, bool small) {
   const ShrinkSplit rule = shrink_rule(dtype, T, small);
   const int tiles = ceil_div(rank, BM) * ceil_div(std::max(T, 1), BN);
   const int nk = ceil_div(d_in, BK);
-  return std::max(1, std::min(std::min(ceil_div(rule.target, tiles), std::max(1, nk / rule.kmin)), 64));
+  return std::max(1, std::min(std::min(ceil_div(rule.target, tiles), std::max(1, nk / rule.kmin)), kShrinkMaxSplit));
 }
 
 int tile_split(Tile t, int T, int d_in, int d_out, int round, int cap) {
@@ -94,6 +95,7 @@ struct TileCost { Tile tile; int max_split; double fixed, per64; };
 constexpr TileCost kTileCosts[] = {
     {Tile::Large, 1, 8.0, 1.50}, {Tile::Wide, 8, 6.0, 0.83}, {Tile::Mid, 8, 5.0, 0.52}, {Tile::Narrow, 8, 4.0, 0.45}};
 constexpr int kPrefillT = 2048;
+constexpr int kF32Round = 768, kF32MaxSplit = 8, kDecodeMaxSplit = 4;
 
 // 0: the tile does not take this reduction
 double tile_us(const TileCost& tc, int T, int d_in, int d_out, int rank, int nseg, int* split) {
@@ -121,11 +123,64 @@ double tile_us(const TileCost& tc, int T, int d_in, int d_out, int rank, int nse
 // 88 us in separate launches and 95 so).  More pieces than three (four past
 // d_in = 8192) cost more in partials than the shorter reduction gives: 4096 x
 // 4096 at 64 tokens 19.7, 21.4 and 21.8 us at three, four and seven.
+int small_cap(int d_in) { return std::min(d_in >= 8192 ? 4 : 3, cts::kExpandMaxSplit); }
+
 int small_split_of(int dtype, int T, int row_tiles, int d_in) {
   const int tiles = row_tiles * ceil_div(T, 64);
   if (dtype != CTS_BF16 || T < 1 || T > cts::kFuseSortMaxT || tiles > 256) return 0;
-  const int cap = std::min(d_in >= 8192 ? 4 : 3, cts::kExpandMaxSplit);
-  return std::max(1, std::min(std::min(cap, 256 / tiles), ceil_div(d_in, 64) / 4));
+  return std::max(1, std::min(std::min(small_cap(d_in), 256 / tiles), ceil_div(d_in, 64) / 4));
+}
+
+// What the partials of any batch of up to T tokens can need, in bytes.  Fewer
+// tokens are split into more pieces (a batch of 77 into four where one of 256 is
+// not split), so the need itself goes up and down with T; a workspace is
+// sized by these bounds, which grow with every size, so that one made for a
+// server's largest batch serves all its smaller ones.
+
+// The shrink's: with S pieces, S <= cap and S < target / tiles + 1, a tile
+// holds at most 64 tokens by 64 of the rank.
+size_t zpart_bound(int dtype, int T, int rank, int d_in, Tile t) {
+  int BM, BN, BK;
+  cts::tile_dims(t, &BM, &BN, &BK);
+  size_t most = 0;
+  for (int upto : {std::min(T, cts::kFuseSortMaxT), T}) {
+    const ShrinkSplit rule = shrink_rule(dtype, upto, false);   // (beside W X it splits less)
+    const uint64_t cap = std::min(std::max(1, ceil_div(d_in, BK) / rule.kmin), kShrinkMaxSplit);
+    const uint64_t one = static_cast<uint64_t>(upto) * rank;
+    most = std::max<size_t>(most, 4 * std::min(cap * one, static_cast<uint64_t>(rule.target) * BN * std::min(rank, BM) + one));
+  }
+  return most;
+}
+
+// The dense product's: at most `round` tiles times pieces (tile_split), over
+// every tile that a batch of up to T tokens may take.
+size_t ypart_bound(int dtype, int T, int d_in, int d_out) {
+  auto bound = [&](Tile t, int upto, int round, int cap) -> size_t {
+    int BM, BN, BK;
+    cts::tile_dims(t, &BM, &BN, &BK);
+    const uint64_t s = std::min(cap, ceil_div(d_in, BK) / 4);
+    if (s < 2) return 0;                                        // one piece is the output itself
+    return 4 * std::min(s * upto * d_out, static_cast<uint64_t>(round) * BM * BN);
+  };
+  if (dtype == CTS_F32) return bound(Tile::F32, T, kF32Round, kF32MaxSplit);
+  const uint64_t small = std::max(1, std::min(small_cap(d_in), ceil_div(d_in, 64) / 4));
+  size_t most = 4 * std::min(small * std::min(T, cts::kFuseSortMaxT) * d_out, uint64_t{256} * 64 * 64);
+  most = std::max(most, bound(Tile::Decode, std::min(T, 64), 256, kDecodeMaxSplit));
+  if (T > 64)
+    for (const TileCost& tc : kTileCosts) most = std::max(most, bound(tc.tile, T, 256, tc.max_split));
+  return most;
+}
+
+// Offsets of Z' and of the dense partials (ypart_bytes of them in this call)
+// after the shrink's partials at off_zpart, and the workspace's size.
+void place_partials(const cts_problem* p, size_t off_zpart, int rank, int shrink_split, Tile shrink_tile, int d_out,
+                    size_t ypart_bytes, int elt, size_t* off_zp, size_t* off_ypart, size_t* total) {
+  const size_t one = static_cast<size_t>(p->T) * rank;
+  *off_zp = align_up(off_zpart + 4 * shrink_split * one);
+  *off_ypart = align_up(*off_zp + elt * one);
+  const size_t bound = align_up(off_zpart + zpart_bound(p->dtype, p->T, rank, p->d_in, shrink_tile)) +
+                       align_up(elt * one) + align_up(ypart_bound(p->dtype, p->T, p->d_in, d_out));
+  *total = std::max(align_up(*off_ypart + ypart_bytes), bound);
 }
 
 // Batches of more than kSortMaxT tokens (the one-workgroup bucketing's
@@ -194,10 +249,10 @@ int plan_piece(const cts_problem* p, bool compressed, Plan* pl) {
     // 2816, 352 tiles: 70 us a call unsplit, 63 in two pieces; 64 tokens, 2048 ->
     // 2048, 32 tiles: 83 and 33 in eight)
     pl->main_tile = Tile::F32;
-    pl->main_split = tile_split(Tile::F32, T, p->d_in, p->d_out, 768, 8);
+    pl->main_split = tile_split(Tile::F32, T, p->d_in, p->d_out, kF32Round, kF32MaxSplit);
   } else if (T <= 64) {
     pl->main_tile = Tile::Decode;
-    pl->main_split = tile_split(Tile::Decode, T, p->d_in, p->d_out, 256, 4);
+    pl->main_split = tile_split(Tile::Decode, T, p->d_in, p->d_out, 256, kDecodeMaxSplit);
   } else {
     double best = 0.0;
     for (const TileCost& tc : kTileCosts) {
@@ -239,31 +294,22 @@ int plan_piece(const cts_problem* p, bool compressed, Plan* pl) {
   pl->off_iaid = off;  off = align_up(off + 4ull * (pl->max_items + 1));
   pl->off_cseg = off;  off = align_up(off + 4ull * (pl->max_ctiles + 1));
   pl->off_ssplit = off; off = align_up(off + 4);
-  pl->off_zpart = off; off = align_up(off + 4ull * pl->shrink_split * T * pl->rank);
-  pl->off_zp = off;    off = align_up(off + static_cast<size_t>(pl->elt) * T * pl->rank);
-  pl->off_ypart = off;
+  pl->off_zpart = off;
   const int pieces = pl->small_split > 0 ? pl->small_split : pl->main_split > 1 ? pl->main_split : 0;
-  off = align_up(off + 4ull * pieces * T * p->d_out);
-  pl->total = off;
+  place_partials(p, off, pl->rank, pl->shrink_split, pl->shrink_tile, p->d_out, 4ull * pieces * T * p->d_out, pl->elt,
+                 &pl->off_zp, &pl->off_ypart, &pl->total);
   return CTS_OK;
 }
 
-// The plan of p: for a batch of pieces, the plan of its largest piece, with
-// a workspace that also fits the smaller piece size.
+// The plan of p: for a batch of pieces, the plan of its largest piece (whose
+// workspace fits the smaller piece size too).
 int make_plan(const cts_problem* p, bool compressed, Plan* pl) {
   if (!p) return CTS_ERR_INVALID_ARG;
   if (p->T <= cts::kSortMaxT) return plan_piece(p, compressed, pl);
   const Pieces pc = pieces_of(p->T);
   cts_problem q = *p;
   q.T = pc.q + (pc.rem ? 1 : 0);
-  int rc = plan_piece(&q, compressed, pl);
-  if (rc != CTS_OK || !pc.rem) return rc;
-  Plan small;
-  q.T = pc.q;
-  rc = plan_piece(&q, compressed, &small);
-  if (rc != CTS_OK) return rc;
-  pl->total = std::max(pl->total, small.total);
-  return CTS_OK;
+  return plan_piece(&q, compressed, pl);
 }
 
 // Stage-boundary events of the profiling aid (null when off).
@@ -654,10 +700,6 @@ int multi_plan_piece(const cts_problem* p, int M, const int32_t* d_out, MultiPla
   mp->small = small > 0;
   // shrink over the stacked rank: as for one module, with M r rank rows
   mp->shrink_split = shrink_split_of(p->dtype, T, mp->rtot, p->d_in, p0.shrink_tile, mp->small);
-  size_t off = p0.off_zpart;                        // the shared sort arrays of module 0's layout
-  mp->off_zpart = off; off = align_up(off + 4ull * mp->shrink_split * T * mp->rtot);
-  mp->off_zp = off;    off = align_up(off + static_cast<size_t>(p0.elt) * T * mp->rtot);
-  mp->off_ypart = off;
   mp->d_sum = 0;
   for (int m = 0; m < M; ++m) mp->d_sum += d_out[m];
   // grouped when the one launch fits one round of workgroups over the
@@ -693,27 +735,20 @@ int multi_plan_piece(const cts_problem* p, int M, const int32_t* d_out, MultiPla
     for (int m = 0; m < M; ++m)
       if (mp->mod[m].main_split > 1) yp = std::max<size_t>(yp, 4ull * mp->mod[m].main_split * T * d_out[m]);
   }
-  off = align_up(off + yp);
-  mp->total = off;
+  mp->off_zpart = p0.off_zpart;                     // after the shared sort arrays of module 0's layout
+  place_partials(p, mp->off_zpart, mp->rtot, mp->shrink_split, p0.shrink_tile, mp->d_sum, yp, p0.elt, &mp->off_zp,
+                 &mp->off_ypart, &mp->total);
   return CTS_OK;
 }
 
-// As make_plan: a batch of pieces takes its largest piece's plan, with a
-// workspace that also fits the smaller piece size.
+// As make_plan: a batch of pieces takes its largest piece's plan.
 int make_multi_plan(const cts_problem* p, int M, const int32_t* d_out, MultiPlan* mp) {
   if (!p) return CTS_ERR_INVALID_ARG;
   if (p->T <= cts::kSortMaxT) return multi_plan_piece(p, M, d_out, mp);
   const Pieces pc = pieces_of(p->T);
   cts_problem q = *p;
   q.T = pc.q + (pc.rem ? 1 : 0);
-  int rc = multi_plan_piece(&q, M, d_out, mp);
-  if (rc != CTS_OK || !pc.rem) return rc;
-  MultiPlan small;
-  q.T = pc.q;
-  rc = multi_plan_piece(&q, M, d_out, &small);
-  if (rc != CTS_OK) return rc;
-  mp->total = std::max(mp->total, small.total);
-  return CTS_OK;
+  return multi_plan_piece(&q, M, d_out, mp);
 }
 
 // ext_perm / ext_bucket: a bucketing from cts_sort_by_cluster (then the ids

@@ -533,3 +533,25 @@ def test_multi_packed_validation():
     assert _packed(p0, ids=False, y=0, ws=0, ws_bytes=0) == B.CTS_OK
     assert cts.lib().cts_apply_multi_packed(None, 2, None, *[None] * 4, 0, *[None] * 6, 0, None, 0, None) \
         == B.CTS_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("kw", [
+    dict(d_in=4096, d_out=14336, r=64, n_adapters=1000, n_clusters=25),
+    dict(d_in=2048, d_out=8192, r=64, n_adapters=1000, n_clusters=25),
+    dict(d_in=4096, d_out=1024, r=128, n_adapters=100, n_clusters=1),
+    dict(d_in=14336, d_out=4096, r=16, n_adapters=50, n_clusters=50),
+    dict(d_in=256, d_out=264, r=72, n_adapters=8, n_clusters=3),
+    dict(d_in=2048, d_out=2048, r=32, n_adapters=200, n_clusters=8, dtype=B.CTS_F32, out_dtype=B.CTS_F32),
+])
+def test_workspace_of_a_batch_serves_every_smaller_one(kw):
+    """The sizes grow with the batch, for every layer call, whatever splits the
+    smaller batches take; the largest still fits the static scratch array."""
+    sizes = {"single": [], "lora": [], "multi": []}
+    for T in [*range(0, 2200), *range(2200, 8192, 37), 8192]:
+        p = _p(T=T, r_lora=64, **kw)
+        sizes["single"].append(cts.workspace_size(p))
+        sizes["lora"].append(cts.workspace_size(p, compressed=False))
+        sizes["multi"].append(cts.workspace_size_multi(p, [kw["d_out"], 1024, 8]))
+    for name, s in sizes.items():
+        assert s[1] > 0 and s == sorted(s), name
+    assert sizes["single"][-1] <= B.NOALLOC_SCRATCH_BYTES
