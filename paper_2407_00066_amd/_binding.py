@@ -18,14 +18,26 @@ _LIB_PATH = os.environ.get("CTS_LIB") or os.path.join(os.path.dirname(os.path.ab
 _lib = None
 _lock = threading.Lock()
 
-try:
-    from ._marshal import address as _address
-except ImportError as _e:          # no fallback: every call says so
-    _marshal_error = str(_e)
 
-    def _address(*_):
+def _load_address():
+    """_marshal's tensor check, or (no fallback) a stand-in whose every call says
+    why it cannot be used."""
+    try:
+        from . import _marshal
+        built_for = getattr(_marshal, "built_for", "another torch")
+        if built_for == torch.__version__:
+            return _marshal.address
+        why = "it was built for torch %s, this is %s" % (built_for, torch.__version__)
+    except ImportError as e:
+        why = str(e)
+
+    def address(*_):
         raise RuntimeError("_marshal.so is not built or does not load (%s); run "
-                           "`python -m paper_2407_00066_amd.build`" % _marshal_error)
+                           "`python -m paper_2407_00066_amd.build`" % why)
+    return address
+
+
+_address = _load_address()
 
 CTS_OK, CTS_ERR_INVALID_ARG, CTS_ERR_UNSUPPORTED, CTS_ERR_WORKSPACE, CTS_ERR_HIP, CTS_ERR_BAD_IDS = range(6)
 CTS_F32, CTS_BF16 = 0, 1

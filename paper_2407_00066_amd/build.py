@@ -65,7 +65,8 @@ def build_marshal() -> str:
     inc = [a for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]] for a in ("-isystem", d)]
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)] + inc + \
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           '-DCTS_TORCH_VERSION="%s"' % torch.__version__] + inc + \
           [os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

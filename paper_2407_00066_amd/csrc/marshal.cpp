@@ -3,6 +3,8 @@
 // of `shape` (None: any), 0 when it is all that and empty, and -1 otherwise
 // (the caller then finds out what is wrong and says so).  A layer call checks
 // eight tensors: about 1 us each as Python attribute reads, 0.1 us here.
+// built_for is the torch it was compiled against (its C++ objects' layout): the
+// binding uses the module with that torch only.
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
@@ -51,4 +53,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__marshal() {
+  PyObject* m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "built_for", CTS_TORCH_VERSION) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -39,3 +39,12 @@ def test_address(make, dtype, shape):
         assert str(got.value) == str(e)
         return
     assert B._dev(t, "t", CPU, dtype, shape) == want
+
+
+def test_a_module_built_for_another_torch_is_not_used(monkeypatch):
+    """_marshal.so reads torch's C++ objects: with a torch other than the one it
+    was compiled against every call refuses, with what to do."""
+    monkeypatch.setattr(torch, "__version__", "1.0.0+other")
+    address = B._load_address()
+    with pytest.raises(RuntimeError, match="built for torch .*, this is 1.0.0.other.*paper_2407_00066_amd.build"):
+        address(torch.zeros(3), CPU, None, None)
