@@ -40,6 +40,7 @@ PyObject* address(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (t.numel() == 0) return PyLong_FromLong(0);
     return PyLong_FromUnsignedLongLong(reinterpret_cast<uintptr_t>(t.data_ptr()));
   } catch (const std::exception&) {      // a tensor without storage, or one that only stands for another
+    PyErr_Clear();                       // (a Python error of its own comes again with the caller's checks)
     return PyLong_FromLong(-1);
   }
 }

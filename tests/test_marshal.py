@@ -48,3 +48,21 @@ def test_a_module_built_for_another_torch_is_not_used(monkeypatch):
     address = B._load_address()
     with pytest.raises(RuntimeError, match="built for torch .*, this is 1.0.0.other.*paper_2407_00066_amd.build"):
         address(torch.zeros(3), CPU, None, None)
+
+
+class _Raises(torch.Tensor):
+    """A wrapper whose attributes are asked for in Python, which raises."""
+    @staticmethod
+    def __new__(cls):
+        return torch.Tensor._make_wrapper_subclass(cls, (3, 8), dispatch_device=True)
+
+    @classmethod
+    def __torch_dispatch__(cls, func, types, args=(), kwargs=None):
+        raise KeyError(str(func))
+
+
+def test_a_tensors_own_error_comes_through():
+    with pytest.raises(KeyError, match="device"):
+        B._check_tensor(_Raises(), "t", CPU, None, None)
+    with pytest.raises(KeyError, match="device"):
+        B._dev(_Raises(), "t", CPU, None, None)
