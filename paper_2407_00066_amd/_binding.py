@@ -192,19 +192,15 @@ def _stream(device: torch.device):
         torch._C._cuda_getCurrentRawStream(device.index)
 
 
-_ws_cache: dict = {}
-
-
 def _workspace(device: torch.device, nbytes: int, workspace):
+    """The caller's workspace, or one for this call alone: the caching allocator
+    hands a freed one to later calls of the same stream only, and a capture's
+    stays with its graph, so calls on several streams or threads share none."""
     if workspace is not None:
         if workspace.device != device or workspace.dtype != torch.uint8:
             raise ValueError("workspace must be a uint8 tensor on %s" % device)
         return workspace
-    ws = _ws_cache.get(device)
-    if ws is None or ws.numel() < nbytes:
-        ws = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=device)
-        _ws_cache[device] = ws
-    return ws
+    return torch.empty(max(nbytes, 1), dtype=torch.uint8, device=device)
 
 
 def make_problem(T, d_in, d_out, r=0, n_adapters=1, n_clusters=1, r_lora=0,

@@ -127,3 +127,37 @@ def test_graph_replay_multi_and_uncompressed():
         for y, e in zip(ys + [yu], ref):
             assert torch.equal(y, e), rep
         assert torch.equal(z, ref[-1]), rep
+
+
+def test_default_workspaces_on_two_streams_and_in_a_graph():
+    """Calls without a workspace argument, interleaved on two streams with other
+    inputs, and a graph captured from such a call replayed after a larger one:
+    each gives what the call alone gives."""
+    layers = [_layer("ws_a", cfg=126, T=100, d_in=512, d_out=1024, r=32, n=30, K=4),
+              _layer("ws_b", cfg=127, T=700, d_in=1024, d_out=512, r=64, n=30, K=4, ids="zipf")]
+    want = [cts.apply(*a) for _, a in layers]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in layers]
+    got = [[torch.empty_like(w) for _ in range(20)] for w in want]
+    say("default workspaces: two streams")
+    for i in range(20):
+        for (_, a), s, g in zip(layers, streams, got):
+            with torch.cuda.stream(s):
+                cts.apply(*a, out=g[i])
+    torch.cuda.synchronize()
+    for w, g in zip(want, got):
+        assert all(torch.equal(y, w) for y in g)
+
+    say("default workspaces: graph")
+    y = torch.empty_like(want[0])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cts.apply(*layers[0][1], out=y)
+    for _ in range(3):
+        big = [torch.full((64 << 20,), 7, dtype=torch.uint8, device="cuda") for _ in range(2)]
+        other = cts.apply(*layers[1][1])
+        y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want[0]) and torch.equal(other, want[1])
+        assert all(bool((b == 7).all()) for b in big)

@@ -66,3 +66,9 @@ def test_a_tensors_own_error_comes_through():
         B._check_tensor(_Raises(), "t", CPU, None, None)
     with pytest.raises(KeyError, match="device"):
         B._dev(_Raises(), "t", CPU, None, None)
+
+
+def test_default_workspaces_are_not_shared():
+    """Two calls that are both on their way hold different workspaces."""
+    a, b = B._workspace(CPU, 4096, None), B._workspace(CPU, 4096, None)
+    assert a.numel() == b.numel() == 4096 and a.data_ptr() != b.data_ptr()
