@@ -286,12 +286,6 @@ def stage_times(fn, sets, steps, torch, cts):
     return out
 
 
-def rides_with_shrink(w):
-    """The dense product of a small bf16 batch runs in the shrink's launch and
-    the last kernel adds U_k Z' to its partials (the rule of csrc/api.hip)."""
-    return w.dtype == "bf16" and w.T <= 128 and -(-w.d_out // 64) * -(-w.T // 64) <= 256
-
-
 def gemm_times(fn, sets, steps, warmup, torch, cts, ride=False):
     """Mean duration (us) of the fused GEMM with the steps run back to back
     as in the timed region, but with only two events around the GEMM, less
@@ -550,7 +544,9 @@ def bench_layer(args, torch, np, cts, B, wl, device):
         (n_sets, set_bytes / 1e6, args.warmup, args.steps))
     ms, ms_g, ms_g1 = time_launches(step, sets, args, torch, one_call=True)
     stages = stage_times(step, sets, args.steps, torch, B)
-    ride = rides_with_shrink(w)
+    tile = B.layer_plan(B.make_problem(w.T, w.d_in, w.d_out, r=w.r, n_adapters=w.n, n_clusters=w.K,
+                                       dtype=B.CTS_BF16 if w.dtype == "bf16" else B.CTS_F32))
+    ride = tile[3] == "beside the shrink"
     g_int, g_mark = gemm_times(step, sets, args.steps, args.warmup, torch, B, ride)
 
     # one adapter: the same batch, every token on LoRA 0 of cluster 0
@@ -592,7 +588,7 @@ def bench_layer(args, torch, np, cts, B, wl, device):
     if ride:
         gemm_kernel = "seg_gemm_dma_kernel (W X beside V_k^T X) + expand_kernel (U_k Z' added to its partials)"
     else:
-        gemm_kernel = ("prefill_gemm_kernel" if args.workload == "prefill_mix" else "seg_gemm_dma_kernel") + \
+        gemm_kernel = ("prefill_gemm_kernel" if tile[:2] == (256, 256) else "seg_gemm_dma_kernel") + \
             " (fused W X + U_k Z')"
     roof.update({"kernel": gemm_kernel, "mean_us": round(gemm_us, 2),
                  "event_interval_us": round(g_int, 2), "marker_us": round(g_mark, 2),

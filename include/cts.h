@@ -129,6 +129,18 @@ size_t cts_workspace_size_uncompressed(const cts_problem* p);
  * the bucketing of the one before). */
 int cts_workspace_bucketing(const cts_problem* p, int32_t compressed, size_t* offsets);
 
+/* Debugging aid: the kernel that forms the dense product of a call with
+ * problem `p` (compressed, M, d_out: the call's; M == 0 for the calls of one
+ * module, else those of cts_apply_multi), chosen from the sizes alone:
+ *   plan[0], plan[1]  output rows and tokens of a workgroup's tile
+ *   plan[2]           pieces the reduction over d_in is split into
+ *   plan[3]           0: U_k Z' is added by the same kernel, a launch per module
+ *                     1: the same, every module in one launch
+ *                     2: W X runs beside the shrink (small bf16 batches)
+ * `plan` is a host array of 4 entries (M > 1 without a common launch: module
+ * 0's).  T > 8192: the largest piece's.  Errors as for the call's sizes. */
+int cts_layer_plan(const cts_problem* p, int32_t compressed, int32_t M, const int32_t* d_out, int32_t* plan);
+
 /* Token bucketing (the grouping of tokens by cluster that makes the shared-
  * basis products contiguous GEMMs; Sec. 3.2 gives every LoRA of a cluster the
  * same U_k, V_k).  Sorts the tokens by the key (cluster_of[adapter_id[t]],

@@ -47,7 +47,8 @@ EXPORTED = ("cts_status_string", "cts_workspace_size", "cts_workspace_size_uncom
             "cts_sort_by_cluster", "cts_apply", "cts_apply_diag", "cts_apply_ranked",
             "cts_apply_uncompressed", "cts_apply_uncompressed_ranked", "cts_validate_ids",
             "cts_set_stage_events", "cts_workspace_size_multi", "cts_apply_multi", "cts_apply_noalloc",
-            "cts_workspace_bucketing", "cts_bucketing_size", "cts_apply_multi_sorted", "cts_apply_multi_packed",
+            "cts_workspace_bucketing", "cts_layer_plan", "cts_bucketing_size", "cts_apply_multi_sorted",
+            "cts_apply_multi_packed",
             # include/cts_compress.h
             "cts_jd_workspace_size", "cts_jd_cluster_workspace_size", "cts_lora_norms2", "cts_jd_full",
             "cts_jd_diag", "cts_jd_sigma", "cts_jd_cluster")
@@ -92,6 +93,8 @@ def lib() -> ctypes.CDLL:
                 L.cts_workspace_size_uncompressed.restype = sz
                 L.cts_workspace_bucketing.argtypes = [pp, i32, ctypes.POINTER(sz)]
                 L.cts_workspace_bucketing.restype = ctypes.c_int
+                L.cts_layer_plan.argtypes = [pp, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+                L.cts_layer_plan.restype = ctypes.c_int
                 L.cts_sort_by_cluster.argtypes = [vp, vp, i32, i32, i32, vp, vp, vp, sz, vp]
                 L.cts_sort_by_cluster.restype = ctypes.c_int
                 L.cts_bucketing_size.argtypes = [i32, i32, i32]
@@ -220,6 +223,17 @@ def workspace_bucketing(p: Problem, compressed: bool = True) -> dict:
     offs = (ctypes.c_size_t * 5)()
     _check(lib().cts_workspace_bucketing(ctypes.byref(p), 1 if compressed else 0, offs), "cts_workspace_bucketing")
     return dict(zip(("perm", "seg", "aid", "items", "n_items"), (int(v) for v in offs)))
+
+
+def layer_plan(p: Problem, compressed: bool = True, d_outs=None) -> tuple:
+    """(rows, tokens, pieces, how) of the dense product of a call with problem p
+    (d_outs: the modules' widths of a multi-module call), how in "fused",
+    "grouped", "beside the shrink" (cts_layer_plan)."""
+    M = 0 if d_outs is None else len(d_outs)
+    out = (ctypes.c_int32 * 4)()
+    _check(lib().cts_layer_plan(ctypes.byref(p), 1 if compressed else 0, M, (ctypes.c_int32 * M)(*d_outs) if M else None,
+                                out), "cts_layer_plan")
+    return out[0], out[1], out[2], ("fused", "grouped", "beside the shrink")[out[3]]
 
 
 def bucketing_size(T: int, n: int, K: int) -> int:

@@ -955,6 +955,23 @@ size_t cts_workspace_size_multi(const cts_problem* p, int32_t M, const int32_t* 
   return make_multi_plan(p, M, d_out, &mp) == CTS_OK ? mp.total : 0;
 }
 
+int cts_layer_plan(const cts_problem* p, int32_t compressed, int32_t M, const int32_t* d_out, int32_t* plan) {
+  if (!plan || M < 0 || (M > 0 && !compressed)) return CTS_ERR_INVALID_ARG;
+  MultiPlan mp{};
+  const int rc = M > 0 ? make_multi_plan(p, M, d_out, &mp) : make_plan(p, compressed != 0, &mp.mod[0]);
+  if (rc != CTS_OK) return rc;
+  const Plan& pl = mp.mod[0];
+  const bool small = M > 0 ? mp.small : pl.small_split > 0;
+  const Tile t = small ? cts::Tile::Shrink : mp.grouped ? mp.g_tile : pl.main_tile;
+  int BM, BN, BK;
+  cts::tile_dims(t, &BM, &BN, &BK);
+  plan[0] = BM;
+  plan[1] = BN;
+  plan[2] = M > 0 && (small || mp.grouped) ? mp.g_split : small ? pl.small_split : pl.main_split;
+  plan[3] = small ? 2 : mp.grouped ? 1 : 0;
+  return CTS_OK;
+}
+
 namespace {
 
 // The checks of cts_apply_multi and cts_apply_multi_sorted: either the ids

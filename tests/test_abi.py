@@ -555,3 +555,22 @@ def test_workspace_of_a_batch_serves_every_smaller_one(kw):
     for name, s in sizes.items():
         assert s[1] > 0 and s == sorted(s), name
     assert sizes["single"][-1] <= B.NOALLOC_SCRATCH_BYTES
+
+
+def test_layer_plan():
+    """The chosen tile, on the host: small batches, one launch for several
+    modules, the sizes a call would refuse."""
+    assert cts.layer_plan(_p(T=64)) == (64, 64, 3, "beside the shrink")
+    assert cts.layer_plan(_p(T=64), compressed=False) == (64, 64, 3, "beside the shrink")
+    assert cts.layer_plan(_p(T=64, d_out=16392)) == (64, 64, 1, "fused")
+    assert cts.layer_plan(_p(T=64, dtype=B.CTS_F32, out_dtype=B.CTS_F32))[3] == "fused"
+    assert cts.layer_plan(_p(T=4096, n_clusters=25)) == (256, 256, 1, "fused")
+    assert cts.layer_plan(_p(T=33), d_outs=(4096, 1024, 1024))[3] == "beside the shrink"
+    assert cts.layer_plan(_p(T=512), d_outs=(4096, 1024, 1024))[3] == "grouped"
+    assert cts.layer_plan(_p(T=9000)) == cts.layer_plan(_p(T=4500))
+    plan = (ctypes.c_int32 * 4)()
+    f = cts.lib().cts_layer_plan
+    assert f(ctypes.byref(_p(r=12)), 1, 0, None, plan) == B.CTS_ERR_UNSUPPORTED
+    assert f(ctypes.byref(_p()), 1, 0, None, None) == B.CTS_ERR_INVALID_ARG
+    assert f(None, 1, 0, None, plan) == f(ctypes.byref(_p()), 1, 2, None, plan) == B.CTS_ERR_INVALID_ARG
+    assert f(ctypes.byref(_p()), 0, 1, (ctypes.c_int32 * 1)(64), plan) == B.CTS_ERR_INVALID_ARG
