@@ -785,13 +785,12 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
 // the 128 accumulators, so nothing spills.
 // The adapter phase is a list of (run, unit) entries in LDS, uniform or mixed
 // ranks alike: one 8-byte read per unit, a unit ahead of its loads.
-// The waits and the barrier leave 16% of the matrix-core slots unused; the
-// clock is 1.74 GHz, held down by power (1.98 GHz with the ring's loads left
-// out), so the rest costs more time than it looks.  The setup before the loop
-// holds no wait for the weights in flight and one round trip for the tokens
-// (6.0 -> 3.7 us), and the output leaves as whole rows (8.7 -> 5.0 us).
-// T = 4096, 4096 x 4096, 17 clusters of rank 64: 124 -> 112 us a launch; the
-// two-stage 64-deep ring it replaces ran at 1315 cycles a unit, this at 1220.
+// The setup before the loop holds no wait for the weights in flight and one
+// round trip for the tokens, and the output leaves as whole rows.
+// T = 4096, 4096 x 4096, 25 clusters of rank 64, against the two-stage 64-deep ring
+// it replaces: 116 -> 111 us a launch with the weights in the last-level cache,
+// 119 -> 118 from HBM.  PAIR (rows that start between multiples of 64 bytes):
+// launch_prefill says why.
 struct PrefillCfg {
   static constexpr int BM = 256, BN = 256, BK = 32, NT = 512, P = 4;   // eight waves, 4 x 2
   static constexpr int ROWB = BK * 2, SB = (BM + BN) * ROWB;
@@ -801,6 +800,7 @@ struct PrefillCfg {
   static constexpr int MAXU = 4;                      // adapter units per run: rank <= 128
 };
 
+template <bool PAIR>
 __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p) {
   using C = PrefillCfg;
   using MT = MfmaTraits<bf16_t, 16>;
@@ -881,7 +881,7 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
   for (int j = 0; j < 2; ++j)
     b0_v[j] = lrow + 128 * j < jn ? b0_v[j] * static_cast<uint32_t>(p.ldb0) * 2 + cbytes : kOob;
 #pragma unroll
-  for (int u = 0; u < C::P - 1; ++u)                  // (unit 3's go out in unit 0)
+  for (int u = 0; u < (PAIR ? C::P : C::P - 1); ++u)  // (one by one, unit 3's go out in unit 0)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
       load16_lds(rB0, smem_b + u * C::SB + j * 8192, b0_v[j], static_cast<uint32_t>(u * C::ROWB));
@@ -1016,9 +1016,9 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
     lds_read16_at<(S & 1) * C::SB + (4 * H + I) * 16 * C::ROWB>(fb[H][I], b_addr[S >> 1]);
   };
 
-  // ---- prologue: units 0 .. 2 and the weights of unit 3 in flight, unit 0's
-  // first fragments
-  wait_vmcnt<4>();                                    // the token loads of units 1 and 2
+  // ---- prologue: units 0 .. 2 and the weights (PAIR: all) of unit 3 in flight,
+  // unit 0's first fragments
+  wait_vmcnt<PAIR ? 6 : 4>();                         // the token loads of units 1 and 2 (and 3)
   __builtin_amdgcn_s_barrier();
   uint32_t n_sched_v;
   lds_read4(n_sched_v, count_addr);
@@ -1038,14 +1038,23 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
   // the weight loads of unit u + 4 into the slot just freed: the loads are
   // spread over the unit, since eight waves issuing theirs at once fill the
   // load queue and hold up the MFMAs behind it.
+  // PAIR: the second half of an odd unit issues every load of units u + 3 and
+  // u + 4, into the slots of u - 1 and of u, a row's two pieces one after the
+  // other (tokens first: weights first took 1 to 5 us longer).
   auto unit = [&](auto slot_c, auto fast_c, int u) __attribute__((always_inline)) {
     constexpr int S = decltype(slot_c)::value;
-    constexpr bool FAST = decltype(fast_c)::value;
+    constexpr bool FAST = decltype(fast_c)::value, ODD = S & 1;
     constexpr int SN = (S + 1) & 3, SP = (S + 3) & 3, PA = S & 1;
-    uint64_t entry = 0;
+    uint64_t entry = 0, entry2 = 0;
+    UnitLoad L2;                                      // (of unit u + 4; L of u + 3 while they are issued)
     auto load = [&](int uu, int slot, int j) __attribute__((always_inline)) {
       if (FAST) issue_fast(uu, slot, j);
       else issue(L, slot, j);
+    };
+    auto load_pair = [&](int h, int j) __attribute__((always_inline)) {
+      if (FAST) issue_fast(u + C::P - 1 + h, h ? S : SP, j);
+      else if (h) issue(L2, S, j);
+      else issue(L, SP, j);
     };
     wait_lgkmcnt<0>();
 #pragma unroll
@@ -1054,21 +1063,34 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
       constexpr int m = decltype(m_c)::value;
       acc[m >> 2][m & 3] = MT::mma(fa[PA][m >> 2], fb[0][m & 3], acc[m >> 2][m & 3]);
       if constexpr (m < 4) rd_b(slot_c, integral_constant<int, 1>{}, m_c);
-      if (!FAST && m == 4) read_entry(u + C::P, entry);
-      if (m == 5) load(u + C::P - 1, SP, 2);
-      if (m == 9) load(u + C::P - 1, SP, 3);
+      if (!FAST && m == 4 && (!PAIR || ODD)) read_entry(u + C::P, PAIR ? entry2 : entry);
+      if (!FAST && m == 5 && PAIR && ODD) read_entry(u + C::P - 1, entry);
+      if (!PAIR && m == 5) load(u + C::P - 1, SP, 2);
+      if (!PAIR && m == 9) load(u + C::P - 1, SP, 3);
       __builtin_amdgcn_sched_barrier(0);
     });
     wait_lgkmcnt<0>();
 #pragma unroll
     for (int i = 0; i < 4; ++i) pin(fb[1][i]);
-    if (!FAST) {
+    if (!FAST) ring_halves >>= 2;
+    if (!FAST && !PAIR) {
       pin(entry);
       L = prep(u + C::P, entry);
-      ring_halves = (ring_halves >> 2) | (L.halves << 6);
+      ring_halves |= L.halves << 6;
     }
-    if (S == 0 && u == 0) wait_vmcnt<4>();            // the prologue's order: weights, then tokens
-    else if (S == 1 && u == 1) wait_vmcnt<6>();
+    if (!FAST && PAIR && ODD) {
+      pin(entry);
+      pin(entry2);
+      L = prep(u + C::P - 1, entry);
+      L2 = prep(u + C::P, entry2);
+      ring_halves |= (L.halves << 4) | (L2.halves << 6);
+    }
+    // this wave's loads of unit u + 1; u = 0 and 1 follow the prologue's order:
+    // weights, then tokens.  (PAIR: of an even unit all but the last load of its
+    // pair's, of an odd one all but the next pair's.)
+    if (PAIR && ODD) wait_vmcnt<1>();
+    else if (S == 0 && u == 0) wait_vmcnt<4>();
+    else if (!PAIR && S == 1 && u == 1) wait_vmcnt<6>();
     else wait_vmcnt<8>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
@@ -1079,8 +1101,9 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
       // (fb[0]'s last use is k = 3)
       if constexpr (k < 4) rd_a(integral_constant<int, SN>{}, PA ^ 1, k_c);
       else if constexpr (k < 8) rd_b(integral_constant<int, SN>{}, integral_constant<int, 0>{}, integral_constant<int, k - 4>{});
-      if (k == 10) load(u + C::P, S, 0);
-      if (k == 15) load(u + C::P, S, 1);
+      if (!PAIR && k == 10) load(u + C::P, S, 0);
+      if (!PAIR && k == 15) load(u + C::P, S, 1);
+      if constexpr (PAIR && ODD && k < 8) load_pair(k & 1, (k >> 1) ^ 2);
       __builtin_amdgcn_sched_barrier(0);
     });
   };
@@ -1093,34 +1116,46 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
     unit(integral_constant<int, 2>{}, FastT{}, u + 2);
     unit(integral_constant<int, 3>{}, FastT{}, u + 3);
   }
-  L = prep(u + C::P - 1, 0);                          // a whole dense unit, as all four in the ring
+  if (!PAIR) L = prep(u + C::P - 1, 0);               // a whole dense unit, as all four in the ring
   // Few adapter units are long runs (a prefill's requests): interleaved like the
   // dense ones.  Many are short runs: the loop below.  (T = 4096, 17 clusters,
   // up to 6 units a tile: 148.8 us a call through the loop below, 145.3 here;
   // T = 512, 4096 -> 28672, 50 clusters, some 50 units a tile: 151 us a launch
   // through the loop, 154 here.)
-  const int n_inter = n_sched <= 16 ? ntot : nd;
-  while (u < n_inter) {
+  // (PAIR: up to a whole pair; a unit past the end is masked)
+  const int n_inter = n_sched <= 16 ? ntot : PAIR ? (nd + 1) & ~1 : nd;
+  for (;;) {                                          // (four dense units at least are left)
     unit(integral_constant<int, 0>{}, AnyT{}, u);
-    if (++u >= n_inter) break;
+    if (++u >= n_inter && !PAIR) break;
     unit(integral_constant<int, 1>{}, AnyT{}, u);
     if (++u >= n_inter) break;
     unit(integral_constant<int, 2>{}, AnyT{}, u);
-    if (++u >= n_inter) break;
+    if (++u >= n_inter && !PAIR) break;
     unit(integral_constant<int, 3>{}, AnyT{}, u);
-    ++u;
+    if (++u >= n_inter) break;
   }
+  // the fragments read ahead for a unit that does not follow: waited for before
+  // their registers can be given to anything else
+  wait_lgkmcnt<0>();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { pin(fa[0][i]); pin(fa[1][i]); pin(fb[0][i]); }
   // Adapter units.  A run has few of the tile's columns, so a wave multiplies
   // only the halves of its columns that the unit's run touches and most waves
   // only load and read: the fragments are read a unit at a time (the first ones
   // again), and nothing is interleaved.
-  for (; u < ntot; ++u) {
+  if (PAIR && u < ntot) {                             // (unit u + 3's tokens go out a second time)
+    uint64_t entry = 0;
+    read_entry(u + C::P - 1, entry);
+    wait_lgkmcnt<0>();
+    pin(entry);
+    L = prep(u + C::P - 1, entry);
+  }
+  for (const int first = u; u < ntot; ++u) {
     const uint32_t so = static_cast<uint32_t>((u & 1) * C::SB);
     const uint32_t aa = a_addr[0] + static_cast<uint32_t>((u & 2) * C::SB) + so;
     const uint32_t ba = b_addr[0] + static_cast<uint32_t>((u & 2) * C::SB) + so;
     const int slot = u & 3, prev = (u + 3) & 3;
     uint64_t entry = 0;
-    wait_lgkmcnt<0>();
     read_entry(u + C::P, entry);
     unrolled<4>([&](auto i_c) __attribute__((always_inline)) {
       constexpr int I = decltype(i_c)::value;
@@ -1137,7 +1172,8 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
     const uint32_t halves = ring_halves;
     L = prep(u + C::P, entry);
     ring_halves = (ring_halves >> 2) | (L.halves << 6);
-    wait_vmcnt<8>();
+    if (PAIR && u == first + 1) wait_vmcnt<7>();      // a unit loaded with its pair: all but that one's last
+    else wait_vmcnt<8>();
     __builtin_amdgcn_s_barrier();
     issue(L, slot, 0);
     issue(L, slot, 1);
@@ -1148,7 +1184,6 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
         for (int m = 0; m < 16; ++m)
           acc[m >> 2][4 * h + (m & 3)] = MT::mma(fa[0][m >> 2], fb[h][m & 3], acc[m >> 2][4 * h + (m & 3)]);
   }
-  wait_lgkmcnt<0>();
   wait_vmcnt<0>();
   __syncthreads();
 
@@ -1204,7 +1239,16 @@ hipError_t launch_prefill(const GemmParams& p, hipStream_t stream) {
   const int gn = (p.N + C::BN - 1) / C::BN;
   GemmParams q = p;
   q.group_m = xcd_group_m(gm, gn, 1);
-  hipLaunchKernelGGL(prefill_gemm_kernel, dim3(gm * gn), dim3(C::NT), 0, stream, q);
+  // A unit takes 64 bytes of a row.  In rows that do not start at a multiple of
+  // 64 bytes these pieces straddle cache lines: 1.4 requests each, which weights
+  // read from HBM feel (from the last-level cache they do not).  A pair's two
+  // pieces together are two lines, but go out later: 2777 tokens, 3000 -> 5000,
+  // cold 121 us a launch one by one and 107 in pairs, 2560 tokens, 4104 -> 5120
+  // 153 and 131, 4096 tokens, 3000 -> 8192 211 and 191 (the two-stage 64-deep ring
+  // before this one: 108, 128 and 202); aligned rows one by one, since 700
+  // tokens, 4096 -> 14336 take 96 us from the last-level cache and 105 in pairs.
+  if (p.K0 % 32) hipLaunchKernelGGL(prefill_gemm_kernel<true>, dim3(gm * gn), dim3(C::NT), 0, stream, q);
+  else hipLaunchKernelGGL(prefill_gemm_kernel<false>, dim3(gm * gn), dim3(C::NT), 0, stream, q);
   return hipGetLastError();
 }
 
