@@ -305,8 +305,9 @@ int cts_validate_ids(const cts_problem* p, const int32_t* adapter_id,
  *   [4] after the fused GEMM          [5] after the split-K reduction
  *                                         (right after [4] when there is none)
  * For small bf16 batches the dense product W X runs in the shrink's launch and
- * [3] to [4] holds the kernel that adds U_k Z' to it; without a full core
- * [2] and [3] are recorded back to back.
+ * [3] to [4] holds the kernel that adds U_k Z' to it; where that kernel also
+ * stands in for the core product (diagonal or none, by sizes) [2] and [3] are
+ * recorded back to back.
  * The setting is process-wide; changing it while another thread is inside a
  * cts_apply call is a race. */
 #define CTS_N_STAGE_EVENTS 6

@@ -131,6 +131,23 @@ int small_split_of(int dtype, int T, int row_tiles, int d_in) {
   return std::max(1, std::min(std::min(small_cap(d_in), 256 / tiles), ceil_div(d_in, 64) / 4));
 }
 
+// Without a full core a small batch's last kernel can sum the shrink's pieces
+// itself: no core launch (1.9 us), but each of its waves reads all pieces of its
+// 16 positions, ceil(r / 32) times four pieces a round trip (0.30 us each), and
+// all waves together r floats per piece and position (0.043 us per MB).  Fitted to
+// 376 calls both ways (diagonal cores and LoRAs, ranks 32 to 128, 1 to 128 tokens,
+// 256 x 256 to 14336 x 4096): within 0.4% of the better one on average; always
+// summing there took up to 1.33 times as long (2048 -> 8192, rank 128 at 128
+// tokens: 42.1 us, 31.6 with the core launch), never 1.22 (256 x 256).
+bool fold_pays(int T, int rank, int nseg, int d_in, int d_out) {
+  const int tiles = ceil_div(rank, 64) * std::max(ceil_div(T, 64), std::min(nseg, T));
+  const ShrinkSplit rule = shrink_rule(CTS_BF16, T, true);
+  const int S = std::max(1, std::min(ceil_div(rule.target, tiles), ceil_div(d_in, 64) / rule.kmin));
+  const double trips = ceil_div(rank, 32) * ceil_div(S, 4);
+  const double waves = 4.0 * ceil_div(d_out, 64) * ceil_div(T, 16);
+  return 0.30 * trips + 0.043e-6 * (16.0 * rank * 4 * S * waves) < 1.9;
+}
+
 // What the partials of any batch of up to T tokens can need, in bytes.  Fewer
 // tokens are split into more pieces (a batch of 77 into four where one of 256 is
 // not split), so the need itself goes up and down with T; a workspace is
@@ -425,12 +442,13 @@ int run_layer(const cts_problem* p, const Plan& pl, bool compressed, const void*
   e = cts::launch_seg_gemm(g, p->dtype, pl.shrink_tile, stream);
   if (e != hipSuccess || mark(2, stream) != hipSuccess) return CTS_ERR_HIP;
 
-  // without a full core, a small batch's last kernel takes the shrink's pieces itself
-  const bool fold = pl.small_split > 0 && (!compressed || sigma_diag);
+  // without a full core, a small batch's last kernel may take the shrink's pieces itself
+  const bool fold = pl.small_split > 0 && (!compressed || sigma_diag) &&
+                    fold_pays(T, rank, pl.nseg, p->d_in, p->d_out);
   if (!fold)
     e = cts::launch_sigma(zpart, pl.shrink_split, T, rank, said, p->n_adapters, items, n_items,
                           pl.max_items, compressed ? Sigma : nullptr, zp, p->dtype, stream, sigma_diag,
-                        sseg, seg_rank, seg_rank ? srank : nullptr, 0, ssplit, nullptr, 0, iaid);
+                          sseg, seg_rank, seg_rank ? srank : nullptr, 0, ssplit, nullptr, 0, iaid);
   if (e != hipSuccess || mark(3, stream) != hipSuccess) return CTS_ERR_HIP;
 
   if (pl.small_split > 0) {

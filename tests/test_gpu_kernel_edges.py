@@ -248,3 +248,23 @@ def test_overflow_below_the_rank_stays_an_infinity(T):
     y = host(cts.apply_ranked(x, aid, cof, W, U, Vt, S, rk))
     assert np.isposinf(y[1]).all()
     assert (np.delete(y, 1, 0) == 64.0).all()      # V^T x = 1, Sigma z = 8, U z' = 64, all exact
+
+
+@pytest.mark.parametrize("T,d_in,d_out,r,K", [
+    (3, 4104, 136, 128, 2),       # eight pieces of rank 128: the core launch sums them
+    (3, 4104, 136, 8, 2),         # of rank 8: the last kernel does
+    (128, 2056, 4104, 64, 3),     # four pieces read by 2080 waves: the core launch
+    (128, 2056, 264, 64, 3),      # by 160 waves: the last kernel
+])
+def test_small_batches_without_a_full_core(oracle_mod, T, d_in, d_out, r, K):
+    """Both routes of diagonal cores and of LoRAs, uniform and mixed ranks."""
+    w = wl.synthetic("nocore", cfg=5300 + T + r + d_out, T=T, d_in=d_in, d_out=d_out, r=r, n=K, K=K, r_l=r, ids="uniform")
+    sg, rk = wl.sigma_diagonals(5300 + T, K, r, "bf16"), wl.mixed_ranks(5300 + T, K, r, lo=8)
+    say("no full core T=%d %dx%d r=%d" % (T, d_in, d_out, r))
+    x, aid, cof, W = [dev(v) for v in (w.x, w.adapter_id, w.cluster_of, w.W)]
+    yd = cts.apply_diag(x, aid, cof, W, dev(w.U), dev(w.Vt), dev(sg))
+    yu = cts.apply_uncompressed(x, aid, W, dev(w.A), dev(w.B))
+    yr = cts.apply_uncompressed_ranked(x, aid, W, dev(w.A), dev(w.B), dev(rk))
+    assert row_rel_err(host(yd), oracle_mod.apply_diag(w.x, w.adapter_id, w.cluster_of, w.W, w.U, w.Vt, sg)) <= TOL["bf16"]
+    assert row_rel_err(host(yu), oracle_mod.apply_uncompressed(w.x, w.adapter_id, w.W, w.A, w.B)) <= TOL["bf16"]
+    assert row_rel_err(host(yr), oracle_mod.apply_uncompressed_ranked(w.x, w.adapter_id, w.W, w.A, w.B, rk)) <= TOL["bf16"]
