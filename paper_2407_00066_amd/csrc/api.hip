@@ -263,10 +263,19 @@ int plan_piece(const cts_problem* p, bool compressed, Plan* pl) {
   // units, at least four k-tiles each (partials summed afterwards)
   if (p->dtype == CTS_F32) {
     // 64x64 tiles, three to a compute unit: a round of 768 (500 tokens, 1024 ->
-    // 2816, 352 tiles: 70 us a call unsplit, 63 in two pieces; 64 tokens, 2048 ->
-    // 2048, 32 tiles: 83 and 33 in eight)
+    // 2816, 352 tiles: 70 us a call unsplit, 59 in two pieces; 64 tokens, 2048 ->
+    // 2048, 32 tiles: 92 and 31 in eight).  Of large outputs a piece must be worth
+    // its partials' way through memory, 12 k-tiles with those of a tile's cluster
+    // runs: 1000 tokens, 256 -> 1024 take 34 us unsplit and 40 in two pieces of four
+    // k-tiles, but 1100 tokens over 200 LoRAs, 512 -> 1024 (12 runs a tile) 68 and 61;
+    // half as many outputs the same either way.
     pl->main_tile = Tile::F32;
     pl->main_split = tile_split(Tile::F32, T, p->d_in, p->d_out, kF32Round, kF32MaxSplit);
+    if (static_cast<int64_t>(T) * p->d_out >= 9 << 16) {
+      const int runs = 1 + std::min(pl->nseg, T) / ceil_div(T, 64);
+      const int ktiles = ceil_div(p->d_in, 32) + runs * ceil_div(pl->rank, 32);
+      pl->main_split = std::max(1, std::min(pl->main_split, ktiles / 12));
+    }
   } else if (T <= 64) {
     pl->main_tile = Tile::Decode;
     pl->main_split = tile_split(Tile::Decode, T, p->d_in, p->d_out, 256, kDecodeMaxSplit);
