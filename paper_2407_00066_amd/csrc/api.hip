@@ -83,18 +83,20 @@ int tile_split(Tile t, int T, int d_in, int d_out, int round, int cap) {
 // The fused GEMM's tile for bf16 batches of more than 64 tokens is the one
 // whose rounds over the 256 compute units are estimated shortest.  A round
 // takes `fixed` us (setup and output) and `per64` us for 64 of the reduction
-// with every compute unit busy, down to 0.7 of that with few; a cluster run
-// costs a workgroup ceil(r / 64) such steps, and a prefill has few runs (its
-// tokens come in requests).  A split adds its partials' way through memory.
-// From a sweep of every tile over 45 shapes (T 192 .. 4096 of 4096 -> 1024,
-// 4096, 6144, 14336, 28672, 14336 -> 4096, 2048 -> 2048, 8192): the choice is
-// the fastest tile or within 5% of it.  Lines drawn by batch size alone took
-// 256x256 from 2048 tokens on: 4096 tokens, 4096 -> 1024 79 us against 37 with
-// 128x128; 2048 tokens, 14336 -> 4096 328 against 211 with 256x128.
-struct TileCost { Tile tile; int max_split; double fixed, per64; };
-constexpr TileCost kTileCosts[] = {
-    {Tile::Large, 1, 8.0, 1.50}, {Tile::Wide, 8, 6.0, 0.83}, {Tile::Mid, 8, 5.0, 0.52}, {Tile::Narrow, 8, 4.0, 0.45}};
-constexpr int kPrefillT = 2048;
+// with every compute unit busy, down to 0.55 of that with few; a cluster run
+// costs a workgroup its whole k-tiles, `run` times a dense one's.  The ids are
+// not known here: half of the clusters that could meet in a tile are counted.  A
+// split adds its partials' way through memory.
+// Fitted to each tile's time in 1293 calls: T 65 .. 8192, 256 -> 256 to 14336 ->
+// 4096 and 4096 -> 28672, some sizes no multiple of 64, ranks 16 to 128, 1 to 500
+// clusters or LoRAs, uniform, Zipf and request-wise ids.  The choice takes 0.7%
+// longer than the fastest tile on average; the worst are Zipf batches over 500
+// LoRAs (1200 tokens, 4096 x 4096: 161 us with 256x128, 133 with 128x128).
+// Lines drawn by batch size alone took 256x256 from 2048 tokens on: 4096 tokens,
+// 4096 -> 1024 79 us against 37 with 128x128.
+struct TileCost { Tile tile; int max_split; double fixed, per64, run; };
+constexpr TileCost kTileCosts[] = {{Tile::Large, 1, 13.02, 1.524, 0.763}, {Tile::Wide, 8, 6.66, 0.854, 0.858},
+                                   {Tile::Mid, 8, 5.35, 0.488, 1.072},    {Tile::Narrow, 8, 3.13, 0.424, 0.801}};
 constexpr int kF32Round = 768, kF32MaxSplit = 8, kDecodeMaxSplit = 4;
 
 // 0: the tile does not take this reduction
@@ -108,11 +110,10 @@ double tile_us(const TileCost& tc, int T, int d_in, int d_out, int rank, int nse
   *split = s;
   const int64_t wgs = tiles * s, rounds = (wgs + 255) / 256;
   const double fill = static_cast<double>(wgs) / static_cast<double>(256 * rounds);
-  const double runs = T < kPrefillT ? 1.0 + static_cast<double>(std::min(nseg, T)) / nt : 0.0;
-  // (256x256 multiplies only the 64-column parts that a run touches)
-  const double steps = (d_in / 64.0 + (tc.tile == Tile::Large ? 0.85 : 1.0) * runs * rank / 64.0) / s;
-  double us = rounds * (tc.fixed + tc.per64 * (0.7 + 0.3 * fill) * steps);
-  if (s > 1) us += 3.0 + 8.0 * s * T * d_out / 5e6;       // written and read once at 5 TB/s
+  const double runs = 1.0 + 0.492 * static_cast<double>(std::min(nseg, T)) / nt;
+  const double steps = (d_in / 64.0 + tc.run * runs * (ceil_div(rank, BK) * BK / 64.0)) / s;
+  double us = rounds * (tc.fixed + tc.per64 * (0.55 + 0.45 * fill) * steps);
+  if (s > 1) us += 2.78 + 8.0 * s * T * d_out / 11.4e6;   // written and read once
   return us;
 }
 

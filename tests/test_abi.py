@@ -574,3 +574,17 @@ def test_layer_plan():
     assert f(ctypes.byref(_p()), 1, 0, None, None) == B.CTS_ERR_INVALID_ARG
     assert f(None, 1, 0, None, plan) == f(ctypes.byref(_p()), 1, 2, None, plan) == B.CTS_ERR_INVALID_ARG
     assert f(ctypes.byref(_p()), 0, 1, (ctypes.c_int32 * 1)(64), plan) == B.CTS_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("T,d_in,d_out,r,K,tile", [
+    (160, 1024, 1024, 128, 50, (128, 64)),        # 44.5 us with 128x128, 39.9
+    (192, 1024, 512, 128, 50, (128, 64)),         # 42.4 with 128x128, 38.0
+    (350, 4096, 4096, 128, 50, (256, 128)),       # 72.9 with 128x128, 68.7
+    (512, 4096, 28672, 64, 50, (256, 256)),       # 205 with 256x128, 170
+    (700, 2048, 16384, 128, 50, (256, 128)),      # 150 with 256x256, 128
+    (4096, 4096, 14336, 64, 25, (256, 256)),      # 495 with 256x128, 467
+])
+def test_layer_plan_by_the_measured_times(T, d_in, d_out, r, K, tile):
+    """Sizes at which the tiles differ and an estimate must not drift (Zipf or
+    uniform ids over 1000 LoRAs)."""
+    assert cts.layer_plan(_p(T=T, d_in=d_in, d_out=d_out, r=r, n_adapters=1000, n_clusters=K))[:2] == tile

@@ -79,9 +79,9 @@ def _same(y, want, rows, dtype=BF16):
     (2304, 3008, 5000, 64, 900, 60, "uniform"),   # aligned rows, whole units, many runs
     (2305, 3008, 5000, 24, 90, 3, "prompts"),     # a column tile of one token
     (4096, 128, 8192, 64, 200, 20, "uniform"),    # exactly four dense units: no whole round of the ring
-    (4100, 136, 8200, 40, 200, 20, "uniform"),    # five, the last of 8; a row tile of 8 rows
-    (4100, 152, 8200, 8, 20, 1, "prompts"),       # one run of one unit over every tile
-    (4096, 288, 8200, 16, 400, 70, "uniform"),    # nine dense units, some five runs of one unit a tile
+    (4090, 136, 16136, 40, 200, 8, "uniform"),    # five, the last of 8; a row tile of 8 rows
+    (4090, 152, 14344, 8, 20, 1, "prompts"),      # one run of one unit over every tile
+    (4096, 288, 16392, 16, 400, 70, "uniform"),   # nine dense units, some five runs of one unit a tile
 ])
 def test_prefill_tile(T, d_in, d_out, r, n, K, ids):
     w = Layer(7000 + T + d_in + r, T, d_in, [d_out], r, n, K, ids)
