@@ -738,7 +738,13 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   };
   for (; t < nfast; ++t) ktile(true);
   for (; t < ntiles; ++t) ktile(false);
+  // (the fragments read ahead for a k-tile that does not follow keep their
+  // registers until they are there)
   wait_lgkmcnt<0>();
+#pragma unroll
+  for (int i = 0; i < C::FM; ++i) pin(fa[0][i]);
+#pragma unroll
+  for (int j = 0; j < C::FN; ++j) pin(fb[0][j]);
   wait_vmcnt<0>();
   __syncthreads();
 
