@@ -424,7 +424,7 @@ int run_layer(const cts_problem* p, const Plan& pl, bool compressed, const void*
   cts::GemmParams g{};
   g.M = rank; g.N = T;
   g.A0 = nullptr; g.K0 = 0;
-  g.A1 = Vbasis; g.seg_stride_a1 = static_cast<int64_t>(rank) * p->d_in; g.lda1 = p->d_in;
+  g.A1 = Vbasis; g.lda1 = p->d_in;
   g.B1 = x; g.ldb1 = p->d_in; g.K1 = p->d_in; g.b1_gather = 1;
   g.a0_bytes = 0; g.b0_bytes = 0;
   g.a1_seg_bytes = static_cast<uint32_t>(static_cast<uint64_t>(rank) * p->d_in * pl.elt);
@@ -485,7 +485,7 @@ int run_layer(const cts_problem* p, const Plan& pl, bool compressed, const void*
   cts::GemmParams f{};
   f.M = p->d_out; f.N = T;
   f.A0 = W; f.lda0 = p->d_in; f.B0 = x; f.ldb0 = p->d_in; f.K0 = p->d_in;
-  f.A1 = Ubasis; f.seg_stride_a1 = static_cast<int64_t>(p->d_out) * rank; f.lda1 = rank;
+  f.A1 = Ubasis; f.lda1 = rank;
   f.B1 = zp; f.ldb1 = rank; f.K1 = rank; f.b1_gather = 0;
   f.a0_bytes = static_cast<uint32_t>(static_cast<uint64_t>(p->d_out) * p->d_in * pl.elt);
   f.b0_bytes = static_cast<uint32_t>(static_cast<uint64_t>(T) * p->d_in * pl.elt);
@@ -831,7 +831,7 @@ int run_multi(const cts_problem* p, const MultiPlan& mp, const int32_t* d_out, c
   cts::GemmParams g{};
   g.M = rt; g.N = T;
   g.A0 = nullptr; g.K0 = 0;
-  g.A1 = Vt; g.seg_stride_a1 = static_cast<int64_t>(rt) * p->d_in; g.lda1 = p->d_in;
+  g.A1 = Vt; g.lda1 = p->d_in;
   g.B1 = x; g.ldb1 = p->d_in; g.K1 = p->d_in; g.b1_gather = 1;
   g.a0_bytes = 0; g.b0_bytes = 0;
   g.a1_seg_bytes = static_cast<uint32_t>(static_cast<uint64_t>(rt) * p->d_in * pl.elt);
@@ -954,7 +954,7 @@ int run_multi(const cts_problem* p, const MultiPlan& mp, const int32_t* d_out, c
     cts::GemmParams f{};
     f.M = dm; f.N = T;
     f.A0 = W[m]; f.lda0 = p->d_in; f.B0 = x; f.ldb0 = p->d_in; f.K0 = p->d_in;
-    f.A1 = U[m]; f.seg_stride_a1 = static_cast<int64_t>(dm) * r; f.lda1 = r;
+    f.A1 = U[m]; f.lda1 = r;
     f.B1 = zp + static_cast<size_t>(m) * r * pl.elt; f.ldb1 = rt; f.K1 = r; f.b1_gather = 0;
     f.a0_bytes = static_cast<uint32_t>(static_cast<uint64_t>(dm) * p->d_in * pl.elt);
     f.b0_bytes = static_cast<uint32_t>(static_cast<uint64_t>(T) * p->d_in * pl.elt);

@@ -9,7 +9,6 @@ namespace cts {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // bfloat16 storage type: raw bits, converted explicitly.
 struct bf16_t { uint16_t bits; };
@@ -73,7 +72,7 @@ constexpr int kMaxGemmModules = 8;
 // out[j][m] (m < M rows of the weight operand, j < N sorted token positions) =
 //     sum_k A0[m][k] * B0[map(j)][k]                       (dense phase, K0)
 //   + sum_k A1_{seg(j)}[m][k] * B1[map1(j)][k]             (segment phase, K1)
-// where seg(j) = sorted_seg[j] and A1_s = A1 + s * seg_stride_a1.
+// where seg(j) = sorted_seg[j] and A1_s lies s * a1_seg_bytes past A1.
 // map(j) = perm[j]; map1(j) = perm[j] if b1_gather else j.
 // Output: part != null -> fp32 partials part[ks][j][m] for split ks;
 //         else out[perm[j]][m] (out_perm) or out[j][m], element type out_dtype.
@@ -82,7 +81,7 @@ constexpr int kMaxGemmModules = 8;
 struct GemmParams {
   int M, N;
   const void* A0; int64_t lda0; const void* B0; int64_t ldb0; int K0;
-  const void* A1; int64_t seg_stride_a1; int64_t lda1; const void* B1; int64_t ldb1; int K1;
+  const void* A1; int64_t lda1; const void* B1; int64_t ldb1; int K1;
   uint32_t a0_bytes, b0_bytes, a1_seg_bytes, b1_bytes;
   int b1_gather;
   const int32_t* perm;        // [N] sorted position -> token
@@ -101,7 +100,7 @@ struct GemmParams {
   // [tile_start[t], tile_start[t+1]) (at most the tile width); n_tiles[0]
   // tiles exist and the grid is sized for max_tiles (the rest exit at once)
   const int32_t* tile_start; const int32_t* n_tiles; int max_tiles;
-  // optional segment of each explicit tile (else sorted_seg[tile_start[t]])
+  // segment of each explicit tile
   const int32_t* tile_seg;
   // optional bucketing inside the kernel (token-tile mode, N <= kFuseSortMaxT;
   // fs_adapter != null): every workgroup sorts the N tokens by (cluster,

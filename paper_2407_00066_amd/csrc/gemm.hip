@@ -48,11 +48,9 @@ template <> struct MfmaTraits<float, 16> {       // 4 x v_mfma_f32_16x16x4_f32
   }
 };
 
-// Row of accumulator element v of lane l inside an MB x MB block (the column
-// is l % MB): 16x16 -> 4*(l/16) + v; 32x32 -> 8*(v/4) + 4*(l/32) + v%4.
-template <int MB> __device__ __forceinline__ int acc_row(int lane, int v) {
-  return MB == 16 ? 4 * (lane >> 4) + v : 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-}
+// Row of accumulator element v of lane l inside a 16 x 16 block (the column is
+// l % 16).
+__device__ __forceinline__ int acc_row(int lane, int v) { return 4 * (lane >> 4) + v; }
 
 __device__ __forceinline__ int split_lo(int n, int ks, int S) { return (int)((int64_t)n * ks / S); }
 
@@ -332,8 +330,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   int K0 = p.K0, K1 = p.K1;
   bool b0_gather = true;
   if (tlist) {
-    const int seg = FSORT ? static_cast<int>(fs_key[j0] >> fs_cshift)
-                          : (p.tile_seg ? p.tile_seg[nt] : p.sorted_seg[j0]);
+    const int seg = FSORT ? static_cast<int>(fs_key[j0] >> fs_cshift) : p.tile_seg[nt];
     A0 = static_cast<const char*>(A1v) + static_cast<int64_t>(seg) * a1_seg_bytes;
     a0_bytes = a1_seg_bytes; lda0 = p.lda1; K0 = p.K1;
     B0 = B1v; b0_bytes = b1v_bytes; ldb0 = p.ldb1; b0_gather = p.b1_gather != 0;
@@ -376,20 +373,11 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   char* const smem_b = smem + BM * C::ROWB + wave * 1024;
 
   // ---- dense k range of this split ----------------------------------------
-  const int nk0 = (K0 > 0) ? (K0 + BK - 1) / BK : 0;
-  const int nk1 = (K1 > 0) ? (K1 + BK - 1) / BK : 0;
-  // With a dense phase, split ks takes its share of the dense k-tiles and the
-  // cluster runs ks, ks + S, ks + 2S, ... (all of each run's k-tiles), so the
-  // adapter phase is spread over the splits; without one, the splits share
-  // the segment's k-tiles.
-  int d_lo = 0, d_hi = 0, s_lo = 0, s_hi = 0, q_first = 0, q_step = 1;
-  if (nk0 > 0) {
-    d_lo = split_lo(nk0, ks, S); d_hi = split_lo(nk0, ks + 1, S);
-    s_lo = 0; s_hi = nk1;
-    q_first = ks; q_step = S;
-  } else {
-    s_lo = split_lo(nk1, ks, S); s_hi = split_lo(nk1, ks + 1, S);
-  }
+  // Split ks takes its share of the dense k-tiles and the cluster runs ks, ks + S,
+  // ks + 2S, ... (all of each run's k-tiles), so the adapter phase is spread over
+  // the splits.
+  const int nk0 = (K0 + BK - 1) / BK, nk1 = (K1 + BK - 1) / BK;
+  const int d_lo = split_lo(nk0, ks, S), d_hi = split_lo(nk0, ks + 1, S);
   const int nd = d_hi - d_lo;
   // dense k-tiles that cover a whole BK slice: d_lo .. d_lo + nd_full - 1
   const int nd_full = nd - ((nd > 0 && d_hi * BK > K0) ? 1 : 0);
@@ -461,7 +449,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   }
 
   // ---- k-tile schedule: the dense tiles, then each cluster run's tiles ------
-  // Wave 0 finds this split's runs (q_first, q_first + q_step, ...) from its
+  // Wave 0 finds this split's runs (ks, ks + S, ...) from its
   // registers and lists their adapter k-tiles of this split below the run's
   // rank: low word = first column | columns << 9 | k-tile << 18, high word =
   // segment | rank << 16.
@@ -490,10 +478,9 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
         const uint64_t above = start[q] & ~(lt_mask | (1ull << lane));
         if (above) hi = 64 * q + __builtin_ctzll(above);
         const int run = run0 + __popcll(start[q] & lt_mask);
-        const bool mine = ((start[q] >> lane) & 1ull) && run >= q_first &&
-                          (q_step == 1 || (run - q_first) % q_step == 0);
+        const bool mine = ((start[q] >> lane) & 1ull) && run >= ks && (S == 1 || (run - ks) % S == 0);
         const int kl = min(max(v_rank[q], 0), K1);
-        const int c = mine ? max(0, min(s_hi, (kl + BK - 1) / BK) - s_lo) : 0;   // at most MAXE <= 4
+        const int c = mine ? min(nk1, (kl + BK - 1) / BK) : 0;   // at most MAXE <= 4
         const uint64_t b0 = __ballot(c & 1), b1 = __ballot(c & 2), b2 = __ballot(c & 4);
         const uint32_t at =
             tot + __popcll(b0 & lt_mask) + 2 * __popcll(b1 & lt_mask) + 4 * __popcll(b2 & lt_mask);
@@ -502,7 +489,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
             static_cast<uint64_t>(static_cast<uint32_t>(v_seg[q]) | (static_cast<uint32_t>(kl) << 16)) << 32;
 #pragma unroll
         for (int i = 0; i < C::MAXE; ++i)
-          if (i < c) lds_write8(sched_addr + 8u * (at + i), ey | (ex | (static_cast<uint32_t>(s_lo + i) << 18)));
+          if (i < c) lds_write8(sched_addr + 8u * (at + i), ey | (ex | (static_cast<uint32_t>(i) << 18)));
         tot += __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
         run0 += __popcll(start[q]);
       }
@@ -758,7 +745,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
     for (int i = 0; i < C::FM; ++i)
 #pragma unroll
       for (int v = 0; v < MT::NACC; v += 4) {
-        const int m = m0 + wm * C::WTM + i * MB + acc_row<MB>(lane, v);
+        const int m = m0 + wm * C::WTM + i * MB + acc_row(lane, v);
         if (!jok || m >= Mv) continue;
         const f32x4 val = f32x4{acc[i][j][v], acc[i][j][v + 1], acc[i][j][v + 2], acc[i][j][v + 3]};
         if (partv) {
@@ -1269,6 +1256,8 @@ hipError_t launch_dma1(const GemmParams& p, hipStream_t stream) {
   const bool mods = MODS && !(p.tile_start || FSORT) && p.n_mod > 0;
   if (!MODS && !DENSE && p.n_mod > 0) return hipErrorInvalidValue;
   if (!DENSE != !(p.d_blocks > 0)) return hipErrorInvalidValue;
+  // every workgroup has a dense reduction (a token tile's is its segment's)
+  if ((p.tile_start || FSORT ? p.K1 : p.K0) <= 0 || (p.tile_start && !p.tile_seg)) return hipErrorInvalidValue;
   if (mods) {
     if (p.n_mod > kMaxGemmModules || p.mod_rt[0] != 0) return hipErrorInvalidValue;
     for (int m = 0; m < p.n_mod; ++m)

@@ -33,15 +33,12 @@ def test_lora_norms2(n, r_l, d_out, d_in):
     rs = np.random.default_rng(1000 + r_l + n)
     A = rs.standard_normal((n, r_l, d_in)).astype(np.float32)
     B = rs.standard_normal((n, d_out, r_l)).astype(np.float32)
-    got = GC.lora_norms2(_f32(A), _f32(B), r=16 if n * r_l >= 16 else n * r_l).cpu().numpy().astype(np.float64) \
-        if n * r_l >= 16 else None
-    if got is None:                                # r must not exceed n r_l: pad the collection with zero LoRAs
-        k = -(-16 // r_l)
-        A2, B2 = np.zeros((k, r_l, d_in), np.float32), np.zeros((k, d_out, r_l), np.float32)
-        A2[:n], B2[:n] = A, B
-        got = GC.lora_norms2(_f32(A2), _f32(B2), r=16).cpu().numpy().astype(np.float64)
-        assert (got[n:] == 0).all()
-        got = got[:n]
+    k = max(n, -(-16 // r_l))                      # r = 16 must not exceed n r_l: pad the collection with zero LoRAs
+    A2, B2 = np.zeros((k, r_l, d_in), np.float32), np.zeros((k, d_out, r_l), np.float32)
+    A2[:n], B2[:n] = A, B
+    got = GC.lora_norms2(_f32(A2), _f32(B2), r=16).cpu().numpy().astype(np.float64)
+    assert (got[n:] == 0).all()
+    got = got[:n]
     A, B = A.astype(np.float64), B.astype(np.float64)
     want = np.array([np.linalg.norm(P) ** 2 for P in OC.products(A, B)])
     ga = np.einsum("nlc,nmc->nlm", np.abs(A), np.abs(A))
