@@ -416,17 +416,13 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
   auto edge = [&](int st) __attribute__((always_inline)) {
     return st < nd_full ? 0u : (st < nd && static_cast<uint32_t>(dk(st) * BK) + celem < static_cast<uint32_t>(K0) ? 0u : kOob);
   };
-  // (masked whole, a load takes no scalar offset: past the end of a small operand
-  // the bounds check would subtract it from less)
-  auto kof = [&](int st) __attribute__((always_inline)) {
-    return st < nd ? static_cast<uint32_t>(dk(st) * BK) * ELT : 0u;
-  };
 #pragma unroll
   for (int st = 0; st < P - 1; ++st) {
     const uint32_t m = edge(st);
 #pragma unroll
     for (int j = 0; j < C::QA; ++j)
-      load16_lds(rA0, smem_a + st * C::SB + j * C::NW * 1024, a0_v[j] | m, kof(st));
+      load16_lds(rA0, smem_a + st * C::SB + j * C::NW * 1024, a0_v[j] | m,
+                 static_cast<uint32_t>(dk(st) * BK) * ELT);
   }
   // ---- token operand rows -------------------------------------------------
 #pragma unroll
@@ -445,7 +441,8 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void seg_gemm_dma_kernel(const Gem
     const uint32_t m = edge(st);
 #pragma unroll
     for (int j = 0; j < C::QB; ++j)
-      load16_lds(rB0, smem_b + st * C::SB + j * C::NW * 1024, b0_v[j] | m, kof(st));
+      load16_lds(rB0, smem_b + st * C::SB + j * C::NW * 1024, b0_v[j] | m,
+                 static_cast<uint32_t>(dk(st) * BK) * ELT);
   }
 
   // ---- k-tile schedule: the dense tiles, then each cluster run's tiles ------
