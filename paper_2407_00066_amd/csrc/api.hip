@@ -124,12 +124,20 @@ double tile_us(const TileCost& tc, int T, int d_in, int d_out, int rank, int nse
 // 88 us in separate launches and 95 so).  More pieces than three (four past
 // d_in = 8192) cost more in partials than the shorter reduction gives: 4096 x
 // 4096 at 64 tokens 19.7, 21.4 and 21.8 us at three, four and seven.
+// Past 64 tokens a tile's reduction is the longest thing in the call: up to 160
+// tiles take two pieces, two workgroups on some compute units (128 tokens, 4104 ->
+// 5120, rank 128: 63.5 us in one piece, 53.7 in two), and a piece is no longer
+// than 8192 (128 tokens, 14336 -> 6144: 83 us riding, 60 in separate launches).
+constexpr int kTwoPieceTiles = 160;
 int small_cap(int d_in) { return std::min(d_in >= 8192 ? 4 : 3, cts::kExpandMaxSplit); }
 
 int small_split_of(int dtype, int T, int row_tiles, int d_in) {
   const int tiles = row_tiles * ceil_div(T, 64);
   if (dtype != CTS_BF16 || T < 1 || T > cts::kFuseSortMaxT || tiles > 256) return 0;
-  return std::max(1, std::min(std::min(small_cap(d_in), 256 / tiles), ceil_div(d_in, 64) / 4));
+  int pieces = std::min(small_cap(d_in), 256 / tiles);
+  if (T > 64 && tiles > 128 && tiles <= kTwoPieceTiles) pieces = 2;
+  pieces = std::max(1, std::min(pieces, ceil_div(d_in, 64) / 4));
+  return T > 64 && d_in > 8192 * pieces ? 0 : pieces;
 }
 
 // Without a full core a small batch's last kernel can sum the shrink's pieces
@@ -182,7 +190,7 @@ size_t ypart_bound(int dtype, int T, int d_in, int d_out) {
   };
   if (dtype == CTS_F32) return bound(Tile::F32, T, kF32Round, kF32MaxSplit);
   const uint64_t small = std::max(1, std::min(small_cap(d_in), ceil_div(d_in, 64) / 4));
-  size_t most = 4 * std::min(small * std::min(T, cts::kFuseSortMaxT) * d_out, uint64_t{256} * 64 * 64);
+  size_t most = 4 * std::min(small * std::min(T, cts::kFuseSortMaxT) * d_out, uint64_t{2 * kTwoPieceTiles} * 64 * 64);
   most = std::max(most, bound(Tile::Decode, std::min(T, 64), 256, kDecodeMaxSplit));
   if (T > 64)
     for (const TileCost& tc : kTileCosts) most = std::max(most, bound(tc.tile, T, 256, tc.max_split));

@@ -541,6 +541,7 @@ def test_multi_packed_validation():
     dict(d_in=4096, d_out=1024, r=128, n_adapters=100, n_clusters=1),
     dict(d_in=14336, d_out=4096, r=16, n_adapters=50, n_clusters=50),
     dict(d_in=256, d_out=264, r=72, n_adapters=8, n_clusters=3),
+    dict(d_in=512, d_out=5120, r=8, n_adapters=8, n_clusters=3),
     dict(d_in=2048, d_out=2048, r=32, n_adapters=200, n_clusters=8, dtype=B.CTS_F32, out_dtype=B.CTS_F32),
 ])
 def test_workspace_of_a_batch_serves_every_smaller_one(kw):
@@ -566,6 +567,12 @@ def test_layer_plan():
     assert cts.layer_plan(_p(T=64, dtype=B.CTS_F32, out_dtype=B.CTS_F32))[3] == "fused"
     assert cts.layer_plan(_p(T=4096, n_clusters=25)) == (256, 256, 1, "fused")
     assert cts.layer_plan(_p(T=33), d_outs=(4096, 1024, 1024))[3] == "beside the shrink"
+    # past 64 tokens: two pieces up to 160 tiles (54 us, 63 in one), no piece past
+    # 8192 (83 us, 60 in separate launches)
+    assert cts.layer_plan(_p(T=128, d_in=4104, d_out=5120, r=128)) == (64, 64, 2, "beside the shrink")
+    assert cts.layer_plan(_p(T=128, d_out=5184))[2:] == (1, "beside the shrink")
+    assert cts.layer_plan(_p(T=64, d_in=14336, d_out=6144))[3] == "beside the shrink"
+    assert cts.layer_plan(_p(T=65, d_in=14336, d_out=6144))[3] == "fused"
     assert cts.layer_plan(_p(T=512), d_outs=(4096, 1024, 1024))[3] == "grouped"
     assert cts.layer_plan(_p(T=9000)) == cts.layer_plan(_p(T=4500))
     plan = (ctypes.c_int32 * 4)()

@@ -104,6 +104,9 @@ def test_bf16_output_is_the_rounded_fp32_output(T, d_out):
     (128, 1032, 264, 16, 3),      # the last size that rides with the shrink
     (129, 136, 136, 16, 3),       # the first that does not
     (128, 64, 8200, 8, 4),        # 258 tiles: more than one round
+    (100, 1032, 5128, 16, 3),     # 162 tiles: one piece
+    (128, 1032, 5112, 16, 3),     # 160 tiles: two, the last of eight k-tiles and a half
+    (66, 32776, 72, 8, 2),        # four pieces would be longer than 8192: separate launches
 ])
 def test_small_batch_edges(oracle_mod, T, d_in, d_out, r, K):
     r = min(r, d_in, d_out)
