@@ -167,15 +167,16 @@ def copy_calibration(torch, device, nbytes=256 << 20, reps=3):
     del src, dst
 
 
-GEMM_SOURCES = [os.path.join(ROOT, "paper_2407_00066_amd", "csrc", f) for f in ("gemm.hip", "ldsdma.h")]
+GEMM_SOURCES = [os.path.join(ROOT, "paper_2407_00066_amd", "csrc", f) for f in ("gemm.hip", "ldsdma.h", "sigma.hip")]
 
 
 def traffic_from_profile(workload):
-    """HBM bytes per launch of the fused GEMM measured with rocprofv3 --pmc
+    """HBM bytes per launch of the fused GEMM (of a small batch, of W X beside the
+    shrink and the expansion together) measured with rocprofv3 --pmc
     (FETCH_SIZE + WRITE_SIZE, each scaled by the copy calibration), read from
     the committed summary of this workload; None when there is none or the
-    GEMM's sources (gemm.hip followed by ldsdma.h) have changed since the
-    counters were taken."""
+    sources (gemm.hip, ldsdma.h, sigma.hip in that order) have changed since
+    the counters were taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "traffic_seg_gemm_%s.md" % workload)
     if not os.path.exists(path):

@@ -1111,10 +1111,11 @@ __global__ __launch_bounds__(512, 1) void prefill_gemm_kernel(const GemmParams p
   }
   if (!PAIR) L = prep(u + C::P - 1, 0);               // a whole dense unit, as all four in the ring
   // Few adapter units are long runs (a prefill's requests): interleaved like the
-  // dense ones.  Many are short runs: the loop below.  (T = 4096, 17 clusters,
-  // up to 6 units a tile: 148.8 us a call through the loop below, 145.3 here;
-  // T = 512, 4096 -> 28672, 50 clusters, some 50 units a tile: 151 us a launch
-  // through the loop, 154 here.)
+  // dense ones.  Many are short runs: the loop below.  Over 21 shapes a line
+  // anywhere up to 32 units changes a launch by 1% at most (8192 tokens of 25
+  // clusters, 4096 -> 14336: 763 us at 16, 769 at 0); with every unit interleaved
+  // tiles of many runs take up to 3% longer (2777 tokens over 500 LoRAs, 3000 ->
+  // 5000: 133 and 138).
   // (PAIR: up to a whole pair; a unit past the end is masked)
   const int n_inter = n_sched <= 16 ? ntot : PAIR ? (nd + 1) & ~1 : nd;
   for (;;) {                                          // (four dense units at least are left)
