@@ -1,6 +1,6 @@
 """GPU parity of decode-sized batches (T <= 64 bf16 tokens: the bucketing
-runs inside the shrink kernel, the fused GEMM takes the 64 x 64 decode tiles
-split along d_in) through the C ABI against the oracle: every token, the
+runs inside the shrink kernel, W X rides in the same launch in one to three
+pieces of d_in, the expansion adds U_k Z') through the C ABI against the oracle: every token, the
 adapter term alone (W = 0), the three core products (full Sigma, diagonal,
 none = uncompressed), ranks that are not multiples of 16, fp32 output, a
 workspace that starts with garbage, and one workspace shared by eager calls

@@ -21,9 +21,9 @@ def _layer(name, **kw):
 
 
 def test_graph_replay_matches_eager():
-    # two layers of different shapes in one graph (the decode tiles with a
-    # 4-way k split summed in the GEMM, and the 256x256 tiles), as a decoder
-    # stack would capture them
+    # two layers of different shapes in one graph (W X beside the shrink in
+    # three pieces with the expansion after it, and 128x64 tiles after the
+    # sort), as a decoder stack would capture them
     w1, a1 = _layer("graph_a", cfg=120, T=64, d_in=2048, d_out=320, r=32, n=40, K=5)
     w2, a2 = _layer("graph_b", cfg=121, T=2100, d_in=256, d_out=296, r=16, n=30, K=4, ids="prefill",
                     n_seq=12, seq_len=(60, 300))

@@ -48,10 +48,10 @@ def test_lora_norms2(n, r_l, d_out, d_in):
 
 
 @pytest.mark.parametrize("T,d_in,d_out,r,K", [
-    (2048, 120, 256, 8, 3),       # one feature short of the prefill kernel's four k-tiles
-    (2048, 128, 264, 16, 3),      # exactly four; a row tile of 8 rows
-    (2050, 136, 248, 128, 20),    # a k tail of 8, a column tile of 2, four adapter units per run
-    (2303, 264, 40, 40, 1),       # one run over whole tiles; rank past one 32-deep unit
+    (2048, 120, 256, 8, 3),       # one k-tile, short by a block of 8
+    (2048, 128, 264, 16, 3),      # exactly one; a row tile of 8 rows
+    (2050, 136, 248, 128, 20),    # a k tail of 8, a column tile of 2, the largest rank
+    (2303, 264, 40, 40, 1),       # one run over whole tiles; a rank within one k-tile
     (2049, 248, 512, 24, 24),
     (600, 8, 264, 8, 12),         # fewer dense k-tiles than ring stages: the prologue
     (300, 72, 4096, 64, 40),      # takes adapter k-tiles
@@ -184,6 +184,8 @@ def test_grouped_prefill_tile():
                   (((d_out, d_in), 1 / 64), ((K, d_out, r), 1 / 8), ((n, r, r), 1 / 4)))
     Vt = draw(K, 2 * r, d_in, s=1 / 64)
     say("grouped prefill tile")
+    plan = cts.layer_plan(cts.make_problem(T, d_in, d_out, r=r, n_adapters=n, n_clusters=K), d_outs=[d_out, d_out])
+    assert plan == (256, 256, 1, "grouped")
     ys = cts.apply_multi(x, aid, cof, Ws, Us, Vt, Ss)
     for m in range(2):
         one = cts.apply(x, aid, cof, Ws[m], Us[m], Vt[:, m * r:(m + 1) * r].contiguous(), Ss[m], out_dtype=torch.float32)

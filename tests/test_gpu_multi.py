@@ -13,19 +13,19 @@ from _gpu_helpers import TOL, dev, host, row_rel_err, say
 pytestmark = pytest.mark.gpu
 
 CASES = {
-    # q, k, v of a decode batch: bucketing inside the shrink (T <= 128), 64x64 tiles split along d_in
+    # q, k, v of a decode batch: bucketing inside the shrink (T <= 128), W X beside it in two pieces of d_in
     "qkv_decode": dict(cfg=140, T=64, d_in=512, d_outs=(512, 128, 128), r=32, n=40, K=4),
     # mid-size batch, Zipf ids
     "qkv_mid": dict(cfg=141, T=300, d_in=256, d_outs=(256, 64, 64), r=16, n=50, K=5, ids="zipf"),
-    # gate and up of a prefill batch: 256x256 tiles
+    # gate and up of a short reduction, 128x128 tiles in one launch (test_gpu_tiles.py has the 256x256 ones)
     "gate_up_prefill": dict(cfg=142, T=2100, d_in=128, d_outs=(512, 512), r=64, n=60, K=6, ids="prefill",
                             n_seq=12, seq_len=(60, 300)),
     # fp32, ragged
     "f32_pair": dict(cfg=143, T=77, d_in=128, d_outs=(96, 64), r=16, n=10, K=3, dtype="f32"),
-    # the modules' GEMMs in one launch split along d_in (decode tile, split 4) with one split-K sum
-    # over all modules' partials
+    # the modules' W X beside the shrink, in three pieces of d_in
     "qkv_grouped_split": dict(cfg=148, T=64, d_in=2048, d_outs=(512, 128, 128), r=32, n=40, K=4),
-    # the same with 128x64 tiles (split 2), a module narrower than one row tile, Zipf ids
+    # the modules' GEMMs in one launch of 128x64 tiles, split in two along d_in with one sum over all
+    # modules' partials; a module narrower than one row tile, Zipf ids
     "mixed_grouped_split": dict(cfg=149, T=200, d_in=1024, d_outs=(256, 128, 64), r=16, n=60, K=5, ids="zipf"),
 }
 

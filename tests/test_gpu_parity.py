@@ -150,14 +150,12 @@ SMALL = {
     "bf16_ring_ragged": dict(cfg=109, T=2300, d_in=328, d_out=280, r=24, n=90, K=11, ids="prefill",
                              n_seq=20, seq_len=(40, 200)),
     "bf16_empty_clusters": dict(cfg=108, T=90, d_in=64, d_out=64, r=16, n=4, K=9),
-    # d_in >= 8192 takes the 256x128 ring tiles with an 8-way split along d_in
+    # a long reduction over few tiles: 128x64 tiles with an 8-way split along d_in
     "bf16_wide_split": dict(cfg=110, T=300, d_in=8200, d_out=264, r=32, n=40, K=6, ids="zipf"),
-    # T <= 64 takes the 64x64 decode tiles (four-stage ring, weight loads issued
-    # before the token setup): ragged d_in over two splits, and a whole-tile case
+    # W X beside the shrink (64x64 tiles) in three pieces: ragged d_in, and a whole-tile case
     "bf16_decode_ragged": dict(cfg=111, T=50, d_in=1000, d_out=200, r=32, n=20, K=3),
     "bf16_decode_split4": dict(cfg=112, T=64, d_in=2048, d_out=320, r=16, n=30, K=2),
-    # 128x128 ring tiles (at least 128 of them, too few 256x128 tiles): ragged
-    # token tail and d_in
+    # a wide output: ragged token tail and d_in
     "bf16_mid_tiles": dict(cfg=113, T=200, d_in=200, d_out=8192, r=24, n=30, K=4, ids="zipf"),
     # the largest batch, rank and LoRA rank the ABI takes (T = 8192, r = r_lora = 128), ragged
     "bf16_max_T": dict(cfg=114, T=8192, d_in=264, d_out=200, r=128, n=2000, K=40, r_l=128, ids="prefill",
@@ -205,9 +203,9 @@ def test_uncompressed_small(oracle_mod, small_cases, name):
 # the adapter term alone: W = 0, so y = U_k Sigma_i V_k^T x (resp. B_i A_i x)
 # and the error is measured against that term's own row maximum (with W the
 # adapter term is about 1/8 of the output, so an error in it would be hidden
-# by the base term's scale).  Every bf16 tile shape: Narrow, Mid, Wide with a
-# split along d_in, Large, Decode (split in four), the bucketing inside the
-# shrink (T <= 128) and the separate sort.
+# by the base term's scale).  The 128x64 tile, unsplit and with a split along
+# d_in, and W X beside the shrink; the bucketing inside the shrink (T <= 128)
+# and the separate sort (the larger tiles: test_gpu_tiles.py).
 
 ADAPTER_TERM_CASES = ["bf16_ragged", "bf16_large_tiles", "bf16_r128_zipf", "bf16_ring_ragged",
                       "bf16_wide_split", "bf16_decode_ragged", "bf16_decode_split4", "bf16_mid_tiles",
@@ -285,8 +283,8 @@ def test_tiny_exact_compressed_equals_uncompressed(oracle_mod):
 
 
 def test_split_sum_repeatable(oracle_mod, small_cases):
-    """The decode tiles split d_in four ways (fp32 partials summed in split
-    order): repeated calls on one workspace give identical bits and match
+    """W X beside the shrink is split in three pieces of d_in (fp32 partials
+    summed in order): repeated calls on one workspace give identical bits and match
     the oracle."""
     w = small_cases["bf16_decode_split4"]
     say("split-sum repeat")

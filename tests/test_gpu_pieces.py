@@ -18,7 +18,7 @@ CASES = {
     # three pieces (5462, 5462, 5461 tokens), prefill-like runs of one adapter
     "bf16_T16385": dict(cfg=170, T=16385, d_in=136, d_out=72, r=16, n=50, K=5, ids="prefill",
                         n_seq=90, seq_len=(60, 300)),
-    # two pieces of 4097 and 4096 tokens (the 256x256 tiles), Zipf ids
+    # two pieces of 4097 and 4096 tokens (128x64 tiles), Zipf ids
     "bf16_T8193": dict(cfg=171, T=8193, d_in=64, d_out=264, r=32, n=300, K=12, ids="zipf"),
     # fp32, three pieces of 6667, 6667 and 6666 tokens
     "f32_T20000": dict(cfg=172, T=20000, d_in=64, d_out=64, r=8, n=20, K=3, dtype="f32"),

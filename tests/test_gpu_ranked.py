@@ -105,8 +105,8 @@ def test_apply_ranked_prefill_full_size(oracle_mod):
 
 
 # More than 64 cluster runs in one token tile (the rank schedule is listed 64
-# runs at a time), many clusters at rank 0 or at most one k-tile: the 128x128
-# tiles (T = 512, d_out = 4096) and the 256x256 tiles (T = 2100).
+# runs at a time), many clusters at rank 0 or at most one k-tile, in 128x64
+# tiles (the larger ones: test_gpu_tiles.py).
 MANY_RUNS = {
     "many_runs_mid": dict(cfg=130, T=512, d_in=256, d_out=4096, r=64, n=600, K=400),
     "many_runs_large": dict(cfg=131, T=2100, d_in=128, d_out=256, r=128, n=900, K=500),

@@ -25,6 +25,8 @@ class Layer:
         rs = np.random.default_rng(seed)
         if ids == "prompts":
             aid = np.repeat(rs.integers(0, n, T), rs.integers(16, 200, T))[:T]
+        elif ids == "once":                       # one adapter takes the batch, every other one token
+            aid = rs.permutation(np.concatenate([np.arange(n), np.full(T - n, n // 2)]))
         else:
             aid = rs.integers(0, n, T) if ids == "uniform" else np.minimum(rs.zipf(1.3, T) - 1, n - 1)
         self.T, self.r, self.n, self.K, self.dtype, self.d_in, self.d_outs = T, r, n, K, dtype, d_in, list(d_outs)
@@ -128,6 +130,30 @@ def test_modules(T, d_in, d_outs, r, n, K, ids, plan):
         scale = w.expected(0, rows).abs().amax(1, keepdim=True)
         assert bool(torch.isfinite(y.float()).all())
         assert float(((y[rows].double() - want).abs() / scale).max()) <= TOL["bf16"], m
+
+
+@pytest.mark.parametrize("T,d_in,d_out,r,tile", [
+    (4096, 288, 16392, 16, (256, 256)),
+    (2048, 256, 8192, 64, (256, 128)),
+    (700, 264, 5000, 40, (128, 128)),
+])
+def test_adapter_term_of_many_runs(T, d_in, d_out, r, tile):
+    """More than 64 cluster runs in one tile's tokens (a tile lists them 64 at a
+    time), with W = 0: the error is then measured by the adapter term alone."""
+    n = 150
+    w = Layer(7900 + T, T, d_in, [d_out], r, n, n, "once")
+    w.W[0].zero_()
+    assert w.plan()[:2] == tile
+    seg = np.sort(w.cof.cpu().numpy()[w.aid.cpu().numpy()])
+    assert max(len(set(seg[i:i + tile[1]])) for i in range(0, T, tile[1])) > 64
+    rows = w.sample()
+    say("many runs T=%d %dx%d r=%d" % (T, d_in, d_out, r))
+    args = (w.x, w.aid, w.cof, w.W[0], w.U[0], w.Vt, w.S[0])
+    out = torch.full((T, d_out), float("nan"), dtype=BF16, device="cuda")
+    _same(cts.apply(*args, out=out), w.expected(0, rows), rows)
+    ranks = np.arange(n) % (r // 8) * 8 + 8
+    rk = torch.from_numpy(ranks.astype(np.int32)).cuda()
+    _same(cts.apply_ranked(*args, rk), w.expected(0, rows, ranks), rows)
 
 
 @pytest.mark.parametrize("T,d_in,d_out,r,K", [
