@@ -33,7 +33,9 @@
  * three events around its U step's projection (C_i = P_i S_i; P_i = A_i V
  * comes from the preceding diagonal step unless the normalization rescaled
  * V since) and expansion kernel (sum_i B_i C_i, before the sum of its
- * pieces).
+ * pieces).  The U step's Gram partials are launched before [1]; for r <= 64
+ * the r x r inverse formed from them runs in a workgroup of the expansion, so
+ * [2]..[3] holds it, and for larger r it is a launch before [1].
  */
 #ifndef CTS_COMPRESS_H
 #define CTS_COMPRESS_H
